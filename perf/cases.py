@@ -1,0 +1,289 @@
+"""The work that the performance of this library is judged on.
+
+Each case is one call of a user's program through the public binding: a
+product with a matrix it keeps, a block product, a batch of products, or the
+construction of a new matrix with its first product. The matrices are the
+families of the repository's own workloads (5-point Laplacian, 27-point
+stencil, power-law rows, few long rows) and rows of random length as in its
+tests, made on the device from the seed alone.
+
+Work counts one pass without what an implementation adds: every nonzero's
+value and column index, the vectors and (construction) the row pointers, each
+read once or written once; 2 flops per nonzero and right-hand side.
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_1307_6209_amd import sellcs
+
+VAL_BYTES = {"f64": 8, "f32": 4, "bf16": 2}
+VEC_BYTES = {"f64": 8, "f32": 4}
+POWERLAW_EXPO, POWERLAW_MAX, POWERLAW_BAND = 2.1, 10000, 1000
+
+
+def _case(name, op, matrix, rows, cols=0, row_len=0, C=32, sigma=1, val="f64", acc="f64", k=1, count=1):
+    """rows: matrix rows (batch: of the largest matrix); cols: columns (0: as
+    many as rows); row_len: mean (long rows) or longest (random) row."""
+    return {"name": name, "op": op, "matrix": matrix, "rows": rows, "cols": cols or rows, "row_len": row_len,
+            "C": C, "sigma": sigma, "val": val, "acc": acc, "k": k, "count": count}
+
+
+def listed():
+    return [
+        # a small cache-resident operator inside a solver loop: launch latency
+        _case("spmv_lap5_128", "spmv", "lap5", 128**2),
+        # the large regular operator of a 3D discretisation, double precision
+        _case("spmv_stencil27_160", "spmv", "stencil27", 160**3),
+        # the same kind of operator held in 16 bits (smoother, preconditioner), odd grid
+        _case("spmv_stencil27_131_bf16", "spmv", "stencil27", 131**3, C=64, val="bf16", acc="f32"),
+        # graph-like matrix, rows sorted globally: the layout the paper recommends for it
+        _case("spmv_powerlaw_2m", "spmv", "powerlaw", 2_000_000, sigma=2_000_000),
+        # the same sorted only in short windows (row order kept nearly): padding-heavy, FP32
+        _case("spmv_powerlaw_1m_window_f32", "spmv", "powerlaw", 999_983, sigma=1024, val="f32", acc="f32"),
+        # constraint matrix of a linear program: few, very long rows
+        _case("spmv_rail", "spmv", "rail", 4284, cols=1_092_610, row_len=2633, sigma=4284),
+        # block Krylov step on a regular operator
+        _case("spmmv_stencil27_96_k8", "spmmv", "stencil27", 96**3, k=8),
+        # block of vectors on a graph-like matrix, wide
+        _case("spmmv_powerlaw_1m_k32", "spmmv", "powerlaw", 1_000_000, sigma=1_000_000, k=32),
+        # a block width that is no power of two, rows of random length
+        _case("spmmv_random_k5", "spmmv", "random", 200_003, row_len=48, sigma=1024, k=5),
+        # many matrices of uneven size in one call
+        _case("batch_powerlaw_64", "batch", "powerlaw", 200_000, sigma=200_000, count=64),
+        # a new operator (time step, nonlinear iteration) built on the device and applied
+        _case("build_stencil27_128", "build", "stencil27", 128**3),
+        # a new graph, globally sorted, built on the device and applied
+        _case("build_powerlaw_1m", "build", "powerlaw", 1_000_000, sigma=1_000_000),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    op = rng.choice(["spmv", "spmv", "spmv", "spmmv", "spmmv", "batch", "build"])
+    val, acc = "f64", "f64"
+    if op in ("spmv", "build"):
+        val, acc = rng.choice([("f64", "f64"), ("f64", "f64"), ("f32", "f32"), ("f32", "f64"), ("bf16", "f32"),
+                               ("bf16", "f64")])
+    k = rng.choice([2, 3, 4, 5, 7, 8, 12, 16, 24, 32]) if op == "spmmv" else 1
+    C = rng.choice([16, 32, 32, 64])
+    if op == "batch":
+        rows = _log_int(rng, 2_000, 200_000)
+        return _case("", op, "powerlaw", rows, C=C, sigma=rng.choice([1024, rows]), count=rng.randint(4, 64))
+    matrix = rng.choice(["lap5", "stencil27", "powerlaw", "powerlaw", "rail", "random"])
+    if matrix == "lap5":
+        rows = _log_int(rng, 32, 1024) ** 2
+        return _case("", op, matrix, rows, C=C, val=val, acc=acc, k=k)
+    if matrix == "stencil27":
+        rows = _log_int(rng, 12, {"spmv": 155, "spmmv": 90, "build": 125}[op]) ** 3
+        return _case("", op, matrix, rows, C=C, val=val, acc=acc, k=k)
+    if matrix == "powerlaw":
+        rows = _log_int(rng, 2_000, 2_000_000 if op == "spmv" else 1_000_000)
+        return _case("", op, matrix, rows, C=C, sigma=rng.choice([1024, 16384, rows]), val=val, acc=acc, k=k)
+    if matrix == "rail":
+        rows = _log_int(rng, 300, 4284)
+        return _case("", op, matrix, rows, cols=_log_int(rng, 50_000, 1_092_610), row_len=_log_int(rng, 300, 2633),
+                     C=C, sigma=rows, val=val, acc=acc, k=min(k, 16))
+    rows = _log_int(rng, 1_000, 400_000)
+    return _case("", op, matrix, rows, cols=_log_int(rng, 1_000, 400_000), row_len=rng.randint(3, 96), C=C,
+                 sigma=rng.choice([1, 256, rows]), val=val, acc=acc, k=k)
+
+
+# ------------------------------------------------------------------ inputs
+def _rng(seed, stream):
+    g = torch.Generator(device="cuda")
+    g.manual_seed((seed * 1_000_003 + stream) % (1 << 62))
+    return g
+
+
+def _uniform(n, a, b, g):
+    return torch.rand(n, generator=g, device="cuda", dtype=torch.float64).mul_(b - a).add_(a)
+
+
+def _grid(m, dims, offsets):
+    """Row pointers and sorted columns of a stencil over an m^dims grid."""
+    n = m**dims
+    i = torch.arange(n, device="cuda", dtype=torch.int32)
+    ok = torch.empty((n, len(offsets)), dtype=torch.bool, device="cuda")
+    col = torch.empty((n, len(offsets)), dtype=torch.int32, device="cuda")
+    coord = [(i // m**d) % m for d in range(dims)]
+    for q, off in enumerate(offsets):
+        inside = torch.ones(n, dtype=torch.bool, device="cuda")
+        for d, o in enumerate(off):
+            if o:
+                inside &= (coord[d] + o >= 0) & (coord[d] + o < m)
+        ok[:, q] = inside
+        col[:, q] = i + sum(o * m**d for d, o in enumerate(off))
+    return _pointers(ok.sum(1)), col[ok]
+
+
+def _pointers(lens):
+    rpt = torch.zeros(lens.numel() + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(lens, 0, out=rpt[1:])
+    return rpt
+
+
+def _powerlaw_lengths(n, g):
+    p = torch.arange(1, min(POWERLAW_MAX, n // 2) + 1, dtype=torch.float64, device="cuda").pow_(-POWERLAW_EXPO)
+    cdf = torch.cumsum(p, 0)
+    u = torch.rand(n, generator=g, device="cuda", dtype=torch.float64) * cdf[-1]
+    return torch.searchsorted(cdf, u).clamp_(max=p.numel() - 1) + 1
+
+
+def _sorted_columns(rows, cols, ncols):
+    return (torch.sort(rows * ncols + cols).values % ncols).to(torch.int32)
+
+
+def _crs(case, seed, rows):
+    """rpt, col, val of one matrix of the case's family with `rows` rows."""
+    g, kind, ncols = _rng(seed, 1), case["matrix"], case["cols"]
+    if kind == "lap5":
+        m = round(rows ** (1 / 2))
+        rpt, col = _grid(m, 2, [(0, -1), (-1, 0), (0, 0), (1, 0), (0, 1)])
+        row = torch.repeat_interleave(torch.arange(rows, device="cuda", dtype=torch.int32), rpt.diff())
+        return rpt, col, torch.where(col == row, 4.0, -1.0).to(torch.float64)
+    if kind == "stencil27":
+        m = round(rows ** (1 / 3))
+        rpt, col = _grid(m, 3, [(dx, dy, dz) for dz in (-1, 0, 1) for dy in (-1, 0, 1) for dx in (-1, 0, 1)])
+        return rpt, col, _uniform(col.numel(), 0.5, 1.5, g)
+    if kind == "powerlaw":
+        lens, ncols = _powerlaw_lengths(rows, g), rows
+    elif kind == "rail":
+        s2 = math.log(1 + 1.6**2)  # lognormal rows of coefficient of variation 1.6
+        z = torch.randn(rows, generator=g, device="cuda", dtype=torch.float64)
+        lens = torch.exp(math.log(case["row_len"]) - s2 / 2 + math.sqrt(s2) * z).round_()
+        lens = lens.clamp_(1, ncols // 2).to(torch.int64)
+    else:
+        lens = torch.randint(0, case["row_len"] + 1, (rows,), generator=g, device="cuda")
+        lens[torch.rand(rows, generator=g, device="cuda") < 0.2] = 0
+    rpt = _pointers(lens)
+    nnz = int(rpt[-1])
+    row = torch.repeat_interleave(torch.arange(rows, device="cuda"), lens)
+    col = torch.randint(0, ncols, (nnz,), generator=g, device="cuda")
+    if kind == "powerlaw":  # half of a row in a band around the diagonal, at most half the band
+        half = POWERLAW_BAND // 2
+        near = (row + torch.randint(-half, half, (nnz,), generator=g, device="cuda")).clamp_(0, ncols - 1)
+        share = (half / lens.to(torch.float64)).clamp_(max=0.5)[row]
+        col = torch.where(torch.rand(nnz, generator=g, device="cuda", dtype=torch.float64) < share, near, col)
+    val = torch.randn(nnz, generator=g, device="cuda", dtype=torch.float64)
+    return rpt, _sorted_columns(row, col, ncols), val
+
+
+def _batch_rows(case):
+    """Sizes of a batch: log-uniform from 1/200 of the largest up."""
+    lo, hi = math.log(max(64, case["rows"] // 200)), math.log(case["rows"])
+    return [int(math.exp(lo + (hi - lo) * (i + 0.5) / case["count"])) for i in range(case["count"])]
+
+
+def _vector(case, ncols, seed):
+    t = torch.float64 if case["val"] == "f64" else torch.float32
+    v = _uniform(ncols * case["k"], -1.0, 1.0, _rng(seed, 2)).to(t)
+    return v.view(ncols, case["k"]) if case["op"] == "spmmv" else v
+
+
+def _build(case, crs, ncols, sigma):
+    return sellcs.sell_build(*crs, ncols, case["C"], sigma, val_dtype=case["val"], acc_dtype=case["acc"],
+                             kmax=max(32, case["k"]))
+
+
+def prepare(case, seed):
+    if case["op"] == "batch":
+        mats, xs, ys = [], [], []
+        for i, rows in enumerate(_batch_rows(case)):
+            mats.append(_build(case, _crs(case, seed * 1000 + i, rows), rows, min(case["sigma"], rows)))
+            xs.append(_vector(case, rows, seed * 1000 + i))
+            ys.append(torch.empty(rows, dtype=mats[-1].y_dtype, device="cuda"))
+        batch = sellcs.sell_batch_create(mats)
+        return {"case": case, "batch": batch, "vectors": sellcs.BatchVectors(batch, xs, ys)}
+    crs = _crs(case, seed, case["rows"])
+    x = _vector(case, case["cols"], seed)
+    out = torch.float64 if case["acc"] == "f64" else torch.float32
+    y = torch.empty((case["rows"],) + tuple(x.shape[1:]), dtype=out, device="cuda")
+    state = {"case": case, "x": x, "y": y}
+    if case["op"] == "build":
+        state["crs"] = crs
+    else:
+        state["matrix"] = _build(case, crs, case["cols"], case["sigma"])
+    return state
+
+
+def run(state):
+    case = state["case"]
+    if case["op"] == "batch":
+        return sellcs.sell_batch_spmv(state["batch"], state["vectors"])
+    if case["op"] == "spmmv":
+        return sellcs.sell_spmmv(state["matrix"], state["x"], state["y"])
+    if case["op"] == "spmv":
+        return sellcs.sell_spmv(state["matrix"], state["x"], state["y"])
+    # the matrix of the previous step is dropped, the new one is kept
+    state.pop("matrix", None)
+    m = state["matrix"] = _build(case, state["crs"], case["cols"], case["sigma"])
+    return {"y": sellcs.sell_spmv(m, state["x"], state["y"]), "chunks": m.info["nchunks"], "slots": m.info["padded"]}
+
+
+# -------------------------------------------------------------- work, exact
+def _nnz(case, rows):
+    if case["matrix"] == "lap5":
+        m = round(rows ** (1 / 2))
+        return 5 * m * m - 4 * m
+    if case["matrix"] == "stencil27":
+        return (3 * round(rows ** (1 / 3)) - 2) ** 3
+    if case["matrix"] == "powerlaw":
+        p = np.arange(1, min(POWERLAW_MAX, rows // 2) + 1, dtype=np.float64) ** -POWERLAW_EXPO
+        return int(rows * float((p * np.arange(1, p.size + 1)).sum() / p.sum()))
+    if case["matrix"] == "rail":
+        return rows * case["row_len"]
+    return int(rows * 0.8 * case["row_len"] / 2)
+
+
+def work(case):
+    sizes = _batch_rows(case) if case["op"] == "batch" else [case["rows"]]
+    nnz = sum(_nnz(case, r) for r in sizes)
+    ncols = sum(sizes) if case["op"] == "batch" else case["cols"]
+    x, y = (VEC_BYTES["f64" if case["val"] == "f64" else "f32"], VEC_BYTES[case["acc"]])
+    stored = nnz * (VAL_BYTES[case["val"]] + 4)
+    bytes_ = stored + case["k"] * (ncols * x + sum(sizes) * y)
+    if case["op"] == "build":  # the CRS arrays read, the stored ones written and read by the product
+        bytes_ += 12 * nnz + 8 * case["rows"] + stored
+    return {"bytes": bytes_, "flops": 2 * nnz * case["k"]}
+
+
+def _stored(case, val):
+    t = {"f64": torch.float64, "f32": torch.float32, "bf16": torch.bfloat16}[case["val"]]
+    return val.to(t).to(torch.float64)
+
+
+def _product(case, crs, x):
+    """A x in extended precision on the host, rounded once to 64 bits."""
+    rpt, col, val = crs[0].cpu().numpy(), crs[1].cpu().numpy(), _stored(case, crs[2]).cpu().numpy()
+    x = x.to(torch.float64).cpu().numpy()
+    x2 = x.reshape(x.shape[0], -1)
+    n = rpt.size - 1
+    y = np.zeros((n, x2.shape[1]), np.float64)
+    step = 1 << 23  # entries at a time
+    r0 = 0
+    while r0 < n:
+        r1 = max(r0 + 1, int(np.searchsorted(rpt, rpt[r0] + step, side="right")) - 1)
+        a, b = int(rpt[r0]), int(rpt[r1])
+        full = np.flatnonzero(rpt[r0 + 1:r1 + 1] > rpt[r0:r1])
+        if full.size:
+            v, c = val[a:b].astype(np.longdouble), col[a:b]
+            for q in range(x2.shape[1]):
+                y[r0 + full, q] = np.add.reduceat(v * x2[c, q], rpt[r0 + full] - a)
+        r0 = r1
+    return y.reshape((n,) + x.shape[1:])
+
+
+def exact(case, seed):
+    if case["op"] == "batch":
+        return [_product(case, _crs(case, seed * 1000 + i, r), _vector(case, r, seed * 1000 + i))
+                for i, r in enumerate(_batch_rows(case))]
+    crs = _crs(case, seed, case["rows"])
+    y = _product(case, crs, _vector(case, case["cols"], seed))
+    if case["op"] != "build":
+        return y
+    return {"y": y, "chunks": None, "slots": None}
