@@ -253,8 +253,11 @@ def work(case):
 
 
 def _stored(case, val):
-    t = {"f64": torch.float64, "f32": torch.float32, "bf16": torch.bfloat16}[case["val"]]
-    return val.to(t).to(torch.float64)
+    """The values as stored: rounded to nearest even, once."""
+    if case["val"] == "bf16":  # 8 significant bits; by way of binary32 some would be rounded twice
+        m, e = torch.frexp(val)
+        return torch.ldexp(torch.round(m * 256.0) / 256.0, e)
+    return val.to(torch.float32).to(torch.float64) if case["val"] == "f32" else val
 
 
 def _product(case, crs, x):
