@@ -707,7 +707,23 @@ sell_status spmmv_run(sell_handle h, const void *X, void *Y, int32_t k, void *st
   if (scratch) a.partial = scratch;
   a.k = k;
   a.kt = KT;
-  hipError_t e = sell::launch_spmmv(h->C, kv, a, static_cast<hipStream_t>(stream));
+  hipError_t e;
+  // Automatic width, and the pass kernel would need several passes: one pass
+  // of any width instead. us, pass kernel / one pass, at C = 16, 32, 64:
+  // 200,003 rows of random length up to 48, sigma = 1024: k = 5 156, 152, 259 /
+  // 105, 106, 106; k = 7 168, 236, 399 / 117; k = 12 138 (one pass), 171, 222 /
+  // 148, 147; k = 24 224, 227, 263 / 192. 27-point stencil 96^3: k = 5 280,
+  // 249, 383 / 146, 107, 107; k = 24 473, 576, 733 / 369. Power-law 1M,
+  // sigma = n: k = 5 204, 273, 429 / 115, 118, 124; k = 24 265, 297, 356 / 224,
+  // 239, 246. Whole passes of 16 stay (k = 48 at C = 16 and 32): 255, 240 / 271
+  // on the random rows, whose X then fits the L2s better (383, 422 / 331, 355
+  // on the power-law ones).
+  if (h->ktile == 0 && ntiles > 1 && k <= 64 && !(KT == 16 && k % 16 == 0)) {
+    a.kt = k;
+    e = sell::launch_spmmv_any(h->C, h->lcol != nullptr, a, static_cast<hipStream_t>(stream));
+  } else {
+    e = sell::launch_spmmv(h->C, kv, a, static_cast<hipStream_t>(stream));
+  }
   if (e != hipSuccess) return hip_fail((w + " launch").c_str(), e);
   return SELL_OK;
 }

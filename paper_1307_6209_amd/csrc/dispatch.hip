@@ -109,4 +109,28 @@ hipError_t launch_spmmv_rows(int C, int LPR, const SpmvArgs &a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_spmmv_any(int C, bool local, const SpmvArgs &a, hipStream_t s) {
+  if (a.nwork <= 0 || a.k <= 0) return hipSuccess;
+  const int rpw = C < 64 ? C : 64;
+  const int lpr = spmmv_any_lanes(C, a.k, local), np = (a.k + 2 * lpr - 1) / (2 * lpr);
+  const int sub = rpw * lpr / 64;
+  const unsigned nb = (unsigned)((a.nwork * sub + kWavesPerBlock - 1) / kWavesPerBlock);
+  hipError_t e = hipErrorInvalidValue;
+#define SELL_L(LL, KK)                                                                                       \
+  if (lpr == LL && np == KK) {                                                                              \
+    hipLaunchKernelGGL((dev::k_spmmv_any<LL, KK>), dim3(nb), dim3(64 * kWavesPerBlock), 0, s, a, C, rpw, sub); \
+    e = hipGetLastError();                                                                                  \
+  }
+  SELL_L(2, 1) SELL_L(2, 2) SELL_L(4, 1) SELL_L(4, 2) SELL_L(8, 1) SELL_L(8, 2) SELL_L(8, 3) SELL_L(8, 4)
+#undef SELL_L
+  if (e != hipSuccess || a.nsplit == 0) return e;
+  const unsigned ncomb = (unsigned)std::min(512, rpw * a.k);
+  const unsigned nzc = (unsigned)((rpw * a.k + (int)ncomb - 1) / (int)ncomb);
+#define SELL_L(CC) \
+  if (C == CC) hipLaunchKernelGGL((dev::k_combine_mm<CC>), dim3((unsigned)a.nsplit, 1, nzc), dim3(ncomb), 0, s, a);
+  SELL_L(8) SELL_L(16) SELL_L(32) SELL_L(64) SELL_L(128)
+#undef SELL_L
+  return hipGetLastError();
+}
+
 }  // namespace sell

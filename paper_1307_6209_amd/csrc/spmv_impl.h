@@ -995,6 +995,116 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) k_spmmv_rows(SpmvArgs a) 
   }
 }
 
+// Block form of any width k <= 2 * LPR * NP in one pass: LPR lanes share a
+// row, lane q holding NP pairs of right-hand sides, pair p starting at
+// (p * LPR + q) * 2 -- one access of the row's lanes covers 16 * LPR contiguous
+// bytes of its X row -- or at k - 2 where that runs past k (those lanes repeat
+// reads and products of others and store only what is theirs). The accesses
+// need element alignment only, so odd k and any X and Y run it. Bound by the
+// reads of X rows; what it saves over k_spmmv, whose lanes hold a power of two
+// that divides k, is the passes over the matrix (k = 5 at C = 32: three, at
+// C = 64: five), each of which also reads every touched line of X again.
+// Units, partial sums (width k) and the order of a row's products are those of
+// k_spmmv, so the result is too, bit for bit. A wave takes 64 / LPR rows, the
+// rpw rows of a unit sub = rpw * LPR / 64 waves.
+typedef double PairA8 __attribute__((ext_vector_type(2), aligned(8)));
+
+template <int LPR, int NP>
+__global__ void __launch_bounds__(64 * kWavesPerBlock) k_spmmv_any(SpmvArgs a, int C, int rpw, int sub) {
+  constexpr int RPA = 64 / LPR;                    // rows per wave
+  constexpr int U = NP >= 3 ? 3 : NP == 2 ? (LPR == 2 ? 8 : 4) : 8;
+  const int lane = threadIdx.x & 63;
+  const int64_t wv = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+  const int64_t w = wv / sub;
+  if (w >= a.nwork) return;
+  const int rl = (int)(wv - w * sub) * RPA + lane / LPR;  // row within the unit
+  int32_t item, seg = 0, nseg = 1;
+  int64_t poff = 0;
+  if (a.units) {
+    const Unit u = a.units[w];
+    item = u.item;
+    seg = u.seg;
+    nseg = u.nseg;
+    if (nseg > 1) poff = a.splits[u.sid].poff;
+  } else {
+    item = (int32_t)w;
+  }
+  const int k = a.k;  // at least 2
+  int vq[NP], v0[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    vq[p] = (p * LPR + lane % LPR) * 2;
+    v0[p] = vq[p] < k - 2 ? vq[p] : k - 2;
+  }
+  const int wpc = C > 64 ? C / 64 : 1;
+  const int64_t chunk = item / wpc;
+  const int r = (item - (int)(chunk * wpc)) * rpw + rl;
+  const int64_t base = a.cs[chunk];
+  const int cl = a.cl[chunk];
+  int jb = 0, je = cl;
+  if (nseg > 1) {
+    jb = seg * a.seg_cols;
+    je = jb + a.seg_cols < cl ? jb + a.seg_cols : cl;
+  }
+  const int32_t *cp = a.col + base + r;
+  const double *vp = static_cast<const double *>(a.val) + base + r;
+  const double *X = static_cast<const double *>(a.x);
+
+  double acc[NP][2];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) acc[p][0] = acc[p][1] = 0.0;
+  for (int j = jb; j < je; j += U) {  // columns past the end read as padding
+    int32_t ci[U];
+    double vv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      ci[u] = 0;
+      vv[u] = 0.0;
+      if (j + u < je) {
+        ci[u] = ld_col(cp + (int64_t)(j + u) * C);
+        vv[u] = ld_val(vp + (int64_t)(j + u) * C);
+      }
+    }
+    // padding slots hold value 0: their lanes skip the gather
+    PairA8 xg[U][NP];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const double *xr = X + (int64_t)ci[u] * k;
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+        xg[u][p] = vv[u] != 0.0 ? *reinterpret_cast<const PairA8 *>(xr + v0[p]) : PairA8{};
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        acc[p][0] = __builtin_fma(vv[u], xg[u][p][0], acc[p][0]);
+        acc[p][1] = __builtin_fma(vv[u], xg[u][p][1], acc[p][1]);
+      }
+  }
+
+  double *out;
+  if (nseg == 1) {
+    const int64_t p = chunk * C + r;
+    if (p >= a.nrows) return;
+    out = static_cast<double *>(a.y) + (a.perm ? (int64_t)a.perm[p] : p) * k;
+  } else {
+    out = static_cast<double *>(a.partial) + (poff + (int64_t)seg * rpw + rl) * k;
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    if (vq[p] + 2 <= k) {
+      PairA8 o;
+      o[0] = acc[p][0];
+      o[1] = acc[p][1];
+      if (nseg == 1) __builtin_nontemporal_store(o, reinterpret_cast<PairA8 *>(out + vq[p]));
+      else *reinterpret_cast<PairA8 *>(out + vq[p]) = o;
+    } else if (vq[p] < k) {  // the last of an odd k: the pair started at k - 2
+      out[vq[p]] = acc[p][1];
+    }
+  }
+}
+
 // Block form: add the segment sums of split row slices. Block (w, tile, z):
 // split slice w, pass tile, z-th part of the slice's (row, right-hand side)
 // elements; one thread per element where the grid covers them all, the
