@@ -358,8 +358,8 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
       if (!iperm) return fail(SELL_ERR_OOM, "sell_build: inverse permutation");
       SELL_HIP(sell::build_invert(h->perm, n, iperm, s));
     }
-    SELL_HIP(sell::build_fill(A->rpt, A->col, A->val, n, C, h->perm, len, h->cs, nc, h->padded, iperm, h->col,
-                              h->val, (int)h->vdt, s));
+    SELL_HIP(sell::build_fill(A->rpt, A->col, A->val, n, C, h->perm, h->cs, nc, h->padded, iperm, h->col, h->val,
+                              (int)h->vdt, s));
   }
   // length of every row in sorted order, for the product whose lanes stop at
   // their rows' ends

@@ -205,9 +205,8 @@ int64_t scan_tmp_elems(int64_t n);
 hipError_t build_scan(const int64_t *in, int64_t *out, int64_t n, int64_t *tmp, hipStream_t s);
 // cmap: column map applied to every stored column index (nullptr: none).
 hipError_t build_fill(const int64_t *rpt, const int32_t *col, const double *val, int64_t n, int C,
-                      const int32_t *perm, const int32_t *len, const int64_t *cs, int64_t nchunks,
-                      int64_t padded, const int32_t *cmap, int32_t *scol, void *sval, int val_dtype,
-                      hipStream_t s);
+                      const int32_t *perm, const int64_t *cs, int64_t nchunks, int64_t padded, const int32_t *cmap,
+                      int32_t *scol, void *sval, int val_dtype, hipStream_t s);
 hipError_t build_invert(const int32_t *perm, int64_t n, int32_t *iperm, hipStream_t s);
 // rl[p] = length of the row in sorted position p (0 for p >= n), p < np
 hipError_t build_sorted_len(const int32_t *len, const int32_t *perm, int64_t n, int64_t np, int32_t *rl,
