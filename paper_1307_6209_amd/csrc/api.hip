@@ -108,6 +108,8 @@ struct Temp {
     if (p) ptrs.push_back(p);
     return p;
   }
+  // p is no longer released here
+  void release(void *p) { ptrs.erase(std::remove(ptrs.begin(), ptrs.end(), p), ptrs.end()); }
   ~Temp() {
     for (void *p : ptrs) mem.put(p);
   }
@@ -127,13 +129,16 @@ struct EventPair {
   }
 };
 
+// Makes p (bytes of device memory) the handle's.
+void own(sell_matrix *h, void *p, size_t bytes) {
+  h->owned.push_back({p, bytes});
+  h->device_bytes += (int64_t)(bytes ? bytes : 256);
+}
+
 void *owned_alloc(sell_matrix *h, const Mem &mem, size_t bytes) {
   Mem m = mem;
   void *p = m.get(bytes);
-  if (p) {
-    h->owned.push_back({p, bytes});
-    h->device_bytes += (int64_t)(bytes ? bytes : 256);
-  }
+  if (p) own(h, p, bytes);
   return p;
 }
 
@@ -491,18 +496,41 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
       XwSmall xs{};
       int gc = 0;
       int64_t ngroups = 0;
+      // the one-pass construction writes the positions before it is known
+      // whether the windows fit; without room for them there are two passes
+      const size_t lcol_bytes = sizeof(uint16_t) * (size_t)h->padded;
+      uint16_t *lcol = static_cast<uint16_t *>(tmp.get(lcol_bytes));
+      int32_t *segtab = nullptr;
+      bool packed = false;  // xs describes tables that build_xw_fast left
+      auto read_back = [&]() -> hipError_t {
+        hipError_t e = sell::build_scan(cnt, offs, ngroups + 1, stmp, s);
+        if (e == hipSuccess) e = hipMemcpyAsync(&dxs->nseg, offs + ngroups, sizeof(int64_t), hipMemcpyDeviceToDevice, s);
+        if (e == hipSuccess) e = hipMemcpyAsync(&xs, dxs, sizeof(XwSmall), hipMemcpyDeviceToHost, s);
+        return e == hipSuccess ? hipStreamSynchronize(s) : e;
+      };
       for (int i = 0; i < ngc && gc == 0; ++i) {
         ngroups = (nc + gcs[i] - 1) / gcs[i];
         // the automatic choice keeps two workgroups per compute unit
         if (ngc > 1 && i + 1 < ngc && (C != 32 || (o.xwindow != 1 && ngroups < 2 * (int64_t)di.cus))) continue;
-        SELL_HIP(hipMemsetAsync(dxs, 0, sizeof(XwSmall), s));
-        SELL_HIP(sell::build_xw_count(h->col, h->cs, nc, gcs[i], cnt, &dxs->flags, &dxs->maxwin, &dxs->maxseg, s));
-        SELL_HIP(sell::build_scan(cnt, offs, ngroups + 1, stmp, s));
-        SELL_HIP(hipMemcpyAsync(&dxs->nseg, offs + ngroups, sizeof(int64_t), hipMemcpyDeviceToDevice, s));
-        SELL_HIP(hipMemcpyAsync(&xs, dxs, sizeof(XwSmall), hipMemcpyDeviceToHost, s));
-        SELL_HIP(hipStreamSynchronize(s));
         // window budget per wave of the workgroup: 4 KiB (16 KiB when required)
         const size_t budget = (o.xwindow == 1 ? (size_t)16 << 10 : (size_t)4 << 10) * (size_t)gcs[i];
+        packed = false;
+        if (lcol) {
+          segtab = static_cast<int32_t *>(tmp.get(sizeof(int32_t) * (size_t)sell::xw_fast_table_elems(nc, gcs[i])));
+          if (segtab) {
+            SELL_HIP(hipMemsetAsync(dxs, 0, sizeof(XwSmall), s));
+            SELL_HIP(sell::build_xw_fast(h->col, h->cs, nc, gcs[i], (int)(budget / xsz), cnt, &dxs->flags,
+                                         &dxs->maxwin, &dxs->maxseg, segtab, lcol, s));
+            SELL_HIP(read_back());
+            if (xs.flags & (1u | 4u)) continue;  // these windows do not fit
+            packed = xs.flags == 0;
+          }
+        }
+        if (!packed) {
+          SELL_HIP(hipMemsetAsync(dxs, 0, sizeof(XwSmall), s));
+          SELL_HIP(sell::build_xw_count(h->col, h->cs, nc, gcs[i], cnt, &dxs->flags, &dxs->maxwin, &dxs->maxseg, s));
+          SELL_HIP(read_back());
+        }
         if (!xs.flags && (size_t)xs.maxwin * xsz <= budget && xs.maxseg <= sell::kXwMaxSeg &&
             xw_lds_bytes(xs.maxwin, xs.maxseg, xsz, gcs[i]) <= di.lds_per_block)
           gc = gcs[i];
@@ -515,11 +543,15 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
       } else {
         h->xsegoff = static_cast<int64_t *>(owned_alloc(h.get(), mem, sizeof(int64_t) * (size_t)(ngroups + 1)));
         h->xseg = static_cast<int32_t *>(owned_alloc(h.get(), mem, sizeof(int32_t) * 3 * (size_t)xs.nseg));
-        h->lcol = static_cast<uint16_t *>(owned_alloc(h.get(), mem, sizeof(uint16_t) * (size_t)h->padded));
-        if (!h->xsegoff || !h->xseg || !h->lcol) return fail(SELL_ERR_OOM, "sell_build: x window arrays");
+        if (!lcol) lcol = static_cast<uint16_t *>(tmp.get(lcol_bytes));
+        if (!h->xsegoff || !h->xseg || !lcol) return fail(SELL_ERR_OOM, "sell_build: x window arrays");
+        tmp.release(lcol);
+        own(h.get(), lcol, lcol_bytes);
+        h->lcol = lcol;
         SELL_HIP(hipMemcpyAsync(h->xsegoff, offs, sizeof(int64_t) * (size_t)(ngroups + 1), hipMemcpyDeviceToDevice,
                                 s));
-        SELL_HIP(sell::build_xw_fill(h->col, h->cs, nc, gc, h->xsegoff, h->xseg, h->lcol, s));
+        if (packed) SELL_HIP(sell::build_xw_segs(segtab, h->xsegoff, ngroups, h->xseg, s));
+        else SELL_HIP(sell::build_xw_fill(h->col, h->cs, nc, gc, h->xsegoff, h->xseg, h->lcol, s));
         SELL_HIP(hipStreamSynchronize(s));
         h->xw_gc = gc;
         h->nxseg = xs.nseg;
