@@ -339,8 +339,8 @@ __device__ __forceinline__ int64_t chunk_of(const int64_t *__restrict__ cs, int6
   return lo;
 }
 
-// One wave per 64 chunk columns (64 * C slots; every chunk starts and ends at a
-// column, so no column is cut). The chunks of the range are searched once per
+// One wave per 2^rc <= 64 chunk columns (every chunk starts and ends at a column,
+// so no column is cut). The chunks of the range are searched once per
 // wave, uniformly. Up to kFillPieces chunks: one after another in tiles of
 // kFillTile slots, which are read along the rows (8 rows by 8 entries an
 // access, 16 accesses in flight) and turned in LDS. More (short chunks): lane c
@@ -354,15 +354,15 @@ __device__ __forceinline__ int64_t chunk_of(const int64_t *__restrict__ cs, int6
 constexpr int kFillPieces = 8;
 constexpr int kFillTile = 1024;
 
-template <int VD>
+template <int VD, bool TILES>
 __global__ void __launch_bounds__(kBlock) k_fill(const int64_t *__restrict__ rpt, const int32_t *__restrict__ col,
-                                                 const double *__restrict__ val, int64_t n, int C, int lc,
+                                                 const double *__restrict__ val, int64_t n, int C, int lc, int rc,
                                                  const int32_t *__restrict__ perm, const int64_t *__restrict__ cs,
                                                  int64_t nchunks, int64_t padded, const int32_t *__restrict__ cmap,
                                                  int32_t *__restrict__ scol, void *__restrict__ sval) {
   constexpr int U = 8;
-  __shared__ double tile_v[kBlock / 64][kFillTile];
-  __shared__ int32_t tile_c[kBlock / 64][kFillTile];
+  __shared__ double tile_v[kBlock / 64][TILES ? kFillTile : 1];
+  __shared__ int32_t tile_c[kBlock / 64][TILES ? kFillTile : 64];
   const int lane = lane_id();
   double *tv = tile_v[threadIdx.x >> 6];
   int32_t *tc = tile_c[threadIdx.x >> 6];
@@ -371,7 +371,7 @@ __global__ void __launch_bounds__(kBlock) k_fill(const int64_t *__restrict__ rpt
   // the lanes of such a read fall on all banks
   const int lr = lc < 3 ? lc : 3, lj = 4 + lr - lc > 0 ? 4 + lr - lc : 0;
   const int64_t w = (int64_t)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t s0 = w << (6 + lc), range = (int64_t)64 << lc;
+  const int64_t s0 = w << (rc + lc), range = (int64_t)1 << (rc + lc);
   if (s0 >= padded) return;  // uniform over the wave; no barrier below
   const int64_t s1 = s0 + range < padded ? s0 + range : padded;
   const int64_t i0 = chunk_of(cs, 0, nchunks, s0);
@@ -379,7 +379,7 @@ __global__ void __launch_bounds__(kBlock) k_fill(const int64_t *__restrict__ rpt
   while (i0 + step < nchunks && cs[i0 + step] < s1) step <<= 1;
   const int64_t i1 = chunk_of(cs, i0, i0 + step < nchunks ? i0 + step : nchunks, s1 - 1);  // last chunk of the range
 
-  if (i1 - i0 < kFillPieces) {
+  if (TILES && i1 - i0 < kFillPieces) {
     for (int64_t i = i0; i <= i1; ++i) {
       const int64_t b = cs[i], e = cs[i + 1];
       const int64_t sb = b > s0 ? b : s0, se = e < s1 ? e : s1;
@@ -637,13 +637,20 @@ hipError_t build_fill(const int64_t *rpt, const int32_t *col, const double *val,
                       int32_t *scol, void *sval, int val_dtype, hipStream_t s) {
   if (padded <= 0) return hipSuccess;
   const int lc = __builtin_ctz((unsigned)C);
-  const int64_t waves = (padded + ((int64_t)64 << lc) - 1) >> (6 + lc);
+  // small matrices: fewer columns a wave, slots on their own (50,000 rows of up
+  // to 20 entries: 32 us with 64 columns in tiles, 21 with the tiles unused but
+  // their LDS taken, 11 so)
+  int rc = 6;
+  const bool tiles = padded >> (rc + lc) >= 2048;
+  while (!tiles && rc > 1 && padded >> (rc + lc) < 8192) --rc;
+  const int64_t waves = (padded + ((int64_t)1 << (rc + lc)) - 1) >> (rc + lc);
   const dim3 nb(blocks_for(waves, kBlock / 64));
-#define SELL_L(VD)                                                                                              \
-  if (val_dtype == VD)                                                                                         \
-    hipLaunchKernelGGL(k_fill<VD>, nb, dim3(kBlock), 0, s, rpt, col, val, n, C, lc, perm, cs, nchunks, padded, \
-                       cmap, scol, sval);
-  SELL_L(SELL_F64) SELL_L(SELL_F32) SELL_L(SELL_BF16)
+#define SELL_L(VD, TT)                                                                                            \
+  if (val_dtype == VD && tiles == TT)                                                                            \
+    hipLaunchKernelGGL((k_fill<VD, TT>), nb, dim3(kBlock), 0, s, rpt, col, val, n, C, lc, rc, perm, cs, nchunks, \
+                       padded, cmap, scol, sval);
+  SELL_L(SELL_F64, true) SELL_L(SELL_F32, true) SELL_L(SELL_BF16, true)
+  SELL_L(SELL_F64, false) SELL_L(SELL_F32, false) SELL_L(SELL_BF16, false)
 #undef SELL_L
   return hipGetLastError();
 }
