@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "batch_plan.h"
+#include "block_cache.h"
 #include "sell_internal.h"
 
 using sell::Geom;
@@ -76,33 +77,73 @@ size_t xw_lds_bytes(int64_t maxwin, int64_t maxseg, size_t xsz, int gc) {
   return (((size_t)maxwin * xsz + 7) & ~(size_t)7) + 8 * (size_t)std::max<int64_t>(maxseg, 64 * (int64_t)gc);
 }
 
-// Device memory through the caller's allocator or hipMalloc.
+void *raw_alloc(size_t bytes) {
+  void *p = nullptr;
+  if (hipMalloc(&p, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return p;
+}
+
+void raw_free(void *p) { (void)hipFree(p); }
+
+// The process's block cache; never destroyed, since at exit the HIP runtime
+// may be gone before it.
+sell::BlockCache &block_cache() {
+  static sell::BlockCache *c = new sell::BlockCache(raw_alloc, raw_free);
+  return *c;
+}
+
+int current_device() {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+  return dev;
+}
+
+// Most bytes kept for later constructions: 1/64 of the device's memory.
+size_t cache_limit() {
+  static const size_t limit = [] {
+    size_t free_bytes = 0, total = 0;
+    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) total = 0;
+    return total / 64;
+  }();
+  return limit;
+}
+
+// Device memory through the caller's allocator, from the block cache, or (kept
+// false) plain. Blocks are put back idle.
 struct Mem {
   sell_allocator alloc{};
   bool custom = false;
+  bool kept = true;
   void *get(size_t bytes) {
     if (bytes == 0) bytes = 256;
-    void *p = nullptr;
-    if (custom) {
-      p = alloc.alloc(bytes, alloc.ctx);
-    } else if (hipMalloc(&p, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      p = nullptr;
-    }
-    return p;
+    if (custom) return alloc.alloc(bytes, alloc.ctx);
+    return kept ? block_cache().get(current_device(), bytes, cache_limit()) : raw_alloc(bytes);
   }
   void put(void *p) {
     if (!p) return;
     if (custom) alloc.free(p, alloc.ctx);
-    else (void)hipFree(p);
+    else if (kept) block_cache().put(current_device(), p, cache_limit());
+    else raw_free(p);
   }
 };
 
-// Temporary device buffers released at scope exit.
+Mem plain_mem() {
+  Mem m;
+  m.kept = false;
+  return m;
+}
+
+// Temporary device buffers released at scope exit, after the work on `stream`
+// (unless the caller has waited for that: idle).
 struct Temp {
   Mem mem;
+  hipStream_t stream;
+  bool idle = false;
   std::vector<void *> ptrs;
-  explicit Temp(const Mem &m) : mem(m) {}
+  Temp(const Mem &m, hipStream_t s) : mem(m), stream(s) {}
   void *get(size_t bytes) {
     void *p = mem.get(bytes);
     if (p) ptrs.push_back(p);
@@ -111,6 +152,7 @@ struct Temp {
   // p is no longer released here
   void release(void *p) { ptrs.erase(std::remove(ptrs.begin(), ptrs.end(), p), ptrs.end()); }
   ~Temp() {
+    if (!idle && !ptrs.empty()) (void)hipStreamSynchronize(stream);
     for (void *p : ptrs) mem.put(p);
   }
 };
@@ -275,16 +317,19 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
   }
   struct Guard {
     sell_matrix *h;
+    hipStream_t s;
     bool armed = true;
     ~Guard() {
-      if (armed && h) free_owned(h);
+      if (!armed || !h) return;
+      (void)hipStreamSynchronize(s);  // kernels may still use what is freed
+      free_owned(h);
     }
-  } guard{h.get()};
+  } guard{h.get(), s};
 
   const int64_t n = A->nrows;
   const int64_t nc = (n + C - 1) / C;
   h->nchunks = nc;
-  Temp tmp(mem);
+  Temp tmp(mem, s);
 
   // small counters: flags (u32), maxlen (i32), sumsq (u64)
   struct Small {
@@ -347,6 +392,7 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
   if (layout_only) {
     SELL_HIP(hipStreamSynchronize(s));
     h->nunits = h->nitems = nc * h->g.wpc;
+    tmp.idle = true;
     guard.armed = false;
     *out = h.release();
     return SELL_OK;
@@ -480,13 +526,16 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
         int64_t nseg;
       };
       const size_t xsz = h->xdt == SELL_F64 ? 8 : 4;
-      XwSmall *dxs = static_cast<XwSmall *>(tmp.get(sizeof(XwSmall)));
       const int64_t ngroups_max = (nc + sell::kXwChunks - 1) / sell::kXwChunks;
-      int64_t *cnt = static_cast<int64_t *>(tmp.get(sizeof(int64_t) * (size_t)(ngroups_max + 1)));
-      int64_t *offs = static_cast<int64_t *>(tmp.get(sizeof(int64_t) * (size_t)(ngroups_max + 1)));
-      int64_t *stmp =
-          static_cast<int64_t *>(tmp.get(sizeof(int64_t) * (size_t)sell::scan_tmp_elems(ngroups_max + 1)));
-      if (!dxs || !cnt || !offs || !stmp) return fail(SELL_ERR_OOM, "sell_build: x window temporaries");
+      // one block for the counters, the groups' run counts and offsets, the
+      // scan's totals and the run tables of the one-pass construction
+      const size_t n_cnt = (size_t)ngroups_max + 1, n_scan = (size_t)sell::scan_tmp_elems(ngroups_max + 1);
+      const size_t n_tab = (size_t)sell::xw_fast_table_elems(nc, sell::kXwChunks);
+      XwSmall *dxs = static_cast<XwSmall *>(
+          tmp.get(sizeof(XwSmall) + sizeof(int64_t) * (2 * n_cnt + n_scan) + sizeof(int32_t) * n_tab));
+      if (!dxs) return fail(SELL_ERR_OOM, "sell_build: x window temporaries");
+      int64_t *cnt = reinterpret_cast<int64_t *>(dxs + 1), *offs = cnt + n_cnt, *stmp = offs + n_cnt;
+      int32_t *segtab = reinterpret_cast<int32_t *>(stmp + n_scan);
       int gcs[2] = {sell::kXwChunksWide, sell::kXwChunks};
       int ngc = 2;
       if (o.xwindow_chunks != 0) {
@@ -500,7 +549,6 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
       // whether the windows fit; without room for them there are two passes
       const size_t lcol_bytes = sizeof(uint16_t) * (size_t)h->padded;
       uint16_t *lcol = static_cast<uint16_t *>(tmp.get(lcol_bytes));
-      int32_t *segtab = nullptr;
       bool packed = false;  // xs describes tables that build_xw_fast left
       auto read_back = [&]() -> hipError_t {
         hipError_t e = sell::build_scan(cnt, offs, ngroups + 1, stmp, s);
@@ -514,19 +562,19 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
         if (ngc > 1 && i + 1 < ngc && (C != 32 || (o.xwindow != 1 && ngroups < 2 * (int64_t)di.cus))) continue;
         // window budget per wave of the workgroup: 4 KiB (16 KiB when required)
         const size_t budget = (o.xwindow == 1 ? (size_t)16 << 10 : (size_t)4 << 10) * (size_t)gcs[i];
+        bool counted = false;
         packed = false;
         if (lcol) {
-          segtab = static_cast<int32_t *>(tmp.get(sizeof(int32_t) * (size_t)sell::xw_fast_table_elems(nc, gcs[i])));
-          if (segtab) {
-            SELL_HIP(hipMemsetAsync(dxs, 0, sizeof(XwSmall), s));
-            SELL_HIP(sell::build_xw_fast(h->col, h->cs, nc, gcs[i], (int)(budget / xsz), cnt, &dxs->flags,
-                                         &dxs->maxwin, &dxs->maxseg, segtab, lcol, s));
-            SELL_HIP(read_back());
-            if (xs.flags & (1u | 4u)) continue;  // these windows do not fit
-            packed = xs.flags == 0;
-          }
+          SELL_HIP(hipMemsetAsync(dxs, 0, sizeof(XwSmall), s));
+          SELL_HIP(sell::build_xw_fast(h->col, h->cs, nc, gcs[i], (int)(budget / xsz), cnt, &dxs->flags, &dxs->maxwin,
+                                       &dxs->maxseg, segtab, lcol, s));
+          SELL_HIP(read_back());
+          if (xs.flags & (1u | 4u)) continue;  // these windows do not fit
+          packed = xs.flags == 0;
+          counted = (xs.flags & 2u) == 0;
+          xs.flags = 0;
         }
-        if (!packed) {
+        if (!counted) {
           SELL_HIP(hipMemsetAsync(dxs, 0, sizeof(XwSmall), s));
           SELL_HIP(sell::build_xw_count(h->col, h->cs, nc, gcs[i], cnt, &dxs->flags, &dxs->maxwin, &dxs->maxseg, s));
           SELL_HIP(read_back());
@@ -569,6 +617,7 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
       }
     }
   }
+  tmp.idle = true;  // every step above waits for the stream before it goes on
   guard.armed = false;
   *out = h.release();
   return SELL_OK;
@@ -578,7 +627,9 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
 
 extern "C" sell_status sell_build(const sell_crs *A, int32_t C, int64_t sigma, const sell_build_opts *opts,
                                   void *stream, sell_handle *out) {
-  return build_impl(A, C, sigma, opts, stream, out, false);
+  const sell_status st = build_impl(A, C, sigma, opts, stream, out, false);
+  block_cache().tick();
+  return st;
 }
 
 // ===========================================================================
@@ -877,7 +928,10 @@ extern "C" sell_status sell_export_xwindow(sell_handle h, int64_t *segoff, int32
 }
 
 extern "C" sell_status sell_destroy(sell_handle h) {
-  if (!h) return SELL_OK;
+  if (!h) {
+    block_cache().flush();
+    return SELL_OK;
+  }
   (void)hipDeviceSynchronize();
   free_owned(h);
   delete h;
@@ -1225,7 +1279,7 @@ extern "C" sell_status sell_autotune(const sell_crs *A, int32_t k, const sell_tu
   hipStream_t s = static_cast<hipStream_t>(stream);
 
   const size_t xs = (o.val_dtype == SELL_F64 ? 8 : 4), ys = (o.acc_dtype == SELL_F64 ? 8 : 4);
-  Temp tmp(Mem{});
+  Temp tmp(plain_mem(), s);
   void *x = tmp.get(xs * (size_t)std::max<int64_t>(1, A->ncols) * (size_t)k);
   void *y = tmp.get(ys * (size_t)std::max<int64_t>(1, A->nrows) * (size_t)k);
   if (!x || !y) return fail(SELL_ERR_OOM, "sell_autotune: vectors");
@@ -1376,7 +1430,7 @@ extern "C" sell_status sell_batch_autotune(const sell_crs *As, int32_t count, co
     ytot += (size_t)(std::max<int64_t>(As[b].nrows, 1) + 31) / 32 * 32;
     nnz += As[b].nnz;
   }
-  Temp tmp(Mem{});
+  Temp tmp(plain_mem(), s);
   char *x = static_cast<char *>(tmp.get(xs * xtot));
   char *y = static_cast<char *>(tmp.get(ys * ytot));
   if (!x || !y) return fail(SELL_ERR_OOM, "sell_batch_autotune: vectors");
@@ -1467,7 +1521,7 @@ extern "C" sell_status sell_probe_bandwidth(int32_t kind, size_t bytes, int32_t 
     return fail(SELL_ERR_INVALID_ARG, "sell_probe_bandwidth: bad arguments");
   hipStream_t s = static_cast<hipStream_t>(stream);
   bytes = bytes / 64 * 64;
-  Temp tmp(Mem{});
+  Temp tmp(plain_mem(), s);
   const size_t abytes = kind == 1 ? bytes / 2 : bytes;
   // second buffer: the copy's target, or the output rows of kinds 7-9
   const size_t bbytes = kind == 1 ? bytes / 2 : kind >= 7 ? bytes : 0;

@@ -219,11 +219,12 @@ hipError_t build_xw_count(const int32_t *col, const int64_t *cs, int64_t nchunks
                           uint32_t *flags, int32_t *maxwin, int32_t *maxseg, hipStream_t s);
 hipError_t build_xw_fill(const int32_t *col, const int64_t *cs, int64_t nchunks, int gc, const int64_t *segoff,
                          int32_t *seg, uint16_t *lcol, hipStream_t s);
-// The same in one pass where no group has more than 64 runs or spans more than
-// 131,072 columns (flag 2 otherwise, flag 4 where a window has over maxwin_ok
-// columns or over kXwMaxSeg runs; with any flag the rest is undefined): counts,
-// maxima and the positions; the runs go to segtab (xw_fast_table_elems int32)
-// until build_xw_segs packs them.
+// The same in one pass where no group spans more than 131,072 columns (flag 2
+// otherwise: nothing is defined; flag 1 or 4: so too, and some window has too
+// many slots, or runs, or over maxwin_ok columns): counts, maxima and the
+// positions; the runs go to segtab (xw_fast_table_elems int32) until
+// build_xw_segs packs them. Flag 8: some group has over 64 runs, and only the
+// counts and maxima are defined.
 int64_t xw_fast_table_elems(int64_t nchunks, int gc);
 hipError_t build_xw_fast(const int32_t *col, const int64_t *cs, int64_t nchunks, int gc, int maxwin_ok, int64_t *nseg,
                          uint32_t *flags, int32_t *maxwin, int32_t *maxseg, int32_t *segtab, uint16_t *lcol,

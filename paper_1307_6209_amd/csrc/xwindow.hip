@@ -288,10 +288,12 @@ __global__ void __launch_bounds__(kXwBlock) k_xw_groups(const int32_t *__restric
 // one's position less its own. The positions go out at once; the runs, whose
 // places follow from every group's count, to a table of kXwFastSegs entries per
 // group that k_xw_segs packs. 24 KiB of LDS (k_xw_groups: 67) leave five
-// workgroups on a CU. A group outside these limits, or a window that the caller
-// would refuse (too many slots, runs or, beyond maxwin_ok, columns), raises a
-// flag, and groups that start after that end at once. 27-point stencil 128^3,
-// 56 M slots (336 MB moved): two passes of k_xw_groups 480 + 580 us, now 109 + 3 (3.1 TB/s).
+// workgroups on a CU. A wider span (flag 2), or a window that the caller would
+// refuse (flag 1: too many slots; 4: too many runs, or over maxwin_ok columns),
+// stops the groups that start after it. More runs in a group (flag 8) leave the
+// counts whole, and the second pass of k_xw_groups to be run. 27-point stencil
+// 128^3, 56 M slots (336 MB moved): two passes of k_xw_groups 480 + 580 us, now
+// 109 + 3 (3.1 TB/s).
 constexpr int kXwFastBlock = 512;
 constexpr int kXwFastWords = 4096;
 constexpr int kXwFastSegs = 64;
@@ -319,7 +321,7 @@ __global__ void __launch_bounds__(kXwFastBlock) k_xw_fast(const int32_t *__restr
   const int64_t c1 = c0 + gc < nchunks ? c0 + gc : nchunks;
   const int64_t sb = cs[c0], se = cs[c1];
   __syncthreads();
-  if (stop || se - sb > kXwMaxSlots) {  // uniform over the block
+  if ((stop & 7u) || se - sb > kXwMaxSlots) {  // uniform over the block
     if (tid == 0) {
       if (se - sb > kXwMaxSlots) atomicOr(flags, 1u);
       nseg[g] = 0;
@@ -434,12 +436,12 @@ __global__ void __launch_bounds__(kXwFastBlock) k_xw_fast(const int32_t *__restr
   if (tid == 0) {
     nseg[g] = ns;
     if (nuniq > maxwin_ok || ns > kXwMaxSeg) atomicOr(flags, 4u);
-    else if (ns > kXwFastSegs) atomicOr(flags, 2u);
+    else if (ns > kXwFastSegs) atomicOr(flags, 8u);
     // most groups raise neither maximum: look before the atomic
     if (nuniq > __hip_atomic_load(maxwin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(maxwin, nuniq);
     if (ns > __hip_atomic_load(maxseg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(maxseg, ns);
   }
-  if (nuniq > maxwin_ok || ns > kXwFastSegs) return;
+  if (stop || nuniq > maxwin_ok || ns > kXwFastSegs) return;
   int pos = (int)(before & 0xffffu) + extra, k0 = (int)(before >> 16) + extra;
   if (tid == 0) {
     if (extra) run[0] = make_int2(0, 0);
