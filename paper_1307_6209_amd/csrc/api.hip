@@ -243,6 +243,110 @@ int32_t auto_seg_cols(int64_t total_steps, int T, int cus) {
   return round_seg(steps * T);
 }
 
+// Segment width of the single-vector product, at most S: at least eight wave
+// steps (one round of loads in flight) and 32 columns, more only where there
+// would be more than two segments per resident wave. The block form keeps
+// longer ones (S): its lanes walk the columns of a row alone and its segment
+// sums are k times as many. us at 32 / 64 / 128 / 256 columns, C = 32: power-law
+// 2M, sigma = n 109.7 / 111.0 / 115.4 / 116.0; 200k 13.3 / 15.8 / 24.4 / 24.3;
+// 1M, sigma = 1024, FP32 70.3 / 70.1 / 77.6 / 77.7; 4,284 rows of 2,633 entries
+// 72 / 70 / 82 / 87; at 16 columns 106, 14.5, 74 and 79.
+int32_t single_seg_cols(int64_t total_steps, int T, int cus, int32_t S) {
+  const int64_t resident = (int64_t)cus * 32;
+  const int64_t cols = std::max<int64_t>(std::max<int64_t>(total_steps / (2 * resident), 8) * T, 32);
+  const int64_t a = std::max(T, 16);
+  return (int32_t)std::min<int64_t>((cols + a - 1) / a * a, S);
+}
+
+// The single-vector product's own work plan on a layout with split chunks
+// (units, splits: the handle's plan, segments of S columns). Sets units1,
+// splits1, seg1 and the partial-sum buffer, which serves both plans.
+//
+// Runs of 64 / C whole chunks at most 64 / C columns wide become one unit each
+// (one wave covers all their rows). The segments of split chunks come first,
+// and where x exceeds an XCD's L2 in the order of the columns they read, each
+// XCD an eighth of them: a row's entries are usually sorted, so a segment
+// reads a range of x, and an eighth of x stays in the L2. 4,284 x 1,092,610
+// with 2,633 entries per row, C = 16 / 32 / 64: 111 / 118 / 124 us in chunk
+// order, 65 / 70 / 100 so (L2 misses 6.1 M -> 1.6 M lines, of which 1.1 M are
+// the matrix); power-law 2M, sigma = n, 115 -> 111. Where most of a segment is
+// padding the order of the chunks, whose rows lie near each other, is the
+// better one: power-law 1M at sigma = 1024 104 / 109, 2M at sigma = 2^14 144 / 159.
+sell_status plan_single(sell_matrix *h, const Mem &mem, Temp &tmp, const std::vector<sell::Unit> &units,
+                        const std::vector<sell::SplitDesc> &splits, const ItemCols &st, int32_t S, bool fixed,
+                        const DeviceInfo &di, hipStream_t s) {
+  const Geom &g = h->g;
+  const int C = h->C;
+  const int32_t S1 = fixed ? S : single_seg_cols(st.total_steps, g.T, di.cus, S);
+  h->seg1 = S1;
+  std::vector<sell::Unit> segs, whole;
+  std::vector<sell::SplitDesc> sp;
+  const size_t grp = C >= 8 && C <= 32 ? (size_t)(64 / C) : 0;
+  const int32_t wmax = (int32_t)grp;
+  int64_t off = 0;
+  for (size_t it = 0; it < (size_t)h->nitems; ++it) {
+    const int32_t w = st.cols[it];
+    if (w > S1) {
+      const int32_t nseg = (w + S1 - 1) / S1, sid = (int32_t)sp.size();
+      sp.push_back({(int32_t)it, nseg, off});
+      off += (int64_t)nseg * g.rpw;
+      for (int32_t q = 0; q < nseg; ++q) segs.push_back({(int32_t)it, q, nseg, sid});
+      continue;
+    }
+    if (grp && w <= wmax && it + grp <= (size_t)h->nitems) {
+      size_t e = it + 1;
+      while (e < it + grp && st.cols[e] <= wmax) ++e;
+      if (e == it + grp) {
+        whole.push_back({(int32_t)it, 0, 0, 0});
+        it = e - 1;
+        continue;
+      }
+    }
+    whole.push_back({(int32_t)it, 0, 1, 0});
+  }
+  const size_t nseg = segs.size();
+  h->nsegs1 = (int64_t)nseg;
+  h->nsplit1 = (int64_t)sp.size();
+  h->nunits1 = (int64_t)(nseg + whole.size());
+  h->units1 = static_cast<sell::Unit *>(owned_alloc(h, mem, sizeof(sell::Unit) * (size_t)h->nunits1));
+  h->splits1 = static_cast<sell::SplitDesc *>(owned_alloc(h, mem, sizeof(sell::SplitDesc) * sp.size()));
+  h->partial = owned_alloc(h, mem, sizeof(double) * (size_t)std::max(h->partial_elems, off));
+  if (!h->units1 || !h->splits1 || !h->partial) return fail(SELL_ERR_OOM, "sell_build: work plan");
+  SELL_HIP(hipMemcpyAsync(h->splits1, sp.data(), sizeof(sell::SplitDesc) * sp.size(), hipMemcpyHostToDevice, s));
+
+  std::vector<int32_t> order;
+  const size_t xbytes = (size_t)h->ncols * dtype_size(h->xdt);
+  if (xbytes > sell::kXcdMinX && nseg > 0) {
+    SELL_HIP(hipMemcpyAsync(h->units1, segs.data(), sizeof(sell::Unit) * nseg, hipMemcpyHostToDevice, s));
+    sell::UnitCol *dcol = static_cast<sell::UnitCol *>(tmp.get(sizeof(sell::UnitCol) * nseg));
+    if (!dcol) return fail(SELL_ERR_OOM, "sell_build: work plan");
+    SELL_HIP(sell::build_unit_cols(h->units1, (int64_t)nseg, g.rpw, g.wpc, C, S1, h->cs, h->cl, h->col, dcol, s));
+    std::vector<sell::UnitCol> uc(nseg);
+    SELL_HIP(hipMemcpyAsync(uc.data(), dcol, sizeof(sell::UnitCol) * nseg, hipMemcpyDeviceToHost, s));
+    SELL_HIP(hipStreamSynchronize(s));
+    int64_t live = 0;
+    std::vector<int32_t> rep(nseg);
+    for (size_t i = 0; i < nseg; ++i) {
+      rep[i] = uc[i].col;
+      live += uc[i].live;
+    }
+    if ((double)live >= sell::kXcdMinLive * (double)g.rpw * (double)nseg)
+      order = sell::order_by_column(rep, sell::kWavesPerBlock, sell::kXcds);
+  }
+  std::vector<sell::Unit> u1;
+  u1.reserve((size_t)h->nunits1);
+  size_t nw = 0;
+  if (order.empty()) u1 = segs;
+  for (int32_t i : order) {
+    if (i >= 0) u1.push_back(segs[(size_t)i]);
+    else if (nw < whole.size()) u1.push_back(whole[nw++]);  // the place of an XCD whose part has ended
+  }
+  u1.insert(u1.end(), whole.begin() + (ptrdiff_t)nw, whole.end());
+  SELL_HIP(hipMemcpyAsync(h->units1, u1.data(), sizeof(sell::Unit) * u1.size(), hipMemcpyHostToDevice, s));
+  SELL_HIP(hipStreamSynchronize(s));  // the lists end with this scope
+  return SELL_OK;
+}
+
 }  // namespace
 
 // ===========================================================================
@@ -453,43 +557,13 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
     const int64_t kcap = next_pow2(h->kmax);
     h->units = static_cast<sell::Unit *>(owned_alloc(h.get(), mem, sizeof(sell::Unit) * units.size()));
     h->splits = static_cast<sell::SplitDesc *>(owned_alloc(h.get(), mem, sizeof(sell::SplitDesc) * splits.size()));
-    h->partial = owned_alloc(h.get(), mem, sizeof(double) * (size_t)(off * kcap));
-    if (!h->units || !h->splits || !h->partial) return fail(SELL_ERR_OOM, "sell_build: work plan");
+    h->partial_elems = off * kcap;
+    if (!h->units || !h->splits) return fail(SELL_ERR_OOM, "sell_build: work plan");
     SELL_HIP(hipMemcpyAsync(h->units, units.data(), sizeof(sell::Unit) * units.size(), hipMemcpyHostToDevice, s));
     SELL_HIP(hipMemcpyAsync(h->splits, splits.data(), sizeof(sell::SplitDesc) * splits.size(),
                             hipMemcpyHostToDevice, s));
-    // the single-vector product's list: runs of 64 / C whole chunks at most
-    // 64 / C columns wide become one unit each (one wave covers all their rows)
-    if (C >= 8 && C <= 32) {
-      const size_t grp = (size_t)(64 / C);
-      const int32_t wmax = 64 / C;
-      size_t nwhole = 0;
-      for (int64_t it = 0; it < h->nitems; ++it) nwhole += st.cols[(size_t)it] <= S;
-      std::vector<sell::Unit> u1(units.begin(), units.end() - (ptrdiff_t)nwhole);  // the split segments
-      int64_t ngroups = 0;
-      for (size_t it = 0; it < (size_t)h->nitems; ++it) {
-        const int32_t w = st.cols[it];
-        if (w > S) continue;
-        if (w <= wmax && it + grp <= (size_t)h->nitems) {
-          size_t e = it + 1;
-          while (e < it + grp && st.cols[e] <= wmax) ++e;
-          if (e == it + grp) {
-            u1.push_back({(int32_t)it, 0, 0, 0});
-            ++ngroups;
-            it = e - 1;
-            continue;
-          }
-        }
-        u1.push_back({(int32_t)it, 0, 1, 0});
-      }
-      if (ngroups > 0) {
-        h->units1 = static_cast<sell::Unit *>(owned_alloc(h.get(), mem, sizeof(sell::Unit) * u1.size()));
-        if (!h->units1) return fail(SELL_ERR_OOM, "sell_build: work plan");
-        h->nunits1 = (int64_t)u1.size();
-        SELL_HIP(hipMemcpyAsync(h->units1, u1.data(), sizeof(sell::Unit) * u1.size(), hipMemcpyHostToDevice, s));
-        SELL_HIP(hipStreamSynchronize(s));  // u1 ends with this scope
-      }
-    }
+    const sell_status ps = plan_single(h.get(), mem, tmp, units, splits, st, S, o.seg_cols > 0, di, s);
+    if (ps != SELL_OK) return ps;
     SELL_HIP(hipStreamSynchronize(s));
   } else {
     h->nunits = h->nitems;
@@ -672,9 +746,12 @@ sell_status spmv_run(sell_handle h, const void *x, void *y, void *stream, void *
   sell::SpmvArgs a = args_of(h, x, y);
   if (partial) a.partial = partial;
   a.rl = h->rl;  // row_lengths: each row's lanes stop at its end
-  if (h->units1) {  // whole chunks of width 0 or 1 grouped 64 / C per wave
+  if (h->units1) {
     a.units = h->units1;
     a.nwork = h->nunits1;
+    a.splits = h->splits1;
+    a.nsplit = h->nsplit1;
+    a.seg_cols = h->seg1;
   }
   // padding-heavy layouts skip the gathers of their zero slots; near-dense
   // chunks skip the per-slot test
@@ -742,8 +819,10 @@ sell_status spmmv_run(sell_handle h, const void *X, void *Y, int32_t k, void *st
                                           " bytes of scratch, more than its " + std::to_string(scratch_bytes));
   };
   if (k == 1) {
-    if (scratch && partial_doubles(h, 1, 1) * (int64_t)sizeof(double) > (int64_t)scratch_bytes)
-      return too_big(partial_doubles(h, 1, 1));
+    // (with an automatic split width a plan has at most two segments per
+    // resident wave and split slice: well below the scratch)
+    const int64_t doubles = h->nsegs1 * (int64_t)h->g.rpw;
+    if (scratch && doubles * (int64_t)sizeof(double) > (int64_t)scratch_bytes) return too_big(doubles);
     return spmv_run(h, X, Y, stream, scratch, who);
   }
   if (h->C < 8) return fail(SELL_ERR_UNSUPPORTED, w + ": C must be >= 8 for k > 1");

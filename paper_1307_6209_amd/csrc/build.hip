@@ -508,6 +508,25 @@ __global__ void __launch_bounds__(kBlock) k_sorted_len(const int32_t *__restrict
   if (p < np) rl[p] = p < n ? len[perm ? (int64_t)perm[p] : p] : 0;
 }
 
+// One wave per split segment: the mean column of its rows at the middle of
+// the segment (rows that have ended hold column 0 there and don't count).
+__global__ void __launch_bounds__(kBlock) k_unit_cols(const Unit *__restrict__ units, int64_t n, int rpw, int wpc,
+                                                      int C, int32_t seg_cols, const int64_t *__restrict__ cs,
+                                                      const int32_t *__restrict__ cl,
+                                                      const int32_t *__restrict__ col, UnitCol *__restrict__ out) {
+  const int64_t w = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  if (w >= n) return;
+  const Unit u = units[w];
+  const int64_t chunk = u.item / wpc;
+  const int64_t jb = (int64_t)u.seg * seg_cols;
+  const int64_t je = jb + seg_cols < cl[chunk] ? jb + seg_cols : cl[chunk];
+  const int r = lane_id();
+  unsigned long long c = 0;
+  if (r < rpw) c = (unsigned long long)col[cs[chunk] + (jb + je) / 2 * C + (u.item - chunk * wpc) * rpw + r];
+  const unsigned long long cnt = wave_sum_u64(c > 0 ? 1 : 0), sum = wave_sum_u64(c);
+  if (r == 0) out[w] = {cnt ? (int32_t)(sum / cnt) : 0, (int32_t)cnt};
+}
+
 // out[p] = in[perm[p]] (gather into sorted order) or out[perm[p]] = in[p]
 // (scatter back), for elements of ES bytes.
 template <typename E, bool SCATTER>
@@ -528,6 +547,14 @@ hipError_t build_sorted_len(const int32_t *len, const int32_t *perm, int64_t n, 
                             hipStream_t s) {
   if (np <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_sorted_len, dim3(blocks_for(np, kBlock)), dim3(kBlock), 0, s, len, perm, n, np, rl);
+  return hipGetLastError();
+}
+
+hipError_t build_unit_cols(const Unit *units, int64_t n, int rpw, int wpc, int C, int32_t seg_cols, const int64_t *cs,
+                           const int32_t *cl, const int32_t *col, UnitCol *out, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_unit_cols, dim3(blocks_for(n, kBlock / 64)), dim3(kBlock), 0, s, units, n, rpw, wpc, C,
+                     seg_cols, cs, cl, col, out);
   return hipGetLastError();
 }
 

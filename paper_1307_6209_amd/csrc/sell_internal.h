@@ -34,6 +34,13 @@ struct SplitDesc {
   int64_t poff;
 };
 
+// Of a split segment, at its middle column: the mean column of the rows that
+// hold an entry there, and their number.
+struct UnitCol {
+  int32_t col;
+  int32_t live;
+};
+
 // Work unit of the batched kernel (adds the matrix index; mat < 0: an empty
 // unit that only fills the grid).
 struct BUnit {
@@ -74,6 +81,12 @@ constexpr int kBatchPersistentWaves = 1;
 // Accelerator dies (XCDs) of the device, each with its own L2; the hardware
 // dispatcher sends workgroup b of a launch to XCD b mod kXcds.
 constexpr int kXcds = 8;
+
+// Split segments are placed on the XCDs by their columns (plan_single) from
+// this size of x on (one XCD's L2) and from this share of rows that hold an
+// entry on (measured gains at 0.75 to 0.98, losses at 0.35 and below).
+constexpr size_t kXcdMinX = 4 << 20;
+constexpr double kXcdMinLive = 0.6;
 
 // Segments of split chunks are whole multiples of this many chunk columns,
 // so that every kernel's step width (at most 64 columns) divides them.
@@ -208,6 +221,9 @@ hipError_t build_fill(const int64_t *rpt, const int32_t *col, const double *val,
                       const int32_t *perm, const int64_t *cs, int64_t nchunks, int64_t padded, const int32_t *cmap,
                       int32_t *scol, void *sval, int val_dtype, hipStream_t s);
 hipError_t build_invert(const int32_t *perm, int64_t n, int32_t *iperm, hipStream_t s);
+// out[u]: where split segment u (u < n) of a unit list reads x.
+hipError_t build_unit_cols(const Unit *units, int64_t n, int rpw, int wpc, int C, int32_t seg_cols, const int64_t *cs,
+                           const int32_t *cl, const int32_t *col, UnitCol *out, hipStream_t s);
 // rl[p] = length of the row in sorted position p (0 for p >= n), p < np
 hipError_t build_sorted_len(const int32_t *len, const int32_t *perm, int64_t n, int64_t np, int32_t *rl,
                             hipStream_t s);
@@ -282,14 +298,17 @@ struct sell_matrix {
   int64_t nitems = 0;
   int64_t nunits = 0;
   sell::Unit *units = nullptr;  // nullptr when no chunk is split
-  // the single-vector product's units: the same, with each run of 64 / C
-  // chunks of width 0 or 1 as one unit (nseg 0; C <= 32); nullptr: units
+  // the single-vector product's plan on split layouts (plan_single)
   sell::Unit *units1 = nullptr;
   int64_t nunits1 = 0;
+  sell::SplitDesc *splits1 = nullptr;
+  int64_t nsplit1 = 0, nsegs1 = 0;
+  int32_t seg1 = 0;
   int64_t nsplit = 0;
   int64_t nsegs = 0;                  // total segments of split items
   sell::SplitDesc *splits = nullptr;  // per split id
-  void *partial = nullptr;            // nsegs * rpw * next_pow2(kmax) doubles
+  int64_t partial_elems = 0;          // nsegs * rpw * next_pow2(kmax): doubles of the block form
+  void *partial = nullptr;            // that many, or what the single-vector plan needs where that is more
 
   uint16_t *lcol = nullptr;     // x window mode: window position of every slot
   int64_t *xsegoff = nullptr;   // ngroups + 1 segment offsets

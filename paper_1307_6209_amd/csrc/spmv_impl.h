@@ -535,11 +535,41 @@ __device__ __forceinline__ void combine_split(const SplitDesc d, const int32_t *
   static_cast<A *>(yv)[row] = sum;
 }
 
+// The single-vector product's combine: one workgroup per split slice, its
+// G = 512 / rpw groups of threads each adding a run of consecutive segments
+// (sixteen loads in flight), then the G sums added in order. With one wave per
+// slice the longest slice's segments are one chain of round trips: on 4,284
+// rows of 2,633 entries on average, cut every 64 columns, 37 us.
+constexpr int kCombineBlock = 512;
+
 template <int COMBO, int C>
-__global__ void __launch_bounds__(64 * kWavesPerBlock) k_combine(SpmvArgs a) {
-  const int64_t w = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-  if (w >= a.nsplit) return;
-  combine_split<COMBO, C>(a.splits[w], a.perm, a.partial, a.y, a.nrows, threadIdx.x & 63);
+__global__ void __launch_bounds__(kCombineBlock) k_combine(SpmvArgs a) {
+  using A = typename Types<COMBO>::A;
+  constexpr int RPW = C < 64 ? C : 64;
+  constexpr int WPC = C > 64 ? C / 64 : 1;
+  constexpr int G = kCombineBlock / RPW;
+  __shared__ A part_sum[kCombineBlock];
+  const SplitDesc d = a.splits[blockIdx.x];
+  const int r = threadIdx.x % RPW, g = threadIdx.x / RPW;
+  const int per = (d.nseg + G - 1) / G;
+  const int q0 = g * per, q1 = q0 + per < d.nseg ? q0 + per : d.nseg;
+  const A *part = static_cast<const A *>(a.partial) + d.poff + r;
+  A sum = 0;
+  for (int q = q0; q < q1; q += 16) {  // +0 past the last segment, as in combine_split
+    A t[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) t[e] = q + e < q1 ? part[(int64_t)(q + e) * RPW] : (A)0;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) sum += t[e];
+  }
+  part_sum[threadIdx.x] = sum;
+  __syncthreads();
+  const int64_t chunk = d.item / WPC;
+  const int64_t p = chunk * C + (d.item - chunk * WPC) * RPW + r;
+  if (g != 0 || p >= a.nrows) return;
+  const int ng = (d.nseg + per - 1) / per;  // groups that hold a segment
+  for (int q = 1; q < ng; ++q) sum += part_sum[q * RPW + r];
+  static_cast<A *>(a.y)[a.perm ? (int64_t)a.perm[p] : p] = sum;
 }
 
 // A group of G = 64 / C consecutive chunks (C in 8..32), each at most
@@ -1178,8 +1208,7 @@ hipError_t launch_spmv_zs(int C, int U, int VV, const SpmvArgs &a, hipStream_t s
     hipLaunchKernelGGL((k_spmv<COMBO, CC, UU, VVV, ZS>), dim3(nb), dim3(64 * kWavesPerBlock), 0, s, a);     \
     hipError_t e_ = hipGetLastError();                                                                       \
     if (e_ != hipSuccess || a.nsplit == 0) return e_;                                                        \
-    const unsigned nbc = (unsigned)((a.nsplit + kWavesPerBlock - 1) / kWavesPerBlock);                        \
-    hipLaunchKernelGGL((k_combine<COMBO, CC>), dim3(nbc), dim3(64 * kWavesPerBlock), 0, s, a);               \
+    hipLaunchKernelGGL((k_combine<COMBO, CC>), dim3((unsigned)a.nsplit), dim3(kCombineBlock), 0, s, a);     \
     return hipGetLastError();                                                                                \
   }
   if constexpr (ZS == 2) {

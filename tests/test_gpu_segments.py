@@ -1,0 +1,48 @@
+"""The single-vector product's own segments on split layouts: fine cuts,
+their combining by several thread groups per slice, and the placement by
+columns where x exceeds an L2."""
+import numpy as np
+import pytest
+
+import synth
+from gpu_util import build, chain_per_row, check_fp64, check_reduced, say, spmv_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def lengths_crs(lens, ncols, seed):
+    """Rows of the given lengths, sorted distinct columns."""
+    rng = np.random.default_rng(seed)
+    rpt = np.zeros(len(lens) + 1, np.int64)
+    np.cumsum(lens, out=rpt[1:])
+    col = np.concatenate([np.sort(rng.choice(ncols, n, replace=False)) for n in lens] + [np.empty(0)])
+    return synth.CRS(len(lens), ncols, rpt, col.astype(np.int32), synth.uniform(int(rpt[-1]), seed, 18))
+
+
+@pytest.mark.parametrize("C", [1, 8, 16, 32, 64, 128])
+@pytest.mark.parametrize("longest", [600, 9000])
+def test_segment_counts(C, longest):
+    """Chunks of 1 to `longest` columns around the cuts of the segments, and
+    rows 0, 1 and 33 of every slice among them."""
+    lens = [longest, 0, 33, 32, 31, 64, 65, 1, 257, 0, 511, 513] * 12 + [longest - 1]
+    A = lengths_crs(lens, 20_000, 91)
+    x = synth.uniform(A.ncols, 92)
+    for sigma in (1, A.nrows):
+        h = build(A, C, sigma)
+        assert h.info["nsplit"] > 0 or longest < h.info["seg_cols"]
+        say("segments C", C, "sigma", sigma, "split", h.info["nsplit"])
+        y = spmv_gpu(h, x)
+        check_fp64(A, y, x, m=chain_per_row(A, h, C))
+        assert np.array_equal(spmv_gpu(h, x), y)
+
+
+@pytest.mark.parametrize("C", [16, 32, 64])
+def test_segments_placed_by_column(C):
+    """x of 5.6 MB: the segments are dealt to the XCDs by their columns."""
+    A = synth.rail_like(nrows=301, ncols=700_001, mean_len=900, seed=93)
+    x = synth.uniform(A.ncols, 94)
+    h = build(A, C, A.nrows)
+    assert h.info["nsplit"] > 0
+    check_fp64(A, spmv_gpu(h, x), x, m=chain_per_row(A, h, C))
+    h = build(A, C, A.nrows, val_dtype="bf16", acc_dtype="f64")
+    check_reduced(A, h, x, "bf16", "f64", C)
