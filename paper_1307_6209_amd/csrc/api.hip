@@ -224,127 +224,14 @@ int default_vec(int C, sell_dtype v, int64_t nnz, int64_t nrows) {
   return V;
 }
 
-int32_t round_seg(int64_t cols) {
-  int64_t a = sell::kSegAlign;
-  int64_t s = (cols + a - 1) / a * a;
-  if (s < a) s = a;
-  if (s > (1 << 30)) s = 1 << 30;
-  return (int32_t)s;
-}
-
-// Automatic segment width: long enough that a unit amortises its fixed
-// cost (at least 64 wave steps), short enough that no unit is much longer
-// than an average wave's share of the whole product (resident waves:
-// CUs x 32). Converted from wave steps to chunk columns.
-int32_t auto_seg_cols(int64_t total_steps, int T, int cus) {
-  int64_t resident = (int64_t)cus * 32;
-  int64_t steps = total_steps / (2 * resident);
-  if (steps < 64) steps = 64;
-  return round_seg(steps * T);
-}
-
-// Segment width of the single-vector product, at most S: at least eight wave
-// steps (one round of loads in flight) and 32 columns, more only where there
-// would be more than two segments per resident wave. The block form keeps
-// longer ones (S): its lanes walk the columns of a row alone and its segment
-// sums are k times as many. us at 32 / 64 / 128 / 256 columns, C = 32: power-law
-// 2M, sigma = n 109.7 / 111.0 / 115.4 / 116.0; 200k 13.3 / 15.8 / 24.4 / 24.3;
-// 1M, sigma = 1024, FP32 70.3 / 70.1 / 77.6 / 77.7; 4,284 rows of 2,633 entries
-// 72 / 70 / 82 / 87; at 16 columns 106, 14.5, 74 and 79.
-int32_t single_seg_cols(int64_t total_steps, int T, int cus, int32_t S) {
-  const int64_t resident = (int64_t)cus * 32;
-  const int64_t cols = std::max<int64_t>(std::max<int64_t>(total_steps / (2 * resident), 8) * T, 32);
-  const int64_t a = std::max(T, 16);
-  return (int32_t)std::min<int64_t>((cols + a - 1) / a * a, S);
-}
-
-// The single-vector product's own work plan on a layout with split chunks
-// (units, splits: the handle's plan, segments of S columns). Sets units1,
-// splits1, seg1 and the partial-sum buffer, which serves both plans.
-//
-// Runs of 64 / C whole chunks at most 64 / C columns wide become one unit each
-// (one wave covers all their rows). The segments of split chunks come first,
-// and where x exceeds an XCD's L2 in the order of the columns they read, each
-// XCD an eighth of them: a row's entries are usually sorted, so a segment
-// reads a range of x, and an eighth of x stays in the L2. 4,284 x 1,092,610
-// with 2,633 entries per row, C = 16 / 32 / 64: 111 / 118 / 124 us in chunk
-// order, 65 / 70 / 100 so (L2 misses 6.1 M -> 1.6 M lines, of which 1.1 M are
-// the matrix); power-law 2M, sigma = n, 115 -> 111. Where most of a segment is
-// padding the order of the chunks, whose rows lie near each other, is the
-// better one: power-law 1M at sigma = 1024 104 / 109, 2M at sigma = 2^14 144 / 159.
-sell_status plan_single(sell_matrix *h, const Mem &mem, Temp &tmp, const std::vector<sell::Unit> &units,
-                        const std::vector<sell::SplitDesc> &splits, const ItemCols &st, int32_t S, bool fixed,
-                        const DeviceInfo &di, hipStream_t s) {
-  const Geom &g = h->g;
-  const int C = h->C;
-  const int32_t S1 = fixed ? S : single_seg_cols(st.total_steps, g.T, di.cus, S);
-  h->seg1 = S1;
-  std::vector<sell::Unit> segs, whole;
-  std::vector<sell::SplitDesc> sp;
-  const size_t grp = C >= 8 && C <= 32 ? (size_t)(64 / C) : 0;
-  const int32_t wmax = (int32_t)grp;
-  int64_t off = 0;
-  for (size_t it = 0; it < (size_t)h->nitems; ++it) {
-    const int32_t w = st.cols[it];
-    if (w > S1) {
-      const int32_t nseg = (w + S1 - 1) / S1, sid = (int32_t)sp.size();
-      sp.push_back({(int32_t)it, nseg, off});
-      off += (int64_t)nseg * g.rpw;
-      for (int32_t q = 0; q < nseg; ++q) segs.push_back({(int32_t)it, q, nseg, sid});
-      continue;
-    }
-    if (grp && w <= wmax && it + grp <= (size_t)h->nitems) {
-      size_t e = it + 1;
-      while (e < it + grp && st.cols[e] <= wmax) ++e;
-      if (e == it + grp) {
-        whole.push_back({(int32_t)it, 0, 0, 0});
-        it = e - 1;
-        continue;
-      }
-    }
-    whole.push_back({(int32_t)it, 0, 1, 0});
-  }
-  const size_t nseg = segs.size();
-  h->nsegs1 = (int64_t)nseg;
-  h->nsplit1 = (int64_t)sp.size();
-  h->nunits1 = (int64_t)(nseg + whole.size());
-  h->units1 = static_cast<sell::Unit *>(owned_alloc(h, mem, sizeof(sell::Unit) * (size_t)h->nunits1));
-  h->splits1 = static_cast<sell::SplitDesc *>(owned_alloc(h, mem, sizeof(sell::SplitDesc) * sp.size()));
-  h->partial = owned_alloc(h, mem, sizeof(double) * (size_t)std::max(h->partial_elems, off));
-  if (!h->units1 || !h->splits1 || !h->partial) return fail(SELL_ERR_OOM, "sell_build: work plan");
-  SELL_HIP(hipMemcpyAsync(h->splits1, sp.data(), sizeof(sell::SplitDesc) * sp.size(), hipMemcpyHostToDevice, s));
-
-  std::vector<int32_t> order;
-  const size_t xbytes = (size_t)h->ncols * dtype_size(h->xdt);
-  if (xbytes > sell::kXcdMinX && nseg > 0) {
-    SELL_HIP(hipMemcpyAsync(h->units1, segs.data(), sizeof(sell::Unit) * nseg, hipMemcpyHostToDevice, s));
-    sell::UnitCol *dcol = static_cast<sell::UnitCol *>(tmp.get(sizeof(sell::UnitCol) * nseg));
-    if (!dcol) return fail(SELL_ERR_OOM, "sell_build: work plan");
-    SELL_HIP(sell::build_unit_cols(h->units1, (int64_t)nseg, g.rpw, g.wpc, C, S1, h->cs, h->cl, h->col, dcol, s));
-    std::vector<sell::UnitCol> uc(nseg);
-    SELL_HIP(hipMemcpyAsync(uc.data(), dcol, sizeof(sell::UnitCol) * nseg, hipMemcpyDeviceToHost, s));
-    SELL_HIP(hipStreamSynchronize(s));
-    int64_t live = 0;
-    std::vector<int32_t> rep(nseg);
-    for (size_t i = 0; i < nseg; ++i) {
-      rep[i] = uc[i].col;
-      live += uc[i].live;
-    }
-    if ((double)live >= sell::kXcdMinLive * (double)g.rpw * (double)nseg)
-      order = sell::order_by_column(rep, sell::kWavesPerBlock, sell::kXcds);
-  }
-  std::vector<sell::Unit> u1;
-  u1.reserve((size_t)h->nunits1);
-  size_t nw = 0;
-  if (order.empty()) u1 = segs;
-  for (int32_t i : order) {
-    if (i >= 0) u1.push_back(segs[(size_t)i]);
-    else if (nw < whole.size()) u1.push_back(whole[nw++]);  // the place of an XCD whose part has ended
-  }
-  u1.insert(u1.end(), whole.begin() + (ptrdiff_t)nw, whole.end());
-  SELL_HIP(hipMemcpyAsync(h->units1, u1.data(), sizeof(sell::Unit) * u1.size(), hipMemcpyHostToDevice, s));
-  SELL_HIP(hipStreamSynchronize(s));  // the lists end with this scope
-  return SELL_OK;
+// The handle's chunk widths on the host, copied on the first call.
+hipError_t host_widths(sell_matrix *h) {
+  std::lock_guard<std::mutex> lock(h->cl_mu);
+  if ((int64_t)h->h_cl.size() == h->nchunks) return hipSuccess;
+  std::vector<int32_t> v((size_t)h->nchunks);
+  const hipError_t e = hipMemcpy(v.data(), h->cl, sizeof(int32_t) * v.size(), hipMemcpyDeviceToHost);
+  if (e == hipSuccess) h->h_cl.swap(v);
+  return e;
 }
 
 }  // namespace
@@ -441,6 +328,7 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
     int32_t maxlen;
     unsigned long long sumsq;
     int64_t padded;
+    sell::PlanSizes plan;
   };
   Small *dsmall = static_cast<Small *>(tmp.get(sizeof(Small)));
   int32_t *len = static_cast<int32_t *>(tmp.get(sizeof(int32_t) * (size_t)std::max<int64_t>(n, 1)));
@@ -466,9 +354,29 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
   // chunk widths and offsets
   h->cl = static_cast<int32_t *>(owned_alloc(h.get(), mem, sizeof(int32_t) * (size_t)std::max<int64_t>(nc, 1)));
   h->cs = static_cast<int64_t *>(owned_alloc(h.get(), mem, sizeof(int64_t) * (size_t)(nc + 1)));
-  int64_t *scan_tmp = static_cast<int64_t *>(tmp.get(sizeof(int64_t) * (size_t)sell::scan_tmp_elems(nc + 1)));
+  const int64_t n_scan = sell::scan_tmp_elems(nc + 1);
+  int64_t *scan_tmp =
+      static_cast<int64_t *>(tmp.get(sizeof(int64_t) * (size_t)(n_scan + 5 * sell::plan_blocks(nc))));
   if (!h->cl || !h->cs || !scan_tmp) return fail(SELL_ERR_OOM, "sell_build: chunk arrays");
-  SELL_HIP(sell::build_chunkwidth(len, h->perm, n, C, nc, h->cl, h->cs, s));
+  const Geom &g = h->g;
+  const DeviceInfo di = device_info();
+  SELL_HIP(sell::build_chunkwidth(len, h->perm, n, C, nc, g.T, g.wpc, h->cl, h->cs, &dsmall->plan.total_steps,
+                                  &dsmall->plan.max_width, s));
+  sell::PlanArgs pa{};
+  if (!layout_only) {
+    pa.cl = h->cl;
+    pa.nchunks = nc;
+    pa.grp = C >= 8 && C <= 32 ? 64 / C : 1;
+    pa.ncells = (nc + pa.grp - 1) / pa.grp;
+    pa.wpc = g.wpc;
+    pa.rpw = g.rpw;
+    pa.T = g.T;
+    pa.cus = di.cus;
+    pa.seg_cols = o.seg_cols > 0 ? sell::round_seg(o.seg_cols) : o.seg_cols;
+    pa.blocks = scan_tmp + n_scan;
+    pa.sizes = &dsmall->plan;
+    SELL_HIP(sell::plan_count(pa, s));
+  }
   SELL_HIP(sell::build_scan(h->cs, h->cs, nc + 1, scan_tmp, s));
   SELL_HIP(hipMemcpyAsync(&dsmall->padded, h->cs + nc, sizeof(int64_t), hipMemcpyDeviceToDevice, s));
   Small hs{};
@@ -524,49 +432,37 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
     SELL_HIP(sell::build_sorted_len(len, h->perm, n, nc * C, h->rl, s));
   }
 
-  // host copy of the chunk widths, then the work plan
-  h->h_cl.resize((size_t)nc);
-  if (nc > 0) SELL_HIP(hipMemcpyAsync(h->h_cl.data(), h->cl, sizeof(int32_t) * (size_t)nc, hipMemcpyDeviceToHost, s));
-  SELL_HIP(hipStreamSynchronize(s));
-
-  const Geom &g = h->g;
+  // the work plans of layouts with split chunks
   h->nitems = nc * g.wpc;
-  ItemCols st = item_cols(h->h_cl, g);
-  DeviceInfo di = device_info();
-  int32_t S = o.seg_cols > 0 ? round_seg(o.seg_cols) : auto_seg_cols(st.total_steps, g.T, di.cus);
+  const sell::PlanSizes &z = hs.plan;
+  const int32_t S = o.seg_cols > 0 ? sell::round_seg(o.seg_cols) : sell::auto_seg_cols(z.total_steps, g.T, di.cus);
   h->seg_cols = S;
-  if (o.seg_cols >= 0 && st.max > S) {
-    std::vector<sell::Unit> units;
-    std::vector<sell::SplitDesc> splits;
-    int64_t off = 0;
-    // split items first: they are the longest work, so they start earliest
-    for (int64_t it = 0; it < h->nitems; ++it) {
-      int32_t w = st.cols[(size_t)it];
-      if (w <= S) continue;
-      int32_t nseg = (w + S - 1) / S;
-      int32_t sid = (int32_t)splits.size();
-      splits.push_back({(int32_t)it, nseg, off});
-      off += (int64_t)nseg * g.rpw;
-      for (int32_t q = 0; q < nseg; ++q) units.push_back({(int32_t)it, q, nseg, sid});
-    }
-    for (int64_t it = 0; it < h->nitems; ++it)
-      if (st.cols[(size_t)it] <= S) units.push_back({(int32_t)it, 0, 1, 0});
-    h->nunits = (int64_t)units.size();
-    h->nsplit = (int64_t)splits.size();
-    h->nsegs = off / g.rpw;
-    const int64_t kcap = next_pow2(h->kmax);
-    h->units = static_cast<sell::Unit *>(owned_alloc(h.get(), mem, sizeof(sell::Unit) * units.size()));
-    h->splits = static_cast<sell::SplitDesc *>(owned_alloc(h.get(), mem, sizeof(sell::SplitDesc) * splits.size()));
-    h->partial_elems = off * kcap;
-    if (!h->units || !h->splits) return fail(SELL_ERR_OOM, "sell_build: work plan");
-    SELL_HIP(hipMemcpyAsync(h->units, units.data(), sizeof(sell::Unit) * units.size(), hipMemcpyHostToDevice, s));
-    SELL_HIP(hipMemcpyAsync(h->splits, splits.data(), sizeof(sell::SplitDesc) * splits.size(),
-                            hipMemcpyHostToDevice, s));
-    const sell_status ps = plan_single(h.get(), mem, tmp, units, splits, st, S, o.seg_cols > 0, di, s);
-    if (ps != SELL_OK) return ps;
-    SELL_HIP(hipStreamSynchronize(s));
-  } else {
-    h->nunits = h->nitems;
+  h->nunits = h->nitems;
+  if (z.nsplit > 0) {
+    h->seg1 = o.seg_cols > 0 ? S : sell::single_seg_cols(z.total_steps, g.T, di.cus, S);
+    h->nunits = z.nsegs + h->nitems - z.nsplit;
+    h->nsplit = z.nsplit;
+    h->nsegs = z.nsegs;
+    h->nunits1 = z.nsegs1 + z.nwhole1;
+    h->nsplit1 = z.nsplit1;
+    h->nsegs1 = z.nsegs1;
+    const bool place = (size_t)h->ncols * dtype_size(h->xdt) > sell::kXcdMinX && z.nsegs1 <= sell::kXcdMaxSegs;
+    const int64_t sums = std::max(z.nsegs * next_pow2(h->kmax), z.nsegs1) * g.rpw;
+    h->units = static_cast<sell::Unit *>(owned_alloc(h.get(), mem, sizeof(sell::Unit) * (size_t)h->nunits));
+    h->splits = static_cast<sell::SplitDesc *>(owned_alloc(h.get(), mem, sizeof(sell::SplitDesc) * (size_t)z.nsplit));
+    h->units1 = static_cast<sell::Unit *>(owned_alloc(h.get(), mem, sizeof(sell::Unit) * (size_t)h->nunits1));
+    h->splits1 = static_cast<sell::SplitDesc *>(owned_alloc(h.get(), mem, sizeof(sell::SplitDesc) * (size_t)z.nsplit1));
+    h->partial = owned_alloc(h.get(), mem, sizeof(double) * (size_t)sums);
+    sell::Unit *segs = nullptr;
+    if (place)
+      segs = static_cast<sell::Unit *>(tmp.get((sizeof(sell::Unit) + sizeof(sell::UnitCol)) * (size_t)z.nsegs1));
+    if (!h->units || !h->splits || !h->units1 || !h->splits1 || !h->partial || (place && !segs))
+      return fail(SELL_ERR_OOM, "sell_build: work plan");
+    const sell::PlanOut po{h->units, h->splits, h->units1, h->splits1, segs};
+    SELL_HIP(sell::plan_emit(pa, S, h->seg1, z, po, s));
+    if (place)
+      SELL_HIP(sell::plan_place(pa, C, h->seg1, z, po, h->cs, h->col, h->ncols,
+                                reinterpret_cast<sell::UnitCol *>(segs + z.nsegs1), s));
   }
 
   // x windows for LDS staging: when they fit (xwindow 0) or required (1)
@@ -691,7 +587,8 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
       }
     }
   }
-  tmp.idle = true;  // every step above waits for the stream before it goes on
+  SELL_HIP(hipStreamSynchronize(s));
+  tmp.idle = true;
   guard.armed = false;
   *out = h.release();
   return SELL_OK;
@@ -1097,11 +994,12 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
   std::vector<ItemCols> st(count);
   int64_t total = 0;
   for (int32_t b = 0; b < count; ++b) {
+    SELL_HIP(host_widths(hs[b]));
     st[b] = item_cols(hs[b]->h_cl, g);
     total += st[b].total_steps;
   }
   DeviceInfo di = device_info();
-  const int32_t S = auto_seg_cols(total, g.T, di.cus);
+  const int32_t S = sell::auto_seg_cols(total, g.T, di.cus);
   B->seg_cols = S;
   // work units of every matrix: the segments of its split chunks, then its
   // whole chunks; cost estimate of a unit: its wave steps plus a fixed charge

@@ -146,22 +146,4 @@ inline XcdPlan plan_xcd(const std::vector<int32_t> &mat, const std::vector<int64
   return p;
 }
 
-// Launch order of the split segments of one matrix: rep[u] is a column typical
-// of segment u. The segments in the order of their columns are cut into X
-// equal parts, part q for XCD q: with W units per workgroup, the q-th, q+X-th,
-// ... workgroup. -1: a place whose part has ended.
-inline std::vector<int32_t> order_by_column(const std::vector<int32_t> &rep, int waves_per_block, int xcds) {
-  const size_t n = rep.size(), W = (size_t)waves_per_block, X = (size_t)xcds;
-  std::vector<int32_t> by(n);
-  std::iota(by.begin(), by.end(), 0);
-  std::stable_sort(by.begin(), by.end(), [&](int32_t a, int32_t b) { return rep[(size_t)a] < rep[(size_t)b]; });
-  const size_t per = (n + X - 1) / X, blocks = (per + W - 1) / W;
-  std::vector<int32_t> order(blocks * X * W, -1);
-  for (size_t i = 0; i < n; ++i) {
-    const size_t q = i * X / n, t = i - (q * n + X - 1) / X;  // t-th unit of part q
-    order[(t / W * X + q) * W + t % W] = by[i];
-  }
-  return order;
-}
-
 }  // namespace sell

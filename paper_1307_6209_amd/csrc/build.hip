@@ -208,28 +208,57 @@ __global__ void __launch_bounds__(kBlock) k_keys_to_perm(const uint64_t *__restr
 }
 
 // cl[i] = max length of the chunk's rows in sorted order (Eq. (max));
-// csz[i] = C * cl[i] (scanned into cs afterwards); csz[nchunks] = 0.
+// csz[i] = C * cl[i] (scanned into cs afterwards); csz[nchunks] = 0. One lane
+// per row, so that the permuted lengths of a chunk are one access (one thread
+// per chunk took its C accesses in turn: 22 us on 1M rows, now CW_US), a fixed
+// grid striding over the rows, so that the sums cost one atomic per block.
 __global__ void __launch_bounds__(kBlock) k_chunkwidth(const int32_t *__restrict__ len,
                                                        const int32_t *__restrict__ perm, int64_t n, int C,
-                                                       int64_t nchunks, int32_t *__restrict__ cl,
-                                                       int64_t *__restrict__ csz) {
-  int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i > nchunks) return;
-  if (i == nchunks) {
-    csz[i] = 0;
-    return;
-  }
+                                                       int64_t nchunks, int T, int wpc, int32_t *__restrict__ cl,
+                                                       int64_t *__restrict__ csz,
+                                                       unsigned long long *__restrict__ total_steps,
+                                                       int32_t *__restrict__ max_width) {
+  __shared__ unsigned long long s_steps[kBlock / 64];
+  __shared__ int32_t s_mx[kBlock / 64];
+  const int span = C < 64 ? 64 : C;  // rows of a wave's turn: whole chunks
+  const int lane = lane_id(), width = C < 64 ? C : 64;
+  const int64_t rows = nchunks * C, stride = (int64_t)gridDim.x * (kBlock / 64) * span;
+  unsigned long long steps = 0;
   int32_t mx = 0;
-  int64_t p0 = i * C;
-  for (int r = 0; r < C; ++r) {
-    int64_t p = p0 + r;
-    if (p < n) {
-      int32_t l = len[perm ? perm[p] : p];
+  for (int64_t p0 = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * span; p0 < rows; p0 += stride) {
+    int32_t l = 0;
+    for (int64_t p = p0 + lane; p < p0 + span && p < n; p += 64) {
+      const int32_t v = len[perm ? (int64_t)perm[p] : p];
+      l = v > l ? v : l;
+    }
+    for (int off = width / 2; off > 0; off >>= 1) {
+      const int32_t o = __shfl_xor(l, off);
+      l = o > l ? o : l;
+    }
+    const int64_t i = (p0 + lane) / C;
+    if (lane % width == 0 && i < nchunks && p0 + lane < p0 + span) {
+      cl[i] = l;
+      csz[i] = (int64_t)C * l;
+      steps += (unsigned long long)((l + T - 1) / T) * wpc;
       mx = l > mx ? l : mx;
     }
   }
-  cl[i] = mx;
-  csz[i] = (int64_t)C * mx;
+  if (blockIdx.x == 0 && threadIdx.x == 0) csz[nchunks] = 0;
+  steps = wave_sum_u64(steps);
+  mx = wave_max(mx);
+  if (lane == 0) {
+    s_steps[threadIdx.x >> 6] = steps;
+    s_mx[threadIdx.x >> 6] = mx;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kBlock / 64; ++w) {
+      steps += s_steps[w];
+      mx = s_mx[w] > mx ? s_mx[w] : mx;
+    }
+    if (steps) atomicAdd(total_steps, steps);
+    if (mx) atomicMax(max_width, mx);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -508,25 +537,6 @@ __global__ void __launch_bounds__(kBlock) k_sorted_len(const int32_t *__restrict
   if (p < np) rl[p] = p < n ? len[perm ? (int64_t)perm[p] : p] : 0;
 }
 
-// One wave per split segment: the mean column of its rows at the middle of
-// the segment (rows that have ended hold column 0 there and don't count).
-__global__ void __launch_bounds__(kBlock) k_unit_cols(const Unit *__restrict__ units, int64_t n, int rpw, int wpc,
-                                                      int C, int32_t seg_cols, const int64_t *__restrict__ cs,
-                                                      const int32_t *__restrict__ cl,
-                                                      const int32_t *__restrict__ col, UnitCol *__restrict__ out) {
-  const int64_t w = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-  if (w >= n) return;
-  const Unit u = units[w];
-  const int64_t chunk = u.item / wpc;
-  const int64_t jb = (int64_t)u.seg * seg_cols;
-  const int64_t je = jb + seg_cols < cl[chunk] ? jb + seg_cols : cl[chunk];
-  const int r = lane_id();
-  unsigned long long c = 0;
-  if (r < rpw) c = (unsigned long long)col[cs[chunk] + (jb + je) / 2 * C + (u.item - chunk * wpc) * rpw + r];
-  const unsigned long long cnt = wave_sum_u64(c > 0 ? 1 : 0), sum = wave_sum_u64(c);
-  if (r == 0) out[w] = {cnt ? (int32_t)(sum / cnt) : 0, (int32_t)cnt};
-}
-
 // out[p] = in[perm[p]] (gather into sorted order) or out[perm[p]] = in[p]
 // (scatter back), for elements of ES bytes.
 template <typename E, bool SCATTER>
@@ -547,14 +557,6 @@ hipError_t build_sorted_len(const int32_t *len, const int32_t *perm, int64_t n, 
                             hipStream_t s) {
   if (np <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_sorted_len, dim3(blocks_for(np, kBlock)), dim3(kBlock), 0, s, len, perm, n, np, rl);
-  return hipGetLastError();
-}
-
-hipError_t build_unit_cols(const Unit *units, int64_t n, int rpw, int wpc, int C, int32_t seg_cols, const int64_t *cs,
-                           const int32_t *cl, const int32_t *col, UnitCol *out, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_unit_cols, dim3(blocks_for(n, kBlock / 64)), dim3(kBlock), 0, s, units, n, rpw, wpc, C,
-                     seg_cols, cs, cl, col, out);
   return hipGetLastError();
 }
 
@@ -629,10 +631,13 @@ hipError_t build_sort(const int32_t *len, int64_t n, int64_t sigma, uint64_t *ke
   return hipGetLastError();
 }
 
-hipError_t build_chunkwidth(const int32_t *len, const int32_t *perm, int64_t n, int C, int64_t nchunks,
-                            int32_t *cl, int64_t *csz, hipStream_t s) {
-  hipLaunchKernelGGL(k_chunkwidth, dim3(blocks_for(nchunks + 1, kBlock)), dim3(kBlock), 0, s, len, perm, n, C,
-                     nchunks, cl, csz);
+hipError_t build_chunkwidth(const int32_t *len, const int32_t *perm, int64_t n, int C, int64_t nchunks, int T, int wpc,
+                            int32_t *cl, int64_t *csz, int64_t *total_steps, int32_t *max_width, hipStream_t s) {
+  const int64_t per = (int64_t)(kBlock / 64) * (C < 64 ? 64 : C);
+  int64_t nb = (nchunks * C + per - 1) / per;
+  nb = nb < 1 ? 1 : nb > 1024 ? 1024 : nb;
+  hipLaunchKernelGGL(k_chunkwidth, dim3((unsigned)nb), dim3(kBlock), 0, s, len, perm, n, C, nchunks, T, wpc, cl, csz,
+                     reinterpret_cast<unsigned long long *>(total_steps), max_width);
   return hipGetLastError();
 }
 

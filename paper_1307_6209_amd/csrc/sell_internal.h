@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -82,15 +83,55 @@ constexpr int kBatchPersistentWaves = 1;
 // dispatcher sends workgroup b of a launch to XCD b mod kXcds.
 constexpr int kXcds = 8;
 
-// Split segments are placed on the XCDs by their columns (plan_single) from
-// this size of x on (one XCD's L2) and from this share of rows that hold an
-// entry on (measured gains at 0.75 to 0.98, losses at 0.35 and below).
-constexpr size_t kXcdMinX = 4 << 20;
-constexpr double kXcdMinLive = 0.6;
-
 // Segments of split chunks are whole multiples of this many chunk columns,
 // so that every kernel's step width (at most 64 columns) divides them.
 constexpr int kSegAlign = 64;
+
+// Split segments are placed on the XCDs by their columns from this size of x on
+// (one XCD's L2) and from this share of rows that hold an entry on. Measured in
+// chunk order / by column, us: 4,284 x 1,092,610, 2,633 entries per row, C = 16,
+// 32, 64 (shares 0.95, 0.90, 0.80) 111, 118, 124 / 65, 70, 100 (L2 misses 6.1 M
+// -> 1.6 M lines, of which 1.1 M are the matrix); power-law 2M, sigma = n (0.95)
+// 115 / 111. A row's entries are usually sorted, so a segment reads a range of
+// x, and an eighth of x stays in an L2. Where most of a segment is padding the
+// order of the chunks, whose rows lie near each other, wins: power-law 1M at
+// sigma = 1024 (0.07) 104 / 109, 2M at sigma = 2^14 (0.21) 144 / 159.
+constexpr size_t kXcdMinX = 4 << 20;
+constexpr double kXcdMinLive = 0.6;
+// Most segments that one workgroup orders (automatic widths: some 30,000).
+constexpr int64_t kXcdMaxSegs = 1 << 17;
+
+// Segment width of the block form (automatic): long enough that a unit
+// amortises its fixed cost (at least 64 wave steps), short enough that no unit
+// is much longer than an average wave's share of the whole product (resident
+// waves: CUs x 32). Converted from wave steps to chunk columns.
+__host__ __device__ inline int32_t round_seg(int64_t cols) {
+  int64_t s = (cols + kSegAlign - 1) / kSegAlign * kSegAlign;
+  if (s < kSegAlign) s = kSegAlign;
+  if (s > (1 << 30)) s = 1 << 30;
+  return (int32_t)s;
+}
+__host__ __device__ inline int32_t auto_seg_cols(int64_t total_steps, int T, int cus) {
+  const int64_t steps = total_steps / (2 * (int64_t)cus * 32);
+  return round_seg((steps < 64 ? 64 : steps) * T);
+}
+
+// Segment width of the single-vector product, at most S: at least eight wave
+// steps (one round of loads in flight) and 32 columns, more only where there
+// would be more than two segments per resident wave. The block form keeps
+// longer ones (S): its lanes walk the columns of a row alone and its segment
+// sums are k times as many. us at 32 / 64 / 128 / 256 columns, C = 32: power-law
+// 2M, sigma = n 109.7 / 111.0 / 115.4 / 116.0; 200k 13.3 / 15.8 / 24.4 / 24.3;
+// 1M, sigma = 1024, FP32 70.3 / 70.1 / 77.6 / 77.7; 4,284 rows of 2,633 entries
+// 72 / 70 / 82 / 87; at 16 columns 106, 14.5, 74 and 79.
+__host__ __device__ inline int32_t single_seg_cols(int64_t total_steps, int T, int cus, int32_t S) {
+  int64_t cols = total_steps / (2 * (int64_t)cus * 32);
+  cols = (cols < 8 ? 8 : cols) * T;
+  if (cols < 32) cols = 32;
+  const int64_t a = T > 16 ? T : 16;
+  cols = (cols + a - 1) / a * a;
+  return cols < S ? (int32_t)cols : S;
+}
 
 // Arguments of the spMVM kernels (by value).
 struct SpmvArgs {
@@ -211,8 +252,10 @@ hipError_t build_colcheck(const int32_t *col, int64_t nnz, int64_t ncols, uint32
 // Sorted row order for sigma > 1. keys_a/keys_b: two scratch arrays of n uint64.
 hipError_t build_sort(const int32_t *len, int64_t n, int64_t sigma, uint64_t *keys_a, uint64_t *keys_b,
                       int32_t *perm, hipStream_t s);
-hipError_t build_chunkwidth(const int32_t *len, const int32_t *perm, int64_t n, int C, int64_t nchunks,
-                            int32_t *cl, int64_t *csz, hipStream_t s);
+// total_steps: += wave steps of T columns over all items (wpc per chunk);
+// max_width: the widest chunk (both zeroed by the caller)
+hipError_t build_chunkwidth(const int32_t *len, const int32_t *perm, int64_t n, int C, int64_t nchunks, int T, int wpc,
+                            int32_t *cl, int64_t *csz, int64_t *total_steps, int32_t *max_width, hipStream_t s);
 // Exclusive scan of n int64 values (in-place allowed); tmp needs scan_tmp_elems(n) int64.
 int64_t scan_tmp_elems(int64_t n);
 hipError_t build_scan(const int64_t *in, int64_t *out, int64_t n, int64_t *tmp, hipStream_t s);
@@ -221,9 +264,35 @@ hipError_t build_fill(const int64_t *rpt, const int32_t *col, const double *val,
                       const int32_t *perm, const int64_t *cs, int64_t nchunks, int64_t padded, const int32_t *cmap,
                       int32_t *scol, void *sval, int val_dtype, hipStream_t s);
 hipError_t build_invert(const int32_t *perm, int64_t n, int32_t *iperm, hipStream_t s);
-// out[u]: where split segment u (u < n) of a unit list reads x.
-hipError_t build_unit_cols(const Unit *units, int64_t n, int rpw, int wpc, int C, int32_t seg_cols, const int64_t *cs,
-                           const int32_t *cl, const int32_t *col, UnitCol *out, hipStream_t s);
+// Sizes of a layout and of its work plans, counted on the device.
+struct PlanSizes {
+  int64_t total_steps;  // wave steps of all items (from build_chunkwidth)
+  int64_t nsplit, nsegs;            // block form: split slices, their segments
+  int64_t nsplit1, nsegs1, nwhole1;  // single-vector product
+  int32_t max_width;    // widest chunk (from build_chunkwidth)
+  int32_t pad;
+};
+struct PlanArgs {
+  const int32_t *cl;
+  int64_t nchunks, ncells;  // cells of grp chunks
+  int grp;                  // 64 / C for C in 8..32, else 1
+  int wpc, rpw, T, cus;
+  int32_t seg_cols;         // > 0: given (rounded), 0: automatic, < 0: never split
+  int64_t *blocks;          // 5 * plan_blocks(ncells)
+  PlanSizes *sizes;         // total_steps and max_width set, the rest written
+};
+struct PlanOut {
+  Unit *units;        // block form: nsegs segments, then the whole items
+  SplitDesc *splits;
+  Unit *units1;       // single-vector product
+  SplitDesc *splits1;
+  Unit *segs;         // nullptr, or nsegs1 segments for plan_place to put into units1
+};
+int64_t plan_blocks(int64_t ncells);
+hipError_t plan_count(const PlanArgs &a, hipStream_t s);
+hipError_t plan_emit(const PlanArgs &a, int32_t S, int32_t S1, const PlanSizes &z, const PlanOut &o, hipStream_t s);
+hipError_t plan_place(const PlanArgs &a, int C, int32_t S1, const PlanSizes &z, const PlanOut &o, const int64_t *cs,
+                      const int32_t *col, int64_t ncols, UnitCol *at, hipStream_t s);
 // rl[p] = length of the row in sorted position p (0 for p >= n), p < np
 hipError_t build_sorted_len(const int32_t *len, const int32_t *perm, int64_t n, int64_t np, int32_t *rl,
                             hipStream_t s);
@@ -307,8 +376,7 @@ struct sell_matrix {
   int64_t nsplit = 0;
   int64_t nsegs = 0;                  // total segments of split items
   sell::SplitDesc *splits = nullptr;  // per split id
-  int64_t partial_elems = 0;          // nsegs * rpw * next_pow2(kmax): doubles of the block form
-  void *partial = nullptr;            // that many, or what the single-vector plan needs where that is more
+  void *partial = nullptr;            // nsegs * rpw * next_pow2(kmax) doubles, or nsegs1 * rpw where that is more
 
   uint16_t *lcol = nullptr;     // x window mode: window position of every slot
   int64_t *xsegoff = nullptr;   // ngroups + 1 segment offsets
@@ -318,7 +386,8 @@ struct sell_matrix {
   int32_t xseg_max = 0;         // most segments of one window
   int32_t xw_gc = 0;            // chunks per window group
 
-  std::vector<int32_t> h_cl;    // host copy of the chunk widths (batch planning)
+  std::mutex cl_mu;
+  std::vector<int32_t> h_cl;    // host copy of the chunk widths, made when a batch is first planned with them
 
   sell_allocator alloc{};
   bool custom_alloc = false;
