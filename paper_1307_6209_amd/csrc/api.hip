@@ -341,14 +341,14 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
   int64_t sig = std::min<int64_t>(sigma, std::max<int64_t>(n, 1));
   if (sig > 1 && n > 1) {
     h->perm = static_cast<int32_t *>(owned_alloc(h.get(), mem, sizeof(int32_t) * (size_t)n));
-    uint64_t *ka = nullptr, *kb = nullptr;
-    if (sig > 4096) {
-      ka = static_cast<uint64_t *>(tmp.get(sizeof(uint64_t) * (size_t)n));
-      kb = static_cast<uint64_t *>(tmp.get(sizeof(uint64_t) * (size_t)n));
-      if (!ka || !kb) return fail(SELL_ERR_OOM, "sell_build: sort buffers");
+    int64_t *sort_tmp = nullptr;
+    const int64_t n_sort = sell::sort_tmp_elems(n, sig);
+    if (n_sort > 0) {
+      sort_tmp = static_cast<int64_t *>(tmp.get(sizeof(int64_t) * (size_t)n_sort));
+      if (!sort_tmp) return fail(SELL_ERR_OOM, "sell_build: sort buffers");
     }
     if (!h->perm) return fail(SELL_ERR_OOM, "sell_build: perm");
-    SELL_HIP(sell::build_sort(len, n, sig, ka, kb, h->perm, s));
+    SELL_HIP(sell::build_sort(len, n, sig, sort_tmp, h->perm, s));
   }
 
   // chunk widths and offsets
@@ -360,8 +360,8 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
   if (!h->cl || !h->cs || !scan_tmp) return fail(SELL_ERR_OOM, "sell_build: chunk arrays");
   const Geom &g = h->g;
   const DeviceInfo di = device_info();
-  SELL_HIP(sell::build_chunkwidth(len, h->perm, n, C, nc, g.T, g.wpc, h->cl, h->cs, &dsmall->plan.total_steps,
-                                  &dsmall->plan.max_width, s));
+  SELL_HIP(sell::build_chunkwidth(len, h->perm, n, C, nc, g.T, g.wpc, h->cl, h->cs, &dsmall->padded,
+                                  &dsmall->plan.total_steps, &dsmall->plan.max_width, s));
   sell::PlanArgs pa{};
   if (!layout_only) {
     pa.cl = h->cl;
@@ -378,7 +378,6 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
     SELL_HIP(sell::plan_count(pa, s));
   }
   SELL_HIP(sell::build_scan(h->cs, h->cs, nc + 1, scan_tmp, s));
-  SELL_HIP(hipMemcpyAsync(&dsmall->padded, h->cs + nc, sizeof(int64_t), hipMemcpyDeviceToDevice, s));
   Small hs{};
   SELL_HIP(hipMemcpyAsync(&hs, dsmall, sizeof(Small), hipMemcpyDeviceToHost, s));
   SELL_HIP(hipStreamSynchronize(s));

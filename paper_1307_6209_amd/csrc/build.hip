@@ -28,31 +28,53 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
   return v;
 }
 
+// Orders the LDS accesses of a wave's lanes among each other.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Validation flag bits.
 constexpr uint32_t F_RPT0 = 1u, F_DECR = 2u, F_COL = 4u, F_RPTN = 8u, F_LONG = 16u;
 
 // len[i] = rpt[i+1] - rpt[i]; flags for a malformed rpt; sum of squared
 // lengths (for the coefficient of variation) and the longest row. A fixed
-// grid strides over the rows and reduces per block, so the three global
-// atomics are issued once per block, not once per wave.
-__global__ void __launch_bounds__(kBlock) k_rowlen(const int64_t *__restrict__ rpt, int64_t n, int64_t nnz,
-                                                   int32_t *__restrict__ len, uint32_t *flags,
-                                                   unsigned long long *sumsq, int32_t *maxlen) {
-  __shared__ unsigned long long s_sq[kBlock / 64];
-  __shared__ int32_t s_mx[kBlock / 64];
-  __shared__ uint32_t s_f[kBlock / 64];
+// grid strides over the rows, U of a thread's loads in flight, and reduces per
+// block; the blocks' atomics on the three totals take turns (10 ns each: with
+// 1,024 blocks they made 20 of the 31 us that it took on 1M to 2M rows, now 11 to 13).
+constexpr int kStrideBlock = 1024;
+constexpr int kStrideGrid = 256;
+
+__global__ void __launch_bounds__(kStrideBlock) k_rowlen(const int64_t *__restrict__ rpt, int64_t n, int64_t nnz,
+                                                         int32_t *__restrict__ len, uint32_t *flags,
+                                                         unsigned long long *sumsq, int32_t *maxlen) {
+  constexpr int U = 4;
+  __shared__ unsigned long long s_sq[kStrideBlock / 64];
+  __shared__ int32_t s_mx[kStrideBlock / 64];
+  __shared__ uint32_t s_f[kStrideBlock / 64];
   uint32_t f = 0;
   int32_t mx = 0;
   unsigned long long sq = 0;
-  const int64_t stride = (int64_t)gridDim.x * kBlock;
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
-    int64_t d = rpt[i + 1] - rpt[i];
-    if (d < 0) f |= F_DECR;
-    if (d > 0x7fffffffLL) f |= F_LONG;
-    int32_t l = (d < 0 || d > 0x7fffffffLL) ? 0 : (int32_t)d;
-    len[i] = l;
-    sq += (unsigned long long)l * (unsigned long long)l;
-    mx = l > mx ? l : mx;
+  const int64_t stride = (int64_t)gridDim.x * kStrideBlock;
+  for (int64_t i0 = (int64_t)blockIdx.x * kStrideBlock + threadIdx.x; i0 < n; i0 += U * stride) {
+    int64_t d[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = i0 + u * stride;
+      d[u] = i < n ? rpt[i + 1] - rpt[i] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = i0 + u * stride;
+      if (i >= n) continue;
+      if (d[u] < 0) f |= F_DECR;
+      if (d[u] > 0x7fffffffLL) f |= F_LONG;
+      const int32_t l = (d[u] < 0 || d[u] > 0x7fffffffLL) ? 0 : (int32_t)d[u];
+      len[i] = l;
+      sq += (unsigned long long)l * (unsigned long long)l;
+      mx = l > mx ? l : mx;
+    }
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     if (rpt[0] != 0) f |= F_RPT0;
@@ -69,7 +91,7 @@ __global__ void __launch_bounds__(kBlock) k_rowlen(const int64_t *__restrict__ r
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int k = 1; k < kBlock / 64; ++k) {
+    for (int k = 1; k < kStrideBlock / 64; ++k) {
       sq += s_sq[k];
       mx = s_mx[k] > mx ? s_mx[k] : mx;
       f |= s_f[k];
@@ -80,14 +102,28 @@ __global__ void __launch_bounds__(kBlock) k_rowlen(const int64_t *__restrict__ r
   }
 }
 
+// Every column index within [0, ncols): 16 bytes an access, four in flight (the
+// array may start at any element: the first few and the last ones singly).
 __global__ void __launch_bounds__(kBlock) k_colcheck(const int32_t *__restrict__ col, int64_t nnz, int64_t ncols,
                                                      uint32_t *flags) {
-  int64_t stride = (int64_t)gridDim.x * kBlock;
+  constexpr int U = 4;
+  const int64_t head0 = (int64_t)((16 - (reinterpret_cast<uintptr_t>(col) & 15)) & 15) / 4;
+  const int64_t head = head0 < nnz ? head0 : nnz, quads = (nnz - head) / 4;
+  const int4 *q = reinterpret_cast<const int4 *>(col + head);
+  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x, stride = (int64_t)gridDim.x * kBlock;
+  const uint32_t lim = (uint32_t)ncols;  // below 2^31: a negative index is above it unsigned
   bool bad = false;
-  for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < nnz; j += stride) {
-    int32_t c = col[j];
-    bad |= (c < 0) | ((int64_t)c >= ncols);
+  for (int64_t j = t; j < quads; j += U * stride) {
+    int4 c[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) c[u] = j + u * stride < quads ? q[j + u * stride] : q[j];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      bad |= ((uint32_t)c[u].x >= lim) | ((uint32_t)c[u].y >= lim) | ((uint32_t)c[u].z >= lim) |
+             ((uint32_t)c[u].w >= lim);
   }
+  if (t < head) bad |= (uint32_t)col[t] >= lim;
+  if (t < nnz - head - 4 * quads) bad |= (uint32_t)col[head + 4 * quads + t] >= lim;
   if (__ballot(bad) != 0ull && lane_id() == 0) atomicOr(flags, F_COL);
 }
 
@@ -95,54 +131,36 @@ __global__ void __launch_bounds__(kBlock) k_colcheck(const int32_t *__restrict__
 // sigma-window sort.
 //
 // Rows are ordered by descending length inside each window of sigma rows,
-// ties by ascending row index. Each element gets a 64-bit key that is unique
-// and whose ascending order is that order:
-//   (window-in-tile, INT32_MAX - len, index)   when sigma <= kTile
-//   (INT32_MAX - len, index in window)         when sigma >  kTile
-// Step 1 sorts tiles of kTile keys in LDS (bitonic network). A tile is a run
-// of whole windows (sigma <= kTile) or a kTile-aligned piece of one window.
-// Step 2 (sigma > kTile only) merges sorted runs pairwise inside each
-// window: with unique keys an element's place in the merged run is its
-// place in its own run plus the number of smaller keys in the partner run,
-// found by binary search.
+// ties by ascending row index.
+//
+// sigma <= kTile: tiles of whole windows are sorted in LDS (bitonic network)
+// by a 64-bit key that is unique and whose ascending order is that order:
+// (window in the tile, INT32_MAX - len, index).
+//
+// sigma > kTile: two stable counting passes over tiles of kTile rows of one
+// window, by the low byte of the length and then by the rest of it (255 for all
+// of 65,280 or more), longest first: counts per (window, digit, tile), their
+// exclusive prefix, ranks inside the tile. Rows of 65,280 entries or more, at most
+// nnz / 65,280, then stand in front of their window in the order of their low
+// byte; k_sort_longest puts them right. (Sorted tiles merged pairwise, log2(sigma
+// / kTile) passes of binary searches: 191 us on one window of 1M rows, now
+// 47.)
 // ---------------------------------------------------------------------------
 constexpr int kTile = 4096;
 constexpr int kSortBlock = 512;
 
 __global__ void __launch_bounds__(kSortBlock) k_sort_tiles(const int32_t *__restrict__ len, int64_t n,
-                                                           int64_t sigma, uint64_t *__restrict__ keys_out,
-                                                           int32_t *__restrict__ perm_out) {
+                                                           int64_t sigma, int32_t *__restrict__ perm_out) {
   __shared__ uint64_t sk[kTile];
-  int64_t start, count;
-  bool small = sigma <= kTile;
-  int64_t wper = 1;
-  if (small) {
-    wper = kTile / sigma;  // whole windows per tile
-    int64_t tile_rows = wper * sigma;
-    start = (int64_t)blockIdx.x * tile_rows;
-    count = n - start < tile_rows ? n - start : tile_rows;
-  } else {
-    int64_t tiles_per_win = (sigma + kTile - 1) / kTile;
-    int64_t w = blockIdx.x / tiles_per_win, tw = blockIdx.x % tiles_per_win;
-    int64_t wstart = w * sigma;
-    int64_t wlen = n - wstart < sigma ? n - wstart : sigma;
-    start = wstart + tw * kTile;
-    int64_t end = wstart + wlen;
-    count = start >= end ? 0 : (end - start < kTile ? end - start : kTile);
-  }
+  const int64_t tile_rows = kTile / sigma * sigma;  // whole windows per tile
+  const int64_t start = (int64_t)blockIdx.x * tile_rows;
+  const int64_t count = n - start < tile_rows ? n - start : tile_rows;
   if (count <= 0) return;  // uniform over the block
   for (int q = threadIdx.x; q < kTile; q += kSortBlock) {
     uint64_t key = ~0ull;
     if (q < count) {
-      int64_t i = start + q;
-      uint64_t inv = (uint64_t)(0x7fffffff - len[i]);
-      if (small) {
-        uint64_t wl = (uint64_t)(q / sigma);
-        key = (wl << 44) | (inv << 13) | (uint64_t)q;
-      } else {
-        int64_t wstart = (i / sigma) * sigma;
-        key = (inv << 32) | (uint64_t)(i - wstart);
-      }
+      const uint64_t inv = (uint64_t)(0x7fffffff - len[start + q]), wl = (uint64_t)(q / sigma);
+      key = (wl << 44) | (inv << 13) | (uint64_t)q;
     }
     sk[q] = key;
   }
@@ -163,69 +181,157 @@ __global__ void __launch_bounds__(kSortBlock) k_sort_tiles(const int32_t *__rest
       __syncthreads();
     }
   }
-  for (int q = threadIdx.x; q < count; q += kSortBlock) {
-    uint64_t key = sk[q];
-    if (small) {
-      perm_out[start + q] = (int32_t)(start + (int64_t)(key & 0x1fffull));
-    } else {
-      keys_out[start + q] = key;
+  for (int q = threadIdx.x; q < count; q += kSortBlock)
+    perm_out[start + q] = (int32_t)(start + (int64_t)(sk[q] & 0x1fffull));
+}
+
+// Tile b of the counting passes: rows [start, start + count) of window w.
+struct SortTile {
+  int64_t start, w, tw;
+  int count;
+};
+__device__ __forceinline__ SortTile sort_tile(int64_t b, int64_t n, int64_t sigma, int64_t per_window) {
+  SortTile t;
+  t.w = b / per_window;
+  t.tw = b - t.w * per_window;
+  t.start = t.w * sigma + t.tw * kTile;
+  const int64_t end = (t.w + 1) * sigma < n ? (t.w + 1) * sigma : n;
+  t.count = end - t.start < kTile ? (end > t.start ? (int)(end - t.start) : 0) : kTile;
+  return t;
+}
+
+// Digit of a length, 0 for the longest.
+template <int PASS>
+__device__ __forceinline__ int sort_digit(uint32_t len) {
+  if (PASS == 0) return 255 - (int)(len & 255u);
+  return 255 - (int)(len >> 8 < 255u ? len >> 8 : 255u);
+}
+
+// Row q of the tile: before pass 0 the rows in order, then what pass 0 left
+// ((length, row) in 32 bits each).
+template <int PASS>
+__device__ __forceinline__ uint64_t sort_item(const int32_t *__restrict__ len, const uint64_t *__restrict__ in,
+                                              int64_t i) {
+  return PASS == 0 ? (uint64_t)(uint32_t)len[i] << 32 | (uint64_t)i : in[i];
+}
+
+template <int PASS>
+__global__ void __launch_bounds__(kSortBlock) k_sort_count(const int32_t *__restrict__ len,
+                                                           const uint64_t *__restrict__ in, int64_t n, int64_t sigma,
+                                                           int64_t per_window, int64_t *__restrict__ counts) {
+  __shared__ int32_t hist[256];
+  const SortTile t = sort_tile(blockIdx.x, n, sigma, per_window);
+  if (threadIdx.x < 256) hist[threadIdx.x] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kTile / kSortBlock; ++k) {
+    const int q = k * kSortBlock + threadIdx.x;
+    if (q < t.count) atomicAdd(&hist[sort_digit<PASS>((uint32_t)(sort_item<PASS>(len, in, t.start + q) >> 32))], 1);
+  }
+  __syncthreads();
+  if (threadIdx.x < 256) counts[(t.w * 256 + threadIdx.x) * per_window + t.tw] = hist[threadIdx.x];
+}
+
+// Wave v of the block takes the tile's rows [512 v, 512 v + 512) in strips of
+// 64: a row's place is its digit's (the prefix of the counts, which covers all
+// windows in turn, plus the earlier waves' rows of the digit) plus its rank among
+// the digit's rows of the wave so far and of its strip.
+template <int PASS>
+__global__ void __launch_bounds__(kSortBlock) k_sort_place(const int32_t *__restrict__ len,
+                                                           const uint64_t *__restrict__ in, int64_t n, int64_t sigma,
+                                                           int64_t per_window, const int64_t *__restrict__ places,
+                                                           uint64_t *__restrict__ out, int32_t *__restrict__ perm) {
+  constexpr int WAVES = kSortBlock / 64, STRIPS = kTile / kSortBlock;
+  __shared__ int32_t next[WAVES][256];
+  const SortTile t = sort_tile(blockIdx.x, n, sigma, per_window);
+  const int lane = lane_id(), v = threadIdx.x >> 6;
+  for (int d = lane; d < 256; d += 64) next[v][d] = 0;
+  wave_sync();
+  uint64_t item[STRIPS];
+#pragma unroll
+  for (int k = 0; k < STRIPS; ++k) {
+    const int q = (v * STRIPS + k) * 64 + lane;
+    item[k] = q < t.count ? sort_item<PASS>(len, in, t.start + q) : 0;
+  }
+#pragma unroll
+  for (int k = 0; k < STRIPS; ++k)
+    if ((v * STRIPS + k) * 64 + lane < t.count) atomicAdd(&next[v][sort_digit<PASS>((uint32_t)(item[k] >> 32))], 1);
+  __syncthreads();
+  if (threadIdx.x < 256) {
+    int32_t at = (int32_t)places[(t.w * 256 + threadIdx.x) * per_window + t.tw];
+#pragma unroll
+    for (int u = 0; u < WAVES; ++u) {
+      const int32_t c = next[u][threadIdx.x];
+      next[u][threadIdx.x] = at;
+      at += c;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < STRIPS; ++k) {
+    const bool real = (v * STRIPS + k) * 64 + lane < t.count;
+    const int d = sort_digit<PASS>((uint32_t)(item[k] >> 32));
+    unsigned long long same = __ballot(real);  // lanes with this lane's digit
+#pragma unroll
+    for (int bit = 0; bit < 8; ++bit) {
+      const unsigned long long b = __ballot((d >> bit) & 1);
+      same &= (d >> bit) & 1 ? b : ~b;
+    }
+    const int rank = __popcll(same & ((1ull << lane) - 1ull));
+    int32_t at = 0;
+    if (real) at = next[v][d] + rank;
+    wave_sync();
+    if (real && rank == 0) next[v][d] += __popcll(same);
+    wave_sync();
+    if (real) {
+      if (PASS == 0) out[at] = item[k];
+      else perm[at] = (int32_t)(uint32_t)item[k];
     }
   }
 }
 
-__global__ void __launch_bounds__(kBlock) k_merge_runs(const uint64_t *__restrict__ in, uint64_t *__restrict__ out,
-                                                       int64_t n, int64_t sigma, int64_t R) {
-  int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
-  int64_t wstart = (i / sigma) * sigma;
-  int64_t wlen = n - wstart < sigma ? n - wstart : sigma;
-  int64_t q = i - wstart;
-  int64_t run = q / R;
-  int64_t pstart = (run ^ 1) * R;
-  uint64_t key = in[i];
-  if (pstart >= wlen) {
-    out[i] = key;
-    return;
+// One workgroup per window: its rows of 65,280 entries or more by length and
+// row, each row's place counted among them; tmp: n int32.
+__global__ void __launch_bounds__(kBlock) k_sort_longest(const int32_t *__restrict__ len, int64_t sigma,
+                                                         int64_t per_window, const int64_t *__restrict__ places,
+                                                         int32_t *__restrict__ tmp, int32_t *__restrict__ perm) {
+  const int64_t w0 = (int64_t)blockIdx.x * sigma;
+  const int64_t m = places[((int64_t)blockIdx.x * 256 + 1) * per_window] - w0;  // rows of digit 0
+  if (m <= 1) return;
+  for (int64_t e = threadIdx.x; e < m; e += kBlock) {
+    const int32_t row = perm[w0 + e], l = len[row];
+    int64_t at = 0;
+    for (int64_t q = 0; q < m; ++q) {
+      const int32_t r2 = perm[w0 + q], l2 = len[r2];
+      at += l2 > l || (l2 == l && r2 < row);
+    }
+    tmp[w0 + at] = row;
   }
-  int64_t pend = pstart + R < wlen ? pstart + R : wlen;
-  // number of partner keys smaller than key (keys are unique)
-  int64_t lo = pstart, hi = pend;
-  while (lo < hi) {
-    int64_t mid = (lo + hi) >> 1;
-    if (in[wstart + mid] < key) lo = mid + 1;
-    else hi = mid;
-  }
-  int64_t pos = ((run & ~(int64_t)1) * R) + (q - run * R) + (lo - pstart);
-  out[wstart + pos] = key;
-}
-
-__global__ void __launch_bounds__(kBlock) k_keys_to_perm(const uint64_t *__restrict__ keys, int64_t n, int64_t sigma,
-                                                         int32_t *__restrict__ perm) {
-  int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
-  int64_t wstart = (i / sigma) * sigma;
-  perm[i] = (int32_t)(wstart + (int64_t)(keys[i] & 0xffffffffull));
+  __syncthreads();
+  for (int64_t e = threadIdx.x; e < m; e += kBlock) perm[w0 + e] = tmp[w0 + e];
 }
 
 // cl[i] = max length of the chunk's rows in sorted order (Eq. (max));
 // csz[i] = C * cl[i] (scanned into cs afterwards); csz[nchunks] = 0. One lane
 // per row, so that the permuted lengths of a chunk are one access (one thread
-// per chunk took its C accesses in turn: 22 us on 1M rows, now CW_US), a fixed
+// per chunk took its C accesses in turn: 22 us on 1M rows, now 10), a fixed
 // grid striding over the rows, so that the sums cost one atomic per block.
-__global__ void __launch_bounds__(kBlock) k_chunkwidth(const int32_t *__restrict__ len,
+__global__ void __launch_bounds__(kStrideBlock) k_chunkwidth(const int32_t *__restrict__ len,
                                                        const int32_t *__restrict__ perm, int64_t n, int C,
                                                        int64_t nchunks, int T, int wpc, int32_t *__restrict__ cl,
                                                        int64_t *__restrict__ csz,
+                                                       unsigned long long *__restrict__ padded,
                                                        unsigned long long *__restrict__ total_steps,
                                                        int32_t *__restrict__ max_width) {
-  __shared__ unsigned long long s_steps[kBlock / 64];
-  __shared__ int32_t s_mx[kBlock / 64];
+  __shared__ unsigned long long s_cols[kStrideBlock / 64];
+  __shared__ unsigned long long s_steps[kStrideBlock / 64];
+  __shared__ int32_t s_mx[kStrideBlock / 64];
   const int span = C < 64 ? 64 : C;  // rows of a wave's turn: whole chunks
   const int lane = lane_id(), width = C < 64 ? C : 64;
-  const int64_t rows = nchunks * C, stride = (int64_t)gridDim.x * (kBlock / 64) * span;
-  unsigned long long steps = 0;
+  const int64_t rows = nchunks * C, stride = (int64_t)gridDim.x * (kStrideBlock / 64) * span;
+  unsigned long long steps = 0, cols = 0;
   int32_t mx = 0;
-  for (int64_t p0 = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * span; p0 < rows; p0 += stride) {
+  for (int64_t p0 = ((int64_t)blockIdx.x * (kStrideBlock / 64) + (threadIdx.x >> 6)) * span; p0 < rows; p0 += stride) {
     int32_t l = 0;
     for (int64_t p = p0 + lane; p < p0 + span && p < n; p += 64) {
       const int32_t v = len[perm ? (int64_t)perm[p] : p];
@@ -239,24 +345,31 @@ __global__ void __launch_bounds__(kBlock) k_chunkwidth(const int32_t *__restrict
     if (lane % width == 0 && i < nchunks && p0 + lane < p0 + span) {
       cl[i] = l;
       csz[i] = (int64_t)C * l;
-      steps += (unsigned long long)((l + T - 1) / T) * wpc;
+      steps += (unsigned long long)(((int64_t)l + T - 1) / T) * wpc;
+      cols += (unsigned long long)l;
       mx = l > mx ? l : mx;
     }
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) csz[nchunks] = 0;
   steps = wave_sum_u64(steps);
+  cols = wave_sum_u64(cols);
   mx = wave_max(mx);
   if (lane == 0) {
     s_steps[threadIdx.x >> 6] = steps;
+    s_cols[threadIdx.x >> 6] = cols;
     s_mx[threadIdx.x >> 6] = mx;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < kBlock / 64; ++w) {
+    for (int w = 1; w < kStrideBlock / 64; ++w) {
       steps += s_steps[w];
+      cols += s_cols[w];
       mx = s_mx[w] > mx ? s_mx[w] : mx;
     }
-    if (steps) atomicAdd(total_steps, steps);
+    if (steps) {
+      atomicAdd(total_steps, steps);
+      atomicAdd(padded, cols * (unsigned long long)C);
+    }
     if (mx) atomicMax(max_width, mx);
   }
 }
@@ -349,13 +462,6 @@ __device__ __forceinline__ void st_val(void *sval, int64_t s, double v) {
   if (VD == SELL_F64) static_cast<double *>(sval)[s] = v;
   else if (VD == SELL_F32) static_cast<float *>(sval)[s] = f64_to_f32_rne(v);
   else static_cast<uint16_t *>(sval)[s] = f64_to_bf16_rne(v);
-}
-
-// Orders the LDS accesses of a wave's lanes among each other.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Last i in [lo, hi) with cs[i] <= s (cs[lo] <= s).
@@ -590,53 +696,61 @@ hipError_t permute_vector(const void *in, void *out, const int32_t *perm, int64_
 
 hipError_t build_rowlen(const int64_t *rpt, int64_t n, int64_t nnz, int32_t *len, uint32_t *flags,
                         unsigned long long *sumsq, int32_t *maxlen, hipStream_t s) {
-  unsigned nb = blocks_for(n > 0 ? n : 1, kBlock);
-  if (nb > 1024) nb = 1024;
-  hipLaunchKernelGGL(k_rowlen, dim3(nb), dim3(kBlock), 0, s, rpt, n, nnz, len, flags, sumsq, maxlen);
+  unsigned nb = blocks_for(n > 0 ? n : 1, kStrideBlock);
+  if (nb > kStrideGrid) nb = kStrideGrid;
+  hipLaunchKernelGGL(k_rowlen, dim3(nb), dim3(kStrideBlock), 0, s, rpt, n, nnz, len, flags, sumsq, maxlen);
   return hipGetLastError();
 }
 
 hipError_t build_colcheck(const int32_t *col, int64_t nnz, int64_t ncols, uint32_t *flags, hipStream_t s) {
   if (nnz <= 0) return hipSuccess;
-  int64_t nb = blocks_for(nnz, kBlock);
-  if (nb > 65536) nb = 65536;
+  int64_t nb = blocks_for((nnz + 15) / 16, kBlock);
+  if (nb > 4096) nb = 4096;
   hipLaunchKernelGGL(k_colcheck, dim3((unsigned)nb), dim3(kBlock), 0, s, col, nnz, ncols, flags);
   return hipGetLastError();
 }
 
-hipError_t build_sort(const int32_t *len, int64_t n, int64_t sigma, uint64_t *keys_a, uint64_t *keys_b,
-                      int32_t *perm, hipStream_t s) {
+int64_t sort_tmp_elems(int64_t n, int64_t sigma) {
+  if (sigma > n) sigma = n;
+  if (sigma <= kTile) return 0;
+  const int64_t counts = (n + sigma - 1) / sigma * ((sigma + kTile - 1) / kTile) * 256;
+  return n + counts + scan_tmp_elems(counts);
+}
+
+hipError_t build_sort(const int32_t *len, int64_t n, int64_t sigma, int64_t *tmp, int32_t *perm, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   if (sigma > n) sigma = n;
-  int64_t ntiles;
   if (sigma <= kTile) {
-    int64_t tile_rows = (kTile / sigma) * sigma;
-    ntiles = (n + tile_rows - 1) / tile_rows;
-  } else {
-    int64_t nwin = (n + sigma - 1) / sigma;
-    ntiles = nwin * ((sigma + kTile - 1) / kTile);
+    const int64_t tile_rows = (kTile / sigma) * sigma;
+    hipLaunchKernelGGL(k_sort_tiles, dim3(blocks_for(n, (int)tile_rows)), dim3(kSortBlock), 0, s, len, n, sigma, perm);
+    return hipGetLastError();
   }
-  hipLaunchKernelGGL(k_sort_tiles, dim3((unsigned)ntiles), dim3(kSortBlock), 0, s, len, n, sigma, keys_a, perm);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || sigma <= kTile) return e;
-  uint64_t *in = keys_a, *out = keys_b;
-  for (int64_t R = kTile; R < sigma; R <<= 1) {
-    hipLaunchKernelGGL(k_merge_runs, dim3(blocks_for(n, kBlock)), dim3(kBlock), 0, s, in, out, n, sigma, R);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    uint64_t *t = in;
-    in = out;
-    out = t;
-  }
-  hipLaunchKernelGGL(k_keys_to_perm, dim3(blocks_for(n, kBlock)), dim3(kBlock), 0, s, in, n, sigma, perm);
+  const int64_t nwin = (n + sigma - 1) / sigma, per = (sigma + kTile - 1) / kTile, ncounts = nwin * per * 256;
+  uint64_t *items = reinterpret_cast<uint64_t *>(tmp);
+  int64_t *counts = tmp + n, *stmp = counts + ncounts;
+  const dim3 tiles((unsigned)(nwin * per));
+  hipError_t e;
+  hipLaunchKernelGGL(k_sort_count<0>, tiles, dim3(kSortBlock), 0, s, len, items, n, sigma, per, counts);
+  if ((e = hipGetLastError()) != hipSuccess || (e = build_scan(counts, counts, ncounts, stmp, s)) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_sort_place<0>, tiles, dim3(kSortBlock), 0, s, len, nullptr, n, sigma, per, counts, items, perm);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_sort_count<1>, tiles, dim3(kSortBlock), 0, s, len, items, n, sigma, per, counts);
+  if ((e = hipGetLastError()) != hipSuccess || (e = build_scan(counts, counts, ncounts, stmp, s)) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_sort_place<1>, tiles, dim3(kSortBlock), 0, s, len, items, n, sigma, per, counts, nullptr, perm);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_sort_longest, dim3((unsigned)nwin), dim3(kBlock), 0, s, len, sigma, per, counts,
+                     reinterpret_cast<int32_t *>(items), perm);
   return hipGetLastError();
 }
 
 hipError_t build_chunkwidth(const int32_t *len, const int32_t *perm, int64_t n, int C, int64_t nchunks, int T, int wpc,
-                            int32_t *cl, int64_t *csz, int64_t *total_steps, int32_t *max_width, hipStream_t s) {
-  const int64_t per = (int64_t)(kBlock / 64) * (C < 64 ? 64 : C);
+                            int32_t *cl, int64_t *csz, int64_t *padded, int64_t *total_steps, int32_t *max_width,
+                            hipStream_t s) {
+  const int64_t per = (int64_t)(kStrideBlock / 64) * (C < 64 ? 64 : C);
   int64_t nb = (nchunks * C + per - 1) / per;
-  nb = nb < 1 ? 1 : nb > 1024 ? 1024 : nb;
-  hipLaunchKernelGGL(k_chunkwidth, dim3((unsigned)nb), dim3(kBlock), 0, s, len, perm, n, C, nchunks, T, wpc, cl, csz,
+  nb = nb < 1 ? 1 : nb > kStrideGrid ? kStrideGrid : nb;
+  hipLaunchKernelGGL(k_chunkwidth, dim3((unsigned)nb), dim3(kStrideBlock), 0, s, len, perm, n, C, nchunks, T, wpc, cl, csz,
+                     reinterpret_cast<unsigned long long *>(padded),
                      reinterpret_cast<unsigned long long *>(total_steps), max_width);
   return hipGetLastError();
 }

@@ -114,12 +114,15 @@ __global__ void __launch_bounds__(kPlanBlock) k_plan_count(PlanArgs a) {
   if (cell < a.ncells) n = count_cell(a, cell_of(a, cell), S, S1);
   block_prefix(n, &total);
   if (threadIdx.x == 0) {
-    int64_t *b = a.blocks + 5 * (int64_t)blockIdx.x;
+    // a single block: its prefixes are zero, its counts the totals
+    int64_t *b = gridDim.x > 1 ? a.blocks + 5 * (int64_t)blockIdx.x : &a.sizes->nsplit;
     b[0] = total.split0;
     b[1] = total.seg0;
     b[2] = total.split1;
     b[3] = total.seg1;
     b[4] = total.whole1;
+    if (gridDim.x == 1)
+      for (int q = 0; q < 5; ++q) a.blocks[q] = 0;
   }
 }
 
@@ -287,7 +290,7 @@ hipError_t plan_count(const PlanArgs &a, hipStream_t s) {
   if (a.ncells <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_plan_count, grid(a.ncells), dim3(kPlanBlock), 0, s, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || plan_blocks(a.ncells) == 1) return e;
   hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(5 * 64), 0, s, a, plan_blocks(a.ncells));
   return hipGetLastError();
 }

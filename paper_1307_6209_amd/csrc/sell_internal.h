@@ -249,13 +249,14 @@ int batch_waves_per_cu(int combo, int C, int U);
 hipError_t build_rowlen(const int64_t *rpt, int64_t n, int64_t nnz, int32_t *len, uint32_t *flags,
                         unsigned long long *sumsq, int32_t *maxlen, hipStream_t s);
 hipError_t build_colcheck(const int32_t *col, int64_t nnz, int64_t ncols, uint32_t *flags, hipStream_t s);
-// Sorted row order for sigma > 1. keys_a/keys_b: two scratch arrays of n uint64.
-hipError_t build_sort(const int32_t *len, int64_t n, int64_t sigma, uint64_t *keys_a, uint64_t *keys_b,
-                      int32_t *perm, hipStream_t s);
-// total_steps: += wave steps of T columns over all items (wpc per chunk);
-// max_width: the widest chunk (both zeroed by the caller)
+// Sorted row order for sigma > 1; tmp needs sort_tmp_elems(n, sigma) int64.
+int64_t sort_tmp_elems(int64_t n, int64_t sigma);
+hipError_t build_sort(const int32_t *len, int64_t n, int64_t sigma, int64_t *tmp, int32_t *perm, hipStream_t s);
+// padded, total_steps: += the slots, the wave steps of T columns over all items
+// (wpc per chunk); max_width: the widest chunk (all zeroed by the caller)
 hipError_t build_chunkwidth(const int32_t *len, const int32_t *perm, int64_t n, int C, int64_t nchunks, int T, int wpc,
-                            int32_t *cl, int64_t *csz, int64_t *total_steps, int32_t *max_width, hipStream_t s);
+                            int32_t *cl, int64_t *csz, int64_t *padded, int64_t *total_steps, int32_t *max_width,
+                            hipStream_t s);
 // Exclusive scan of n int64 values (in-place allowed); tmp needs scan_tmp_elems(n) int64.
 int64_t scan_tmp_elems(int64_t n);
 hipError_t build_scan(const int64_t *in, int64_t *out, int64_t n, int64_t *tmp, hipStream_t s);
