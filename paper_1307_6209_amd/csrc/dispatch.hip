@@ -133,4 +133,23 @@ hipError_t launch_spmmv_any(int C, bool local, const SpmvArgs &a, hipStream_t s)
   return hipGetLastError();
 }
 
+size_t spmmv_xw_lds(int kb, const XwArgs &w, int maxseg) {
+  return (size_t)w.wcap * (size_t)kb * sizeof(double) + sizeof(int2) * (size_t)maxseg;
+}
+
+hipError_t launch_spmmv_xw(int C, int kb, int turns, const SpmvArgs &a, const XwArgs &w, size_t lds, hipStream_t s) {
+  const dim3 nb((unsigned)((a.nwork + w.gc - 1) / w.gc), (unsigned)((a.k + kb * turns - 1) / (kb * turns)));
+#define SELL_L(CC, GG, KK, HH)                                                                       \
+  if (C == CC && w.gc == GG && kb == KK && turns == HH) {                                           \
+    hipLaunchKernelGGL((dev::k_spmmv_xw<CC, GG, KK, HH>), nb, dim3(64 * GG), lds, s, a, w);         \
+    return hipGetLastError();                                                                       \
+  }
+#define SELL_LG(GG, KK, HH) SELL_L(16, GG, KK, HH) SELL_L(32, GG, KK, HH) SELL_L(64, GG, KK, HH)
+  SELL_LG(4, 4, 1) SELL_LG(4, 4, 2) SELL_LG(4, 4, 4) SELL_LG(8, 4, 1) SELL_LG(8, 4, 2) SELL_LG(8, 4, 4)
+  SELL_LG(4, 8, 1) SELL_LG(4, 8, 2) SELL_LG(8, 8, 1) SELL_LG(8, 8, 2)
+#undef SELL_LG
+#undef SELL_L
+  return hipErrorInvalidValue;
+}
+
 }  // namespace sell

@@ -1135,6 +1135,183 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) k_spmmv_any(SpmvArgs a, i
   }
 }
 
+// Value of lane q of each run of G lanes (G 2 or 4: within a quad, G 8: by way
+// of LDS).
+template <int G>
+__device__ __forceinline__ int from_lane(int v, int q, int lane) {
+  if constexpr (G == 1) return v;
+  else if constexpr (G == 2)
+    return q == 0 ? __builtin_amdgcn_update_dpp(0, v, 0xA0, 0xf, 0xf, true)
+                  : __builtin_amdgcn_update_dpp(0, v, 0xF5, 0xf, 0xf, true);
+  else if constexpr (G == 4)
+    return q == 0   ? __builtin_amdgcn_update_dpp(0, v, 0x00, 0xf, 0xf, true)
+           : q == 1 ? __builtin_amdgcn_update_dpp(0, v, 0x55, 0xf, 0xf, true)
+           : q == 2 ? __builtin_amdgcn_update_dpp(0, v, 0xAA, 0xf, 0xf, true)
+                    : __builtin_amdgcn_update_dpp(0, v, 0xFF, 0xf, 0xf, true);
+  else return __shfl(v, (lane & ~(G - 1)) | q);
+}
+template <int G>
+__device__ __forceinline__ double from_lane(double v, int q, int lane) {
+  int w[2];
+  __builtin_memcpy(w, &v, 8);
+  w[0] = from_lane<G>(w[0], q, lane);
+  w[1] = from_lane<G>(w[1], q, lane);
+  __builtin_memcpy(&v, w, 8);
+  return v;
+}
+
+// Block form on layouts with x windows (FP64): workgroup g (GC waves, one chunk
+// each) stages its window of X in LDS, KB right-hand sides at a time, H times
+// over, and every slot finds its row of X by its 16-bit window position; the
+// first 28 columns of a chunk stay in registers meanwhile, so the matrix is read
+// once for KB * H right-hand sides (from blockIdx.y * KB * H on). In the other
+// block kernels each nonzero reads its row of X through L1, which holds little
+// of it, so that on a stencil the L2s' rate bounds them (27 rows of 64 bytes per
+// row of Y at k = 8, 1.5 GB on 96^3). KB = 4 keeps the window of 256 stencil rows
+// at 43 KB and three workgroups on a CU; k = 8 takes 90 us there with H = 2, 130
+// with 8 at once (86 KB, one workgroup), 122 in k_spmmv. U = 28 / G steps in
+// flight hold a chunk of the stencil in 76 VGPRs, six waves per SIMD; with 32 it
+// was 82, five waves and 106 us. G = 64 / C lanes share a row,
+// KV = KB / G right-hand sides each; a lane loads one of the G columns of a step,
+// its neighbours get it by a lane move. Per row the products are added in column
+// order and slots holding 0 skip X, as in k_spmmv: the same bits.
+template <int C, int GC, int KB, int H>
+__global__ void __launch_bounds__(64 * GC) k_spmmv_xw(SpmvArgs a, XwArgs xa) {
+  constexpr int G = 64 / C, KV = KB / G;
+  constexpr int U = 28 / G;       // steps of G columns in flight
+  constexpr int PP = KB / 2;      // pairs of right-hand sides of a window row
+  static_assert(KV >= 1 && KB % 2 == 0, "a lane holds at least one right-hand side");
+  extern __shared__ __align__(16) unsigned char xw_lds[];
+  double *xw = reinterpret_cast<double *>(xw_lds);
+  int2 *segt = reinterpret_cast<int2 *>(xw_lds + (size_t)xa.wcap * KB * sizeof(double));
+
+  int64_t grp = blockIdx.x;  // XCD tiles, as in k_spmv_xw
+  {
+    const int64_t nb = gridDim.x, xcd = grp % 8, i = grp / 8;
+    if (grp < nb / (8 * kXcdTile) * (8 * kXcdTile))
+      grp = (i / kXcdTile) * 8 * kXcdTile + xcd * kXcdTile + i % kXcdTile;
+  }
+  const int lane = threadIdx.x & 63;
+  const int64_t chunk = grp * GC + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const bool live = chunk < a.nwork;
+  const int64_t base = live ? a.cs[chunk] : 0;
+  const int cl = live ? a.cl[chunk] : 0;
+  const int r = lane / G, g = lane % G;
+  const uint32_t lo0 = (uint32_t)(g * C + r);  // slot of step s: s * 64 + lo0
+  const __amdgpu_buffer_rsrc_t rc = chunk_rsrc(xa.lcol + base, (int64_t)C * cl);
+  const __amdgpu_buffer_rsrc_t rv = chunk_rsrc(static_cast<const double *>(a.val) + base, (int64_t)C * cl);
+  const int k = a.k;
+
+  const int64_t s0 = xa.segoff[grp];
+  const int ns = (int)(xa.segoff[grp + 1] - s0);
+  // the first U steps (slots past the chunk read as 0)
+  uint16_t ci[U][1];
+  double vv[U][1];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    ld_buf<1>(rc, lo0 + 64u * u, ci[u]);
+    ld_buf<1>(rv, lo0 + 64u * u, vv[u]);
+  }
+  for (int q = threadIdx.x; q < ns; q += 64 * GC)
+    segt[q] = make_int2(xa.seg[3 * (s0 + q)], xa.seg[3 * (s0 + q) + 1]);
+  const int nwin = ns > 0 ? xa.seg[3 * (s0 + ns - 1) + 1] + xa.seg[3 * (s0 + ns - 1) + 2] : 0;
+
+  double acc[H][KV];
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+#pragma unroll
+    for (int v = 0; v < KV; ++v) acc[h][v] = 0.0;
+    const int v0 = (blockIdx.y * H + h) * KB;  // right-hand sides of this turn
+    if (v0 >= k) continue;                     // uniform over the launch
+    const int kb = k - v0 < KB ? k - v0 : KB;
+    __syncthreads();
+    {  // stage the window, KB / 2 lanes per element
+      typedef double P2 __attribute__((ext_vector_type(2)));
+      const double *X = static_cast<const double *>(a.x) + v0;
+      const int pv = ((int)threadIdx.x % PP) * 2;
+      constexpr int E = 64 * GC / PP, K = 4;  // elements per round, rounds in flight
+      for (int b = threadIdx.x / PP; b < nwin; b += E * K) {
+        P2 t[K];
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+          const int i = b + q * E;
+          t[q] = P2{};
+          if (i < nwin) {
+            int lo = 0, hi = ns - 1;  // last segment with position <= i
+            while (lo < hi) {
+              const int mid = (lo + hi + 1) >> 1;
+              if (segt[mid].y <= i) lo = mid;
+              else hi = mid - 1;
+            }
+            const double *xr = X + (int64_t)(segt[lo].x + (i - segt[lo].y)) * k + pv;
+            if (pv + 1 < kb) {
+              const PairA8 p = *reinterpret_cast<const PairA8 *>(xr);
+              t[q][0] = p[0];
+              t[q][1] = p[1];
+            } else if (pv < kb) {
+              t[q][0] = xr[0];
+            }
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+          const int i = b + q * E;
+          if (i < nwin) *reinterpret_cast<P2 *>(xw + (size_t)i * KB + pv) = t[q];
+        }
+      }
+    }
+    __syncthreads();
+    auto add = [&](double v1, int c1) {
+#pragma unroll
+      for (int q = 0; q < G; ++q) {
+        const double v = from_lane<G>(v1, q, lane);
+        const int c = from_lane<G>(c1, q, lane);
+        if (v != 0.0) {
+          const double *xr = xw + (size_t)c * KB + g * KV;
+          double xg[KV];
+          __builtin_memcpy(xg, __builtin_assume_aligned(xr, KV * 8 < 16 ? KV * 8 : 16), sizeof(xg));
+#pragma unroll
+          for (int e = 0; e < KV; ++e) acc[h][e] = __builtin_fma(v, xg[e], acc[h][e]);
+        }
+      }
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u) add(vv[u][0], (int)ci[u][0]);
+    constexpr int U2 = 8 / G > 0 ? 8 / G : 1;  // the columns past 28, read once per turn
+    for (int s = U; s * G < cl; s += U2) {
+      uint16_t c2[U2][1];
+      double w2[U2][1];
+#pragma unroll
+      for (int u = 0; u < U2; ++u) {
+        ld_buf<1>(rc, lo0 + 64u * (uint32_t)(s + u), c2[u]);
+        ld_buf<1>(rv, lo0 + 64u * (uint32_t)(s + u), w2[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < U2; ++u) add(w2[u][0], (int)c2[u][0]);
+    }
+  }
+  const int64_t p = chunk * C + r;
+  if (!live || p >= a.nrows) return;
+  double *y = static_cast<double *>(a.y) + (a.perm ? (int64_t)a.perm[p] : p) * k;
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const int v0 = (blockIdx.y * H + h) * KB + g * KV;
+#pragma unroll
+    for (int v = 0; v + 2 <= KV; v += 2) {
+      if (v0 + v + 2 <= k) {
+        PairA8 o;
+        o[0] = acc[h][v];
+        o[1] = acc[h][v + 1];
+        __builtin_nontemporal_store(o, reinterpret_cast<PairA8 *>(y + v0 + v));
+      } else if (v0 + v < k) {
+        __builtin_nontemporal_store(acc[h][v], y + v0 + v);
+      }
+    }
+    if constexpr (KV % 2 != 0)
+      if (v0 + KV - 1 < k) __builtin_nontemporal_store(acc[h][KV - 1], y + v0 + KV - 1);
+  }
+}
+
 // Block form: add the segment sums of split row slices. Block (w, tile, z):
 // split slice w, pass tile, z-th part of the slice's (row, right-hand side)
 // elements; one thread per element where the grid covers them all, the
