@@ -378,12 +378,16 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
   h->cs = static_cast<int64_t *>(owned_alloc(h.get(), mem, sizeof(int64_t) * (size_t)(nc + 1)));
   const int64_t n_scan = sell::scan_tmp_elems(nc + 1);
   int64_t *scan_tmp =
-      static_cast<int64_t *>(tmp.get(sizeof(int64_t) * (size_t)(n_scan + 5 * sell::plan_blocks(nc))));
+      static_cast<int64_t *>(tmp.get(sizeof(int64_t) * (size_t)(n_scan + 5 * sell::plan_blocks(nc) + 2 * nc)));
   if (!h->cl || !h->cs || !scan_tmp) return fail(SELL_ERR_OOM, "sell_build: chunk arrays");
   const Geom &g = h->g;
   const DeviceInfo di = device_info();
+  // two per item, at most two items a chunk; kept in the scan's block
+  int32_t *few = layout_only || sell::thin_rows(g.rpw, g.T) == 0
+                     ? nullptr
+                     : reinterpret_cast<int32_t *>(scan_tmp + n_scan + 5 * sell::plan_blocks(nc));
   SELL_HIP(sell::build_chunkwidth(len, h->perm, n, C, nc, g.T, g.wpc, h->cl, h->cs, &dsmall->padded,
-                                  &dsmall->plan.total_steps, &dsmall->plan.max_width, s));
+                                  &dsmall->plan.total_steps, &dsmall->plan.max_width, few, s));
   sell::PlanArgs pa{};
   if (!layout_only) {
     pa.cl = h->cl;
@@ -395,6 +399,10 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
     pa.T = g.T;
     pa.cus = di.cus;
     pa.seg_cols = o.seg_cols > 0 ? sell::round_seg(o.seg_cols) : o.seg_cols;
+    pa.few = few;
+    pa.len = len;
+    pa.perm = h->perm;
+    pa.nrows = n;
     pa.blocks = scan_tmp + n_scan;
     pa.sizes = &dsmall->plan;
     SELL_HIP(sell::plan_count(pa, s));
@@ -460,7 +468,7 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
   h->seg_cols = S;
   h->nunits = h->nitems;
   if (z.nsplit > 0) {
-    h->seg1 = o.seg_cols > 0 ? S : sell::single_seg_cols(z.total_steps, g.T, di.cus, S);
+    const int32_t S1 = o.seg_cols > 0 ? S : sell::single_seg_cols(z.total_steps, g.T, di.cus, S);
     h->nunits = z.nsegs + h->nitems - z.nsplit;
     h->nsplit = z.nsplit;
     h->nsegs = z.nsegs;
@@ -471,18 +479,18 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
     const int64_t sums = std::max(z.nsegs * next_pow2(h->kmax), z.nsegs1) * g.rpw;
     h->units = static_cast<sell::Unit *>(owned_alloc(h.get(), mem, sizeof(sell::Unit) * (size_t)h->nunits));
     h->splits = static_cast<sell::SplitDesc *>(owned_alloc(h.get(), mem, sizeof(sell::SplitDesc) * (size_t)z.nsplit));
-    h->units1 = static_cast<sell::Unit *>(owned_alloc(h.get(), mem, sizeof(sell::Unit) * (size_t)h->nunits1));
+    h->units1 = static_cast<sell::Unit1 *>(owned_alloc(h.get(), mem, sizeof(sell::Unit1) * (size_t)h->nunits1));
     h->splits1 = static_cast<sell::SplitDesc *>(owned_alloc(h.get(), mem, sizeof(sell::SplitDesc) * (size_t)z.nsplit1));
     h->partial = owned_alloc(h.get(), mem, sizeof(double) * (size_t)sums);
-    sell::Unit *segs = nullptr;
+    sell::Unit1 *segs = nullptr;
     if (place)
-      segs = static_cast<sell::Unit *>(tmp.get((sizeof(sell::Unit) + sizeof(sell::UnitCol)) * (size_t)z.nsegs1));
+      segs = static_cast<sell::Unit1 *>(tmp.get((sizeof(sell::Unit1) + sizeof(sell::UnitCol)) * (size_t)z.nsegs1));
     if (!h->units || !h->splits || !h->units1 || !h->splits1 || !h->partial || (place && !segs))
       return fail(SELL_ERR_OOM, "sell_build: work plan");
     const sell::PlanOut po{h->units, h->splits, h->units1, h->splits1, segs};
-    SELL_HIP(sell::plan_emit(pa, S, h->seg1, z, po, s));
+    SELL_HIP(sell::plan_emit(pa, S, S1, z, po, s));
     if (place)
-      SELL_HIP(sell::plan_place(pa, C, h->seg1, z, po, h->cs, h->col, h->ncols,
+      SELL_HIP(sell::plan_place(pa, C, z, po, h->cs, h->col, h->ncols,
                                 reinterpret_cast<sell::UnitCol *>(segs + z.nsegs1), s));
   }
 
@@ -666,11 +674,10 @@ sell_status spmv_run(sell_handle h, const void *x, void *y, void *stream, void *
   if (partial) a.partial = partial;
   a.rl = h->rl;  // row_lengths: each row's lanes stop at its end
   if (h->units1) {
-    a.units = h->units1;
+    a.units1 = h->units1;
     a.nwork = h->nunits1;
     a.splits = h->splits1;
     a.nsplit = h->nsplit1;
-    a.seg_cols = h->seg1;
   }
   // padding-heavy layouts skip the gathers of their zero slots; near-dense
   // chunks skip the per-slot test

@@ -311,6 +311,9 @@ __global__ void __launch_bounds__(kBlock) k_sort_longest(const int32_t *__restri
   for (int64_t e = threadIdx.x; e < m; e += kBlock) perm[w0 + e] = tmp[w0 + e];
 }
 
+// Chunks up to this width are never split: their few[] is not looked at.
+constexpr int32_t kFewMin = 32;
+
 // cl[i] = max length of the chunk's rows in sorted order (Eq. (max));
 // csz[i] = C * cl[i] (scanned into cs afterwards); csz[nchunks] = 0. One lane
 // per row, so that the permuted lengths of a chunk are one access (one thread
@@ -322,7 +325,8 @@ __global__ void __launch_bounds__(kStrideBlock) k_chunkwidth(const int32_t *__re
                                                        int64_t *__restrict__ csz,
                                                        unsigned long long *__restrict__ padded,
                                                        unsigned long long *__restrict__ total_steps,
-                                                       int32_t *__restrict__ max_width) {
+                                                       int32_t *__restrict__ max_width,
+                                                       int32_t *__restrict__ few) {
   __shared__ unsigned long long s_cols[kStrideBlock / 64];
   __shared__ unsigned long long s_steps[kStrideBlock / 64];
   __shared__ int32_t s_mx[kStrideBlock / 64];
@@ -331,10 +335,35 @@ __global__ void __launch_bounds__(kStrideBlock) k_chunkwidth(const int32_t *__re
   const int64_t rows = nchunks * C, stride = (int64_t)gridDim.x * (kStrideBlock / 64) * span;
   unsigned long long steps = 0, cols = 0;
   int32_t mx = 0;
+  const int nfew = thin_rows(width, T);
   for (int64_t p0 = ((int64_t)blockIdx.x * (kStrideBlock / 64) + (threadIdx.x >> 6)) * span; p0 < rows; p0 += stride) {
     int32_t l = 0;
-    for (int64_t p = p0 + lane; p < p0 + span && p < n; p += 64) {
-      const int32_t v = len[perm ? (int64_t)perm[p] : p];
+    for (int64_t p = p0 + lane; p < p0 + span; p += 64) {
+      const int32_t v = p < n ? len[perm ? (int64_t)perm[p] : p] : 0;
+      if (few && nfew > 0) {
+        // the longest row of each item taken out nfew times, then the longest
+        // left; kFewMin where all of the wave's rows are that short (half of a
+        // wide chunk at C = 128 may be)
+        int32_t f = kFewMin, f2 = kFewMin;
+        if (__ballot(v > kFewMin) != 0ull) {
+          int64_t key = (int64_t)v << 6 | lane;
+          for (int t = 0;; ++t) {
+            int64_t m = key;
+            for (int off = width / 2; off > 0; off >>= 1) {
+              const int64_t o = __shfl_xor(m, off);
+              m = o > m ? o : m;
+            }
+            f = (int32_t)(m >> 6);
+            if (t == kThinnestRows) f2 = f;
+            if (t == nfew) break;
+            if (m == key) key = -64;
+          }
+        }
+        if (lane % width == 0 && p < rows) {
+          few[2 * (p / width)] = f;
+          few[2 * (p / width) + 1] = f2;
+        }
+      }
       l = v > l ? v : l;
     }
     for (int off = width / 2; off > 0; off >>= 1) {
@@ -745,13 +774,13 @@ hipError_t build_sort(const int32_t *len, int64_t n, int64_t sigma, int64_t *tmp
 
 hipError_t build_chunkwidth(const int32_t *len, const int32_t *perm, int64_t n, int C, int64_t nchunks, int T, int wpc,
                             int32_t *cl, int64_t *csz, int64_t *padded, int64_t *total_steps, int32_t *max_width,
-                            hipStream_t s) {
+                            int32_t *few, hipStream_t s) {
   const int64_t per = (int64_t)(kStrideBlock / 64) * (C < 64 ? 64 : C);
   int64_t nb = (nchunks * C + per - 1) / per;
   nb = nb < 1 ? 1 : nb > kStrideGrid ? kStrideGrid : nb;
   hipLaunchKernelGGL(k_chunkwidth, dim3((unsigned)nb), dim3(kStrideBlock), 0, s, len, perm, n, C, nchunks, T, wpc, cl, csz,
                      reinterpret_cast<unsigned long long *>(padded),
-                     reinterpret_cast<unsigned long long *>(total_steps), max_width);
+                     reinterpret_cast<unsigned long long *>(total_steps), max_width, few);
   return hipGetLastError();
 }
 

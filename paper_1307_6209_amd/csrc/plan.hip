@@ -42,6 +42,10 @@ __device__ __forceinline__ Cell cell_of(const PlanArgs &a, int64_t cell) {
   return r;
 }
 
+__device__ __forceinline__ Split1 split_item(const PlanArgs &a, int64_t it, int32_t w, int32_t S1) {
+  return split1_of(a.few ? a.few + 2 * it : nullptr, w, S1, a.seg_cols > 0);
+}
+
 __device__ __forceinline__ Counts count_cell(const PlanArgs &a, const Cell &e, int32_t S, int32_t S1) {
   Counts n{};
   for (int64_t c = e.c0; c < e.c1; ++c) {
@@ -52,7 +56,7 @@ __device__ __forceinline__ Counts count_cell(const PlanArgs &a, const Cell &e, i
     }
     if (w > S1) {
       n.split1 += a.wpc;
-      n.seg1 += (w + S1 - 1) / S1 * a.wpc;
+      for (int h = 0; h < a.wpc; ++h) n.seg1 += split_item(a, c * a.wpc + h, w, S1).all;
     } else if (!e.group) {
       n.whole1 += a.wpc;
     }
@@ -159,7 +163,7 @@ __global__ void __launch_bounds__(kPlanBlock) k_plan_emit(PlanArgs a, int32_t S,
   const int64_t *b = a.blocks + 5 * (int64_t)blockIdx.x;
   int64_t split0 = b[0] + at.split0, seg0 = b[1] + at.seg0, split1 = b[2] + at.split1, seg1 = b[3] + at.seg1;
   int64_t whole1 = b[4] + at.whole1;
-  if (e.group) o.units1[nsegs1 + whole1++] = {(int32_t)(e.c0 * a.wpc), 0, 0, 0};
+  if (e.group) o.units1[nsegs1 + whole1++] = {(int32_t)(e.c0 * a.wpc), 0, 0, 0, -1, 0, 0};
   for (int64_t c = e.c0; c < e.c1; ++c) {
     const int32_t w = a.cl[c];
     for (int h = 0; h < a.wpc; ++h) {
@@ -172,11 +176,11 @@ __global__ void __launch_bounds__(kPlanBlock) k_plan_emit(PlanArgs a, int32_t S,
         o.units[nsegs + item - split0] = {item, 0, 1, 0};
       }
       if (w > S1) {
-        const int32_t ns = (w + S1 - 1) / S1;
+        const int32_t ns = split_item(a, item, w, S1).all;
         o.splits1[split1++] = {item, ns, seg1 * a.rpw};
         seg1 += ns;
       } else if (!e.group) {
-        o.units1[nsegs1 + whole1++] = {item, 0, 1, 0};
+        o.units1[nsegs1 + whole1++] = {item, 1, 0, w, -1, 0, 0};
       }
     }
   }
@@ -198,22 +202,56 @@ __global__ void __launch_bounds__(kPlanBlock) k_plan_segs(const SplitDesc *__res
   out[i] = {d.item, (int32_t)(i - d.poff / rpw), d.nseg, (int32_t)lo};
 }
 
+// The same for the single plan, one wave per segment, with the rows of the thin
+// ones.
+__global__ void __launch_bounds__(kPlanBlock) k_plan_segs1(PlanArgs a, const SplitDesc *__restrict__ splits,
+                                                           int64_t nsplit, int64_t nsegs, int32_t S1,
+                                                           Unit1 *__restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * (kPlanBlock / 64) +
+                    __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (i >= nsegs) return;
+  int64_t lo = 0, hi = nsplit;
+  while (hi - lo > 1) {
+    const int64_t mid = (lo + hi) >> 1;
+    if (splits[mid].poff <= i * a.rpw) lo = mid;
+    else hi = mid;
+  }
+  const SplitDesc d = splits[lo];
+  const int32_t q = (int32_t)(i - d.poff / a.rpw), w = a.cl[d.item / a.wpc];
+  const Split1 sp = split_item(a, d.item, w, S1);
+  Unit1 u{d.item, d.nseg, 0, 0, (int32_t)(i * a.rpw), 0, 0};
+  if (q < sp.dense) {
+    u.jb = q * S1;
+    u.je = u.jb + S1 < sp.thin ? u.jb + S1 : sp.thin;
+  } else {
+    if (q < sp.segs) {
+      u.jb = sp.thin + (q - sp.dense) * sp.tc;
+      u.je = u.jb + sp.tc < sp.thinnest ? u.jb + sp.tc : sp.thinnest;
+    } else {
+      u.jb = sp.thinnest + (q - sp.segs) * sp.uc;
+      u.je = u.jb + sp.uc < w ? u.jb + sp.uc : w;
+    }
+    const int r = threadIdx.x & 63;
+    const int64_t p = (int64_t)d.item * a.rpw + r;
+    u.rows = __ballot(r < a.rpw && p < a.nrows && a.len[a.perm ? (int64_t)a.perm[p] : p] > u.jb);
+  }
+  if ((threadIdx.x & 63) == 0) out[i] = u;
+}
+
 // One wave per split segment: the mean column of its rows at the middle of
 // the segment (rows that have ended hold column 0 there and don't count), and
 // how many those are.
-__global__ void __launch_bounds__(kPlanBlock) k_unit_cols(const Unit *__restrict__ units, int64_t n, int rpw, int wpc,
-                                                          int C, int32_t seg_cols, const int64_t *__restrict__ cs,
-                                                          const int32_t *__restrict__ cl,
+__global__ void __launch_bounds__(kPlanBlock) k_unit_cols(const Unit1 *__restrict__ units, int64_t n, int rpw, int wpc,
+                                                          int C, const int64_t *__restrict__ cs,
                                                           const int32_t *__restrict__ col, UnitCol *__restrict__ out) {
   const int64_t w = (int64_t)blockIdx.x * (kPlanBlock / 64) + (threadIdx.x >> 6);
   if (w >= n) return;
-  const Unit u = units[w];
+  const Unit1 u = units[w];
   const int64_t chunk = u.item / wpc;
-  const int64_t jb = (int64_t)u.seg * seg_cols;
-  const int64_t je = jb + seg_cols < cl[chunk] ? jb + seg_cols : cl[chunk];
   const int r = threadIdx.x & 63;
   unsigned long long sum = 0;
-  if (r < rpw) sum = (unsigned long long)col[cs[chunk] + (jb + je) / 2 * C + (u.item - chunk * wpc) * rpw + r];
+  if (r < rpw)
+    sum = (unsigned long long)col[cs[chunk] + ((int64_t)u.jb + u.je) / 2 * C + (u.item - chunk * wpc) * rpw + r];
   const int cnt = __popcll(__ballot(sum > 0));
   for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
   if (r == 0) out[w] = {cnt ? (int32_t)(sum / (unsigned)cnt) : 0, cnt};
@@ -228,25 +266,28 @@ __global__ void __launch_bounds__(kPlanBlock) k_unit_cols(const Unit *__restrict
 constexpr int kOrderBlock = 1024;
 constexpr int kOrderBins = 4096;
 
-__global__ void __launch_bounds__(kOrderBlock) k_order_segs(const Unit *__restrict__ segs,
+__global__ void __launch_bounds__(kOrderBlock) k_order_segs(const Unit1 *__restrict__ segs,
                                                             const UnitCol *__restrict__ at, int64_t n, int rpw,
-                                                            int64_t ncols, Unit *__restrict__ out) {
+                                                            int64_t ncols, Unit1 *__restrict__ out) {
   __shared__ int32_t bin[kOrderBins];
   __shared__ int32_t ws[kOrderBlock / 64];
-  __shared__ unsigned long long live;
+  __shared__ unsigned long long live, cols;  // entries (by the middle columns) and columns of all segments
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   for (int b = tid; b < kOrderBins; b += kOrderBlock) bin[b] = 0;
-  if (tid == 0) live = 0;
+  if (tid == 0) live = cols = 0;
   __syncthreads();
-  unsigned long long mine = 0;
+  unsigned long long mine = 0, width = 0;
   for (int64_t i = tid; i < n; i += kOrderBlock) {
     const UnitCol u = at[i];
-    mine += (unsigned)u.live;
+    const unsigned w = (unsigned)(segs[i].je - segs[i].jb);
+    mine += (unsigned long long)u.live * w;
+    width += w;
     atomicAdd(&bin[(int64_t)u.col * kOrderBins / ncols], 1);
   }
   if (mine) atomicAdd(&live, mine);
+  if (width) atomicAdd(&cols, width);
   __syncthreads();
-  if ((double)live < kXcdMinLive * (double)rpw * (double)n) {  // uniform
+  if ((double)live < kXcdMinLive * (double)rpw * (double)cols) {  // uniform
     for (int64_t i = tid; i < n; i += kOrderBlock) out[i] = segs[i];
     return;
   }
@@ -302,15 +343,15 @@ hipError_t plan_emit(const PlanArgs &a, int32_t S, int32_t S1, const PlanSizes &
   hipLaunchKernelGGL(k_plan_segs, grid(z.nsegs), dim3(kPlanBlock), 0, s, o.splits, z.nsplit, z.nsegs, a.rpw, o.units);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // o.segs: the single plan's segments are placed by column from there
-  hipLaunchKernelGGL(k_plan_segs, grid(z.nsegs1), dim3(kPlanBlock), 0, s, o.splits1, z.nsplit1, z.nsegs1, a.rpw,
-                     o.segs ? o.segs : o.units1);
+  hipLaunchKernelGGL(k_plan_segs1, dim3((unsigned)((z.nsegs1 + kPlanBlock / 64 - 1) / (kPlanBlock / 64))),
+                     dim3(kPlanBlock), 0, s, a, o.splits1, z.nsplit1, z.nsegs1, S1, o.segs ? o.segs : o.units1);
   return hipGetLastError();
 }
 
-hipError_t plan_place(const PlanArgs &a, int C, int32_t S1, const PlanSizes &z, const PlanOut &o, const int64_t *cs,
+hipError_t plan_place(const PlanArgs &a, int C, const PlanSizes &z, const PlanOut &o, const int64_t *cs,
                       const int32_t *col, int64_t ncols, UnitCol *at, hipStream_t s) {
   hipLaunchKernelGGL(k_unit_cols, dim3((unsigned)((z.nsegs1 + kPlanBlock / 64 - 1) / (kPlanBlock / 64))),
-                     dim3(kPlanBlock), 0, s, o.segs, z.nsegs1, a.rpw, a.wpc, C, S1, cs, a.cl, col, at);
+                     dim3(kPlanBlock), 0, s, o.segs, z.nsegs1, a.rpw, a.wpc, C, cs, col, at);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_order_segs, dim3(1), dim3(kOrderBlock), 0, s, o.segs, at, z.nsegs1, a.rpw, ncols, o.units1);

@@ -35,6 +35,20 @@ struct SplitDesc {
   int64_t poff;
 };
 
+// One work unit of the single-vector product on a layout with split chunks:
+// columns [jb, je) of an item. nseg 0: a group of short chunks from item on;
+// part < 0: the whole item, y is written; else a segment, whose row sums go to
+// partial[part ...]. rows: the rows that a thin segment holds, at most eight
+// (bit r: row r of the item); 0: all.
+struct Unit1 {
+  int32_t item;
+  int32_t nseg;
+  int32_t jb, je;
+  int32_t part;
+  int32_t pad;
+  uint64_t rows;
+};
+
 // Of a split segment, at its middle column: the mean column of the rows that
 // hold an entry there, and their number.
 struct UnitCol {
@@ -133,6 +147,48 @@ __host__ __device__ inline int32_t single_seg_cols(int64_t total_steps, int T, i
   return cols < S ? (int32_t)cols : S;
 }
 
+// Thin segments: where at most thin_rows rows of a slice still hold entries the single-vector product takes those rows alone, 64 / rows columns a
+// step and no fewer than the T of the others, whose lanes would step over padding
+// for 24 of 32 rows and more. kThinCols columns a unit with up to eight rows,
+// kThinnestCols with up to two: at most eight steps, one round of loads. us
+// without / with thin segments, C = 16, 32, 64: power-law 1M, sigma = 1024 71, 98,
+// 155 / 70, 80, 89; the same in FP32 53, 69, 105 / 51, 65, 73 (at C = 32 a row's
+// entries lie one to a line of val and of col: the bytes stay); 2M, sigma = 2^14
+// 125, 138, 171 / 124, 130, 140; 50k, sigma = 1024 10.6, 12.6, 19.4 / 10.7, 10.9,
+// 12.2; 200k, sigma = n 11.9, 13.5, 18.5 / 12.5, 12.7, 16.1. 256 columns with up
+// to two rows: 200k 13.9, 14.2, 16.4; 256 with up to eight: 18, 18, 19.
+constexpr int32_t kThinCols = 64;
+constexpr int32_t kThinnestCols = 128;
+constexpr int kThinnestRows = 2;
+__host__ __device__ inline int thin_rows(int rpw, int T) {
+  const int few = rpw < 16 ? 0 : rpw < 32 ? 4 : 8;  // a quarter of the rows at most
+  return 64 / T < few ? 64 / T : few;
+}
+
+// Segments of a slice w columns wide in the single plan: dense ones of S1
+// columns up to column thin, thin ones of tc columns up to column thinnest, then
+// thin ones of uc columns. few: the columns in which more than thin_rows, and
+// more than kThinnestRows, rows hold entries (nullptr: no thin segments).
+struct Split1 {
+  int32_t thin, thinnest, tc, uc;
+  int32_t dense, segs;  // dense segments, dense and thin ones
+  int32_t all;
+};
+__host__ __device__ inline Split1 split1_of(const int32_t *few, int32_t w, int32_t S1, bool fixed) {
+  Split1 r;
+  const int64_t t = few ? ((int64_t)few[0] + S1 - 1) / S1 * S1 : w;
+  r.thin = t < w ? (int32_t)t : w;
+  r.tc = fixed || S1 > kThinCols ? S1 : kThinCols;
+  r.uc = fixed || S1 > kThinnestCols ? S1 : kThinnestCols;
+  const int64_t f2 = few && few[1] > r.thin ? few[1] - r.thin : 0;
+  const int64_t t2 = r.thin + (f2 + r.tc - 1) / r.tc * r.tc;
+  r.thinnest = t2 < w ? (int32_t)t2 : w;
+  r.dense = (int32_t)(((int64_t)r.thin + S1 - 1) / S1);
+  r.segs = r.dense + (int32_t)(((int64_t)r.thinnest - r.thin + r.tc - 1) / r.tc);
+  r.all = r.segs + (int32_t)(((int64_t)w - r.thinnest + r.uc - 1) / r.uc);
+  return r;
+}
+
 // Arguments of the spMVM kernels (by value).
 struct SpmvArgs {
   const void *val;
@@ -149,6 +205,7 @@ struct SpmvArgs {
   int64_t nsplit;
   void *partial;
   int32_t seg_cols;     // chunk columns per segment (multiple of kSegAlign)
+  const Unit1 *units1;  // single-vector product: its units, or nullptr (wave w handles item w)
   const int32_t *rl;    // single-vector product: length of every row in sorted
                         // order (N_c * C entries), or nullptr
   // block form only
@@ -259,10 +316,12 @@ hipError_t build_colcheck(const int32_t *col, int64_t nnz, int64_t ncols, uint32
 int64_t sort_tmp_elems(int64_t n, int64_t sigma);
 hipError_t build_sort(const int32_t *len, int64_t n, int64_t sigma, int64_t *tmp, int32_t *perm, hipStream_t s);
 // padded, total_steps: += the slots, the wave steps of T columns over all items
-// (wpc per chunk); max_width: the widest chunk (all zeroed by the caller)
+// (wpc per chunk); max_width: the widest chunk (all zeroed by the caller). few
+// (or nullptr): per item, the lengths of its (thin_rows + 1)-th and its
+// (kThinnestRows + 1)-th longest row.
 hipError_t build_chunkwidth(const int32_t *len, const int32_t *perm, int64_t n, int C, int64_t nchunks, int T, int wpc,
                             int32_t *cl, int64_t *csz, int64_t *padded, int64_t *total_steps, int32_t *max_width,
-                            hipStream_t s);
+                            int32_t *few, hipStream_t s);
 // Exclusive scan of n int64 values (in-place allowed); tmp needs scan_tmp_elems(n) int64.
 int64_t scan_tmp_elems(int64_t n);
 hipError_t build_scan(const int64_t *in, int64_t *out, int64_t n, int64_t *tmp, hipStream_t s);
@@ -285,20 +344,23 @@ struct PlanArgs {
   int grp;                  // 64 / C for C in 8..32, else 1
   int wpc, rpw, T, cus;
   int32_t seg_cols;         // > 0: given (rounded), 0: automatic, < 0: never split
+  const int32_t *few;       // two per item (split1_of), or nullptr
+  const int32_t *len, *perm;  // row lengths and order (perm nullptr: identity)
+  int64_t nrows;
   int64_t *blocks;          // 5 * plan_blocks(ncells)
   PlanSizes *sizes;         // total_steps and max_width set, the rest written
 };
 struct PlanOut {
   Unit *units;        // block form: nsegs segments, then the whole items
   SplitDesc *splits;
-  Unit *units1;       // single-vector product
+  Unit1 *units1;      // single-vector product
   SplitDesc *splits1;
-  Unit *segs;         // nullptr, or nsegs1 segments for plan_place to put into units1
+  Unit1 *segs;        // nullptr, or nsegs1 segments for plan_place to put into units1
 };
 int64_t plan_blocks(int64_t ncells);
 hipError_t plan_count(const PlanArgs &a, hipStream_t s);
 hipError_t plan_emit(const PlanArgs &a, int32_t S, int32_t S1, const PlanSizes &z, const PlanOut &o, hipStream_t s);
-hipError_t plan_place(const PlanArgs &a, int C, int32_t S1, const PlanSizes &z, const PlanOut &o, const int64_t *cs,
+hipError_t plan_place(const PlanArgs &a, int C, const PlanSizes &z, const PlanOut &o, const int64_t *cs,
                       const int32_t *col, int64_t ncols, UnitCol *at, hipStream_t s);
 // rl[p] = length of the row in sorted position p (0 for p >= n), p < np
 hipError_t build_sorted_len(const int32_t *len, const int32_t *perm, int64_t n, int64_t np, int32_t *rl,
@@ -375,11 +437,10 @@ struct sell_matrix {
   int64_t nunits = 0;
   sell::Unit *units = nullptr;  // nullptr when no chunk is split
   // the single-vector product's plan on split layouts (plan_single)
-  sell::Unit *units1 = nullptr;
+  sell::Unit1 *units1 = nullptr;
   int64_t nunits1 = 0;
   sell::SplitDesc *splits1 = nullptr;
   int64_t nsplit1 = 0, nsegs1 = 0;
-  int32_t seg1 = 0;
   int64_t nsplit = 0;
   int64_t nsegs = 0;                  // total segments of split items
   sell::SplitDesc *splits = nullptr;  // per split id

@@ -141,8 +141,9 @@ __device__ __forceinline__ void opaque(T &v) {
 }
 
 
-// One work unit: rows [h*rpw, (h+1)*rpw) of chunk `chunk`, chunk columns
-// [seg*seg_cols, ...) of it (all of them when nseg == 1).
+// One work unit: columns [jb, je) of the rows [h*rpw, (h+1)*rpw) of a chunk
+// (item: the chunk and h), jb a multiple of T. part < 0: all columns, y is
+// written; else a segment, whose row sums go to partial[part ...].
 //
 // Lane l holds the VV consecutive slots VV*l .. VV*l+VV-1 of every wave step
 // (64*VV consecutive slots = T chunk columns of RPW rows): rows
@@ -157,11 +158,11 @@ __device__ __forceinline__ void opaque(T &v) {
 // zero by zero -- and the result are those of the plain product.
 template <int COMBO, int C, int U, int VV, int ZS>
 __device__ __forceinline__ void spmv_unit(const void *__restrict__ valv, const int32_t *__restrict__ col,
-                                          const int64_t *__restrict__ cs, const int32_t *__restrict__ clp,
-                                          const int32_t *__restrict__ perm, const void *__restrict__ xv,
-                                          void *__restrict__ yv, int64_t nrows, int32_t item, int32_t seg,
-                                          int32_t nseg, int64_t poff, void *__restrict__ partial,
-                                          int32_t seg_cols, int lane, const int32_t *__restrict__ rlp = nullptr) {
+                                          const int64_t *__restrict__ cs, const int32_t *__restrict__ perm,
+                                          const void *__restrict__ xv, void *__restrict__ yv, int64_t nrows,
+                                          int32_t item, int32_t jb, int32_t je, int64_t part,
+                                          void *__restrict__ partial, int lane,
+                                          const int32_t *__restrict__ rlp = nullptr) {
   constexpr bool RL = ZS == 2;
   using V = typename Types<COMBO>::V;
   using X = typename Types<COMBO>::X;
@@ -178,12 +179,6 @@ __device__ __forceinline__ void spmv_unit(const void *__restrict__ valv, const i
   const int h = item - (int)(chunk * WPC);
   const int rl0 = (VV * lane) % RPW, t = (VV * lane) / RPW;
   const int64_t base = cs[chunk];
-  const int cl = clp[chunk];
-  int jb = 0, je = cl;
-  if (nseg > 1) {
-    jb = seg * seg_cols;
-    je = jb + seg_cols < cl ? jb + seg_cols : cl;
-  }
   const int sb = jb / T, se = (je + T - 1) / T;
   const int full = je / T;  // steps below this one hold a real column in every lane
   const int64_t off0 = base + (int64_t)t * C + h * RPW + rl0;
@@ -285,7 +280,7 @@ __device__ __forceinline__ void spmv_unit(const void *__restrict__ valv, const i
   A *y = static_cast<A *>(yv);
   const int64_t p0 = chunk * C + h * RPW + rl0;
   if (t != 0) return;
-  if (nseg == 1) {
+  if (part < 0) {
     if constexpr (VV > 1) {
       if (!perm && p0 + VV <= nrows &&
           (reinterpret_cast<uintptr_t>(y + p0) & (VV * sizeof(A) - 1)) == 0) {  // VV consecutive rows: one store
@@ -305,9 +300,61 @@ __device__ __forceinline__ void spmv_unit(const void *__restrict__ valv, const i
     return;
   }
   // segment of a split row slice: leave the sums for the combining kernel
-  A *part = static_cast<A *>(partial) + poff + (int64_t)seg * RPW + rl0;
+  A *mine = static_cast<A *>(partial) + part + rl0;
 #pragma unroll
-  for (int v = 0; v < VV; ++v) part[v] = acc[v];
+  for (int v = 0; v < VV; ++v) mine[v] = acc[v];
+}
+
+// A thin segment: columns [jb, je) of a slice of which only `rows` (one to eight
+// bits) still hold entries. L = 1, 2, 4 or 8 lanes side by side take a column's
+// rows, 64 / L columns a step, so a step of one row covers 64 columns where
+// spmv_unit covers T; the other rows' sums are 0. Bound by the lines of val and
+// col that the rows lie in (one of each per column, whatever the row). Slots
+// holding 0 skip the gather.
+template <int COMBO, int C>
+__device__ __forceinline__ void spmv_thin(const void *__restrict__ valv, const int32_t *__restrict__ col,
+                                          const int64_t *__restrict__ cs, const void *__restrict__ xv, int32_t item,
+                                          int32_t jb, int32_t je, uint64_t rows, int64_t part,
+                                          void *__restrict__ partial, int lane) {
+  using V = typename Types<COMBO>::V;
+  using X = typename Types<COMBO>::X;
+  using A = typename Types<COMBO>::A;
+  using R = typename std::conditional<sizeof(V) < 4, uint32_t, V>::type;
+  constexpr int RPW = C < 64 ? C : 64;
+  constexpr int WPC = C > 64 ? C / 64 : 1;
+  constexpr int U = 8;
+  const int n = __popcll(rows);
+  const int lg = n > 4 ? 3 : n > 2 ? 2 : n > 1 ? 1 : 0;
+  const int q = lane & ((1 << lg) - 1), step = 64 >> lg;
+  uint64_t m = rows;
+  for (int e = 0; e < q; ++e) m &= m - 1;  // the q-th row
+  const int r = q < n ? __ffsll((unsigned long long)m) - 1 : -1;
+  const int64_t chunk = item / WPC;
+  const int64_t off = cs[chunk] + (item - chunk * WPC) * RPW;
+  const X *x = static_cast<const X *>(xv);
+  A acc = 0;
+  for (int32_t j0 = jb + (lane >> lg); j0 - (lane >> lg) < je; j0 += U * step) {
+    int32_t ci[U];
+    R raw[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int32_t j = j0 + u * step;
+      const bool ok = r >= 0 && j < je;
+      const int64_t o = ok ? off + (int64_t)j * C + r : 0;
+      ci[u] = __builtin_nontemporal_load(col + o);
+      raw[u] = (R)__builtin_nontemporal_load(static_cast<const V *>(valv) + o);
+      if (!ok) raw[u] = 0;
+    }
+    X xg[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) xg[u] = raw[u] != 0 ? x[ci[u]] : (X)0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc = fmac(cvt(raw[u]), xg[u], acc);
+  }
+  for (int o = 32; o >= 1 << lg; o >>= 1) acc += __shfl_xor(acc, o);
+  // row `lane` of the slice: the sum that its place among the set bits holds
+  const A sum = __shfl(acc, __popcll(rows & ((1ull << lane) - 1ull)) & 63);
+  if (lane < RPW) static_cast<A *>(partial)[part + lane] = rows >> lane & 1ull ? sum : (A)0;
 }
 
 // Raw buffer loads over the slots of one chunk. The descriptor (uniform over
@@ -623,25 +670,26 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) k_spmv(SpmvArgs a) {
   const int lane = threadIdx.x & 63;
   const int64_t w = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   if (w >= a.nwork) return;
-  int32_t item, seg = 0, nseg = 1;
-  int64_t poff = 0;
-  if (a.units) {
-    const Unit u = a.units[w];
-    item = u.item;
-    seg = u.seg;
-    nseg = u.nseg;
-    if (nseg > 1) poff = a.splits[u.sid].poff;
+  Unit1 u{(int32_t)w, 1, 0, 0, -1, 0, 0};
+  if (a.units1) {
+    u = a.units1[w];
     if constexpr (C >= 8 && C <= 32) {
-      if (nseg == 0) {  // a group of short chunks
-        spmv_group<COMBO, C, ZS == 2>(a.val, a.col, a.cs, a.cl, a.perm, a.x, a.y, a.nrows, item, lane, a.rl);
+      if (u.nseg == 0) {  // a group of short chunks
+        spmv_group<COMBO, C, ZS == 2>(a.val, a.col, a.cs, a.cl, a.perm, a.x, a.y, a.nrows, u.item, lane, a.rl);
+        return;
+      }
+    }
+    if constexpr (C >= 16) {
+      if (u.rows != 0) {
+        spmv_thin<COMBO, C>(a.val, a.col, a.cs, a.x, u.item, u.jb, u.je, u.rows, u.part, a.partial, lane);
         return;
       }
     }
   } else {
-    item = (int32_t)w;
+    u.je = a.cl[C > 64 ? w / (C / 64) : w];
   }
-  spmv_unit<COMBO, C, U, VV, ZS>(a.val, a.col, a.cs, a.cl, a.perm, a.x, a.y, a.nrows, item, seg, nseg, poff,
-                                 a.partial, a.seg_cols, lane, a.rl);
+  spmv_unit<COMBO, C, U, VV, ZS>(a.val, a.col, a.cs, a.perm, a.x, a.y, a.nrows, u.item, u.jb, u.je, u.part, a.partial,
+                                 lane, a.rl);
 }
 
 // Batched form: one launch over the concatenated work units of all
@@ -675,9 +723,16 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) k_batch(BatchArgs a) {
         continue;
       }
     }
-    const int64_t poff = u.nseg > 1 ? a.splits[u.sid].poff : 0;
-    spmv_unit<COMBO, C, U, 1, true>(m.val, m.col, m.cs, m.cl, m.perm, m.x, m.y, m.nrows, u.item, u.seg, u.nseg,
-                                    poff, a.partial, a.seg_cols, lane);
+    constexpr int WPC = C > 64 ? C / 64 : 1, RPW = C < 64 ? C : 64;
+    int32_t jb = 0, je = m.cl[u.item / WPC];
+    int64_t part = -1;
+    if (u.nseg > 1) {
+      jb = u.seg * a.seg_cols;
+      je = jb + a.seg_cols < je ? jb + a.seg_cols : je;
+      part = a.splits[u.sid].poff + (int64_t)u.seg * RPW;
+    }
+    spmv_unit<COMBO, C, U, 1, true>(m.val, m.col, m.cs, m.perm, m.x, m.y, m.nrows, u.item, jb, je, part, a.partial,
+                                    lane);
   }
 }
 

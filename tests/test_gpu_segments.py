@@ -46,3 +46,33 @@ def test_segments_placed_by_column(C):
     check_fp64(A, spmv_gpu(h, x), x, m=chain_per_row(A, h, C))
     h = build(A, C, A.nrows, val_dtype="bf16", acc_dtype="f64")
     check_reduced(A, h, x, "bf16", "f64", C)
+
+
+@pytest.mark.parametrize("C", [16, 32, 64, 128])
+@pytest.mark.parametrize("m", [1, 2, 3, 4, 5, 8, 9])
+def test_thin_segments(C, m):
+    """Slices of which m rows, anywhere in them, are long: the columns past the
+    other rows' ends are taken by the long rows alone where those are few. Widths
+    around the cuts of 32, 64 and 128 columns; at C = 128 one half of a chunk
+    without long rows."""
+    tails = [33, 64, 65, 96, 97, 128, 129, 161, 400, 3000, 9001]
+    lens = []
+    for c, w in enumerate(tails):
+        part = np.full(C, 1 + c % 3)
+        at = (synth.u64(C + c, 61, C) % np.uint64(min(C, 64))).astype(np.int64)
+        for q, r in enumerate(dict.fromkeys(at.tolist())):
+            if q < m:
+                part[r] = max(2, w - 37 * q)
+        lens += part.tolist()
+    A = lengths_crs(lens, 20_000, 95)
+    x = synth.uniform(A.ncols, 96)
+    for sigma in (1, A.nrows):
+        h = build(A, C, sigma)
+        assert h.info["nsplit"] > 0
+        say("thin C", C, "rows", m, "sigma", sigma)
+        check_fp64(A, spmv_gpu(h, x), x, m=chain_per_row(A, h, C))
+        if C <= 64:
+            r = build(A, C, sigma, row_lengths=True)
+            assert np.array_equal(spmv_gpu(r, x), spmv_gpu(h, x))
+    h = build(A, C, 1, seg_cols=64, val_dtype="f32", acc_dtype="f32")
+    check_reduced(A, h, x, "f32", "f32", C)
