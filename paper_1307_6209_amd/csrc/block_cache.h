@@ -30,7 +30,7 @@ class BlockCache {
   using Free = void (*)(void *);
   BlockCache(Alloc a, Free f) : alloc_(a), free_(f) {}
 
-  static constexpr uint64_t kKeep = 8;
+  static constexpr uint64_t kKeep = 256;  // a batch of matrices may turn over between two uses
 
   // Sizes within a sixteenth of each other share a size, so that matrices of
   // about the same size reuse each other's blocks.
