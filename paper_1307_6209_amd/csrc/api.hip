@@ -351,6 +351,7 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
     unsigned long long sumsq;
     int64_t padded;
     sell::PlanSizes plan;
+    uint32_t next_thin;
   };
   Small *dsmall = static_cast<Small *>(tmp.get(sizeof(Small)));
   int32_t *len = static_cast<int32_t *>(tmp.get(sizeof(int32_t) * (size_t)std::max<int64_t>(n, 1)));
@@ -376,16 +377,16 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
   // chunk widths and offsets
   h->cl = static_cast<int32_t *>(owned_alloc(h.get(), mem, sizeof(int32_t) * (size_t)std::max<int64_t>(nc, 1)));
   h->cs = static_cast<int64_t *>(owned_alloc(h.get(), mem, sizeof(int64_t) * (size_t)(nc + 1)));
-  const int64_t n_scan = sell::scan_tmp_elems(nc + 1);
+  const int64_t n_scan = sell::scan_tmp_elems(nc + 1), n_plan = sell::kPlanCounts * sell::plan_blocks(nc);
   int64_t *scan_tmp =
-      static_cast<int64_t *>(tmp.get(sizeof(int64_t) * (size_t)(n_scan + 5 * sell::plan_blocks(nc) + 2 * nc)));
+      static_cast<int64_t *>(tmp.get(sizeof(int64_t) * (size_t)(n_scan + n_plan + 2 * nc)));
   if (!h->cl || !h->cs || !scan_tmp) return fail(SELL_ERR_OOM, "sell_build: chunk arrays");
   const Geom &g = h->g;
   const DeviceInfo di = device_info();
   // two per item, at most two items a chunk; kept in the scan's block
   int32_t *few = layout_only || sell::thin_rows(g.rpw, g.T) == 0
                      ? nullptr
-                     : reinterpret_cast<int32_t *>(scan_tmp + n_scan + 5 * sell::plan_blocks(nc));
+                     : reinterpret_cast<int32_t *>(scan_tmp + n_scan + n_plan);
   SELL_HIP(sell::build_chunkwidth(len, h->perm, n, C, nc, g.T, g.wpc, h->cl, h->cs, &dsmall->padded,
                                   &dsmall->plan.total_steps, &dsmall->plan.max_width, few, s));
   sell::PlanArgs pa{};
@@ -405,6 +406,7 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
     pa.nrows = n;
     pa.blocks = scan_tmp + n_scan;
     pa.sizes = &dsmall->plan;
+    pa.next_thin = &dsmall->next_thin;
     SELL_HIP(sell::plan_count(pa, s));
   }
   SELL_HIP(sell::build_scan(h->cs, h->cs, nc + 1, scan_tmp, s));
@@ -492,6 +494,20 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
     if (place)
       SELL_HIP(sell::plan_place(pa, C, z, po, h->cs, h->col, h->ncols,
                                 reinterpret_cast<sell::UnitCol *>(segs + z.nsegs1), s));
+    // the thin segments' slots once more, side by side; without room for them
+    // the product takes the slots from their places
+    if (z.nthin1 > 0) {
+      h->tslots = sell::thin_slots(S1, o.seg_cols > 0);
+      const size_t slots = (size_t)z.nthin1 * (size_t)h->tslots, cb = sizeof(int32_t) * slots;
+      void *tc = mem.get(cb + dtype_size(h->vdt) * slots);
+      if (tc) {
+        own(h.get(), tc, cb + dtype_size(h->vdt) * slots);
+        h->tcol = static_cast<int32_t *>(tc);
+        h->tval = static_cast<char *>(tc) + cb;
+        SELL_HIP(sell::build_thin(h->units1, z.nsegs1, C, h->cs, h->col, h->val, (int)dtype_size(h->vdt), h->tslots,
+                                  h->tcol, h->tval, s));
+      }
+    }
   }
 
   // x windows for LDS staging: when they fit (xwindow 0) or required (1)
@@ -675,6 +691,9 @@ sell_status spmv_run(sell_handle h, const void *x, void *y, void *stream, void *
   a.rl = h->rl;  // row_lengths: each row's lanes stop at its end
   if (h->units1) {
     a.units1 = h->units1;
+    a.tcol = h->tcol;
+    a.tval = h->tval;
+    a.tslots = h->tslots;
     a.nwork = h->nunits1;
     a.splits = h->splits1;
     a.nsplit = h->nsplit1;

@@ -672,6 +672,31 @@ __global__ void __launch_bounds__(kBlock) k_sorted_len(const int32_t *__restrict
   if (p < np) rl[p] = p < n ? len[perm ? (int64_t)perm[p] : p] : 0;
 }
 
+// One wave per unit: a thin segment's slots in the order that the product's lanes
+// take them -- of step t, lane l: column jb + t * (64 / L) + l / L of the (l % L)-th
+// row, L the number of rows raised to a power of two; zeros past the rows and the
+// columns.
+template <typename E>
+__global__ void __launch_bounds__(kBlock) k_thin(const Unit1 *__restrict__ units, int64_t nunits, int C,
+                                                 const int64_t *__restrict__ cs, const int32_t *__restrict__ col,
+                                                 const E *__restrict__ val, int64_t slots, int32_t *__restrict__ tcol,
+                                                 E *__restrict__ tval) {
+  const int64_t w = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  if (w >= nunits) return;
+  const Unit1 u = units[w];
+  if (u.rows == 0) return;
+  const ThinLane t = thin_lane(u.rows, lane_id());
+  const int wpc = C > 64 ? C / 64 : 1, rpw = C < 64 ? C : 64;
+  const int64_t chunk = u.item / wpc, off = cs[chunk] + (u.item - chunk * wpc) * rpw;
+  int64_t o = u.thin * slots + lane_id();
+  for (int32_t j0 = u.jb; j0 < u.je; j0 += t.step, o += 64) {
+    const int32_t j = j0 + t.col;
+    const bool ok = t.row >= 0 && j < u.je;
+    tcol[o] = ok ? col[off + (int64_t)j * C + t.row] : 0;
+    tval[o] = ok ? val[off + (int64_t)j * C + t.row] : E{};
+  }
+}
+
 // out[p] = in[perm[p]] (gather into sorted order) or out[perm[p]] = in[p]
 // (scatter back), for elements of ES bytes.
 template <typename E, bool SCATTER>
@@ -692,6 +717,19 @@ hipError_t build_sorted_len(const int32_t *len, const int32_t *perm, int64_t n, 
                             hipStream_t s) {
   if (np <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_sorted_len, dim3(blocks_for(np, kBlock)), dim3(kBlock), 0, s, len, perm, n, np, rl);
+  return hipGetLastError();
+}
+
+hipError_t build_thin(const Unit1 *units, int64_t nunits, int C, const int64_t *cs, const int32_t *col, const void *val,
+                      int esize, int64_t slots, int32_t *tcol, void *tval, hipStream_t s) {
+  if (nunits <= 0) return hipSuccess;
+  const dim3 nb(blocks_for(nunits, kBlock / 64));
+#define SELL_L(SS, EE)                                                                                      \
+  if (esize == SS)                                                                                         \
+    hipLaunchKernelGGL(k_thin<EE>, nb, dim3(kBlock), 0, s, units, nunits, C, cs, col,                       \
+                       static_cast<const EE *>(val), slots, tcol, static_cast<EE *>(tval));
+  SELL_L(8, uint64_t) SELL_L(4, uint32_t) SELL_L(2, uint16_t)
+#undef SELL_L
   return hipGetLastError();
 }
 

@@ -17,13 +17,14 @@ constexpr int kPlanBlock = 256;
 
 // Split slices, segments and (single plan) whole units of some cells.
 struct Counts {
-  int32_t split0, seg0, split1, seg1, whole1;
+  int32_t split0, seg0, split1, seg1, whole1, thin1;
   __device__ void add(const Counts &o) {
     split0 += o.split0;
     seg0 += o.seg0;
     split1 += o.split1;
     seg1 += o.seg1;
     whole1 += o.whole1;
+    thin1 += o.thin1;
   }
 };
 
@@ -56,7 +57,11 @@ __device__ __forceinline__ Counts count_cell(const PlanArgs &a, const Cell &e, i
     }
     if (w > S1) {
       n.split1 += a.wpc;
-      for (int h = 0; h < a.wpc; ++h) n.seg1 += split_item(a, c * a.wpc + h, w, S1).all;
+      for (int h = 0; h < a.wpc; ++h) {
+        const Split1 sp = split_item(a, c * a.wpc + h, w, S1);
+        n.seg1 += sp.all;
+        n.thin1 += sp.all - sp.dense;
+      }
     } else if (!e.group) {
       n.whole1 += a.wpc;
     }
@@ -82,6 +87,7 @@ __device__ Counts block_prefix(const Counts &v, Counts *total) {
   i.split1 = wave_incl(v.split1);
   i.seg1 = wave_incl(v.seg1);
   i.whole1 = wave_incl(v.whole1);
+  i.thin1 = wave_incl(v.thin1);
   const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 63) ws[w] = i;
   __syncthreads();
@@ -119,30 +125,31 @@ __global__ void __launch_bounds__(kPlanBlock) k_plan_count(PlanArgs a) {
   block_prefix(n, &total);
   if (threadIdx.x == 0) {
     // a single block: its prefixes are zero, its counts the totals
-    int64_t *b = gridDim.x > 1 ? a.blocks + 5 * (int64_t)blockIdx.x : &a.sizes->nsplit;
+    int64_t *b = gridDim.x > 1 ? a.blocks + kPlanCounts * (int64_t)blockIdx.x : &a.sizes->nsplit;
     b[0] = total.split0;
     b[1] = total.seg0;
     b[2] = total.split1;
     b[3] = total.seg1;
     b[4] = total.whole1;
+    b[5] = total.thin1;
     if (gridDim.x == 1)
-      for (int q = 0; q < 5; ++q) a.blocks[q] = 0;
+      for (int q = 0; q < kPlanCounts; ++q) a.blocks[q] = 0;
   }
 }
 
 // One workgroup: the blocks' counts to their exclusive prefixes (lane l of a
 // wave takes block l of 64, wave q quantity q), the totals to *sizes.
-__global__ void __launch_bounds__(5 * 64) k_plan_scan(PlanArgs a, int64_t nblocks) {
+__global__ void __launch_bounds__(kPlanCounts * 64) k_plan_scan(PlanArgs a, int64_t nblocks) {
   const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int64_t sum = 0;
   for (int64_t b = 0; b < nblocks; b += 64) {
-    int64_t v = b + lane < nblocks ? a.blocks[5 * (b + lane) + q] : 0;
+    int64_t v = b + lane < nblocks ? a.blocks[kPlanCounts * (b + lane) + q] : 0;
     int64_t i = v;
     for (int off = 1; off < 64; off <<= 1) {
       const int64_t o = __shfl_up(i, off);
       if (lane >= off) i += o;
     }
-    if (b + lane < nblocks) a.blocks[5 * (b + lane) + q] = sum + i - v;
+    if (b + lane < nblocks) a.blocks[kPlanCounts * (b + lane) + q] = sum + i - v;
     sum += __shfl(i, 63);
   }
   if (lane == 0) (&a.sizes->nsplit)[q] = sum;
@@ -160,7 +167,7 @@ __global__ void __launch_bounds__(kPlanBlock) k_plan_emit(PlanArgs a, int32_t S,
   }
   const Counts at = block_prefix(n, &total);
   if (cell >= a.ncells) return;
-  const int64_t *b = a.blocks + 5 * (int64_t)blockIdx.x;
+  const int64_t *b = a.blocks + kPlanCounts * (int64_t)blockIdx.x;
   int64_t split0 = b[0] + at.split0, seg0 = b[1] + at.seg0, split1 = b[2] + at.split1, seg1 = b[3] + at.seg1;
   int64_t whole1 = b[4] + at.whole1;
   if (e.group) o.units1[nsegs1 + whole1++] = {(int32_t)(e.c0 * a.wpc), 0, 0, 0, -1, 0, 0};
@@ -235,7 +242,10 @@ __global__ void __launch_bounds__(kPlanBlock) k_plan_segs1(PlanArgs a, const Spl
     const int64_t p = (int64_t)d.item * a.rpw + r;
     u.rows = __ballot(r < a.rpw && p < a.nrows && a.len[a.perm ? (int64_t)a.perm[p] : p] > u.jb);
   }
-  if ((threadIdx.x & 63) == 0) out[i] = u;
+  if ((threadIdx.x & 63) == 0) {
+    if (u.rows != 0) u.thin = (int32_t)atomicAdd(a.next_thin, 1u);
+    out[i] = u;
+  }
 }
 
 // One wave per split segment: the mean column of its rows at the middle of
@@ -332,7 +342,7 @@ hipError_t plan_count(const PlanArgs &a, hipStream_t s) {
   hipLaunchKernelGGL(k_plan_count, grid(a.ncells), dim3(kPlanBlock), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || plan_blocks(a.ncells) == 1) return e;
-  hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(5 * 64), 0, s, a, plan_blocks(a.ncells));
+  hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(kPlanCounts * 64), 0, s, a, plan_blocks(a.ncells));
   return hipGetLastError();
 }
 

@@ -39,13 +39,14 @@ struct SplitDesc {
 // columns [jb, je) of an item. nseg 0: a group of short chunks from item on;
 // part < 0: the whole item, y is written; else a segment, whose row sums go to
 // partial[part ...]. rows: the rows that a thin segment holds, at most eight
-// (bit r: row r of the item); 0: all.
+// (bit r: row r of the item); 0: all. thin: its number among the thin segments
+// (its copy of its slots).
 struct Unit1 {
   int32_t item;
   int32_t nseg;
   int32_t jb, je;
   int32_t part;
-  int32_t pad;
+  int32_t thin;
   uint64_t rows;
 };
 
@@ -147,16 +148,20 @@ __host__ __device__ inline int32_t single_seg_cols(int64_t total_steps, int T, i
   return cols < S ? (int32_t)cols : S;
 }
 
-// Thin segments: where at most thin_rows rows of a slice still hold entries the single-vector product takes those rows alone, 64 / rows columns a
-// step and no fewer than the T of the others, whose lanes would step over padding
-// for 24 of 32 rows and more. kThinCols columns a unit with up to eight rows,
-// kThinnestCols with up to two: at most eight steps, one round of loads. us
-// without / with thin segments, C = 16, 32, 64: power-law 1M, sigma = 1024 71, 98,
-// 155 / 70, 80, 89; the same in FP32 53, 69, 105 / 51, 65, 73 (at C = 32 a row's
-// entries lie one to a line of val and of col: the bytes stay); 2M, sigma = 2^14
-// 125, 138, 171 / 124, 130, 140; 50k, sigma = 1024 10.6, 12.6, 19.4 / 10.7, 10.9,
-// 12.2; 200k, sigma = n 11.9, 13.5, 18.5 / 12.5, 12.7, 16.1. 256 columns with up
-// to two rows: 200k 13.9, 14.2, 16.4; 256 with up to eight: 18, 18, 19.
+// Thin segments: where at most thin_rows rows of a slice still hold entries the
+// single-vector product takes those rows alone, 64 / rows columns a step and no
+// fewer than the T of the others, whose lanes would step over padding for 24 of 32
+// rows and more. kThinCols columns a unit with up to eight rows, kThinnestCols with
+// up to two: at most eight steps, one round of loads. us without thin segments /
+// with them, slots in their places / slots copied, at C = 16; 32; 64:
+//   power-law 1M, sigma 1024  71 / 70 / 53;    98 / 80 / 55;    155 / 89 / 63
+//   the same in FP32          53 / 51 / 41;    69 / 65 / 41;    105 / 73 / 49
+//   2M, sigma 2^14            125 / 124 / 117; 138 / 130 / 120; 171 / 140 / 129
+//   50k, sigma 1024           10.6 / 10.7 / 10.9; 12.6 / 10.9 / 11.0; 19.4 / 12.2 / 12.0
+//   200k, sigma n             11.9 / 12.5 / 12.3; 13.5 / 12.7 / 13.2; 18.5 / 16.1 / 16.6
+// In place, 256 columns with up to two rows: 200k 13.9, 14.2, 16.4; 256 with up to
+// eight: 18, 18, 19. Copied, with up to sixteen rows (half or a quarter of the
+// slice): within 2 %, at up to 20 % more memory.
 constexpr int32_t kThinCols = 64;
 constexpr int32_t kThinnestCols = 128;
 constexpr int kThinnestRows = 2;
@@ -165,13 +170,22 @@ __host__ __device__ inline int thin_rows(int rpw, int T) {
   return 64 / T < few ? 64 / T : few;
 }
 
+// Slots of a thin segment's copy, in the order that the lanes take them (64 a
+// step): whole steps of eight rows, or of two. Split slices are wider than a
+// segment and their segments full but for the last, so with C >= 16 rows the copies
+// hold about as many slots as val at most.
+__host__ __device__ inline int64_t thin_slots(int32_t S1, bool fixed) {
+  const int64_t tc = fixed || S1 > kThinCols ? S1 : kThinCols, uc = fixed || S1 > kThinnestCols ? S1 : kThinnestCols;
+  return ((8 * tc > 2 * uc ? 8 * tc : 2 * uc) + 63) / 64 * 64;
+}
+
 // Segments of a slice w columns wide in the single plan: dense ones of S1
 // columns up to column thin, thin ones of tc columns up to column thinnest, then
 // thin ones of uc columns. few: the columns in which more than thin_rows, and
 // more than kThinnestRows, rows hold entries (nullptr: no thin segments).
 struct Split1 {
   int32_t thin, thinnest, tc, uc;
-  int32_t dense, segs;  // dense segments, dense and thin ones
+  int32_t dense, segs;  // dense segments, dense and thin ones of tc columns
   int32_t all;
 };
 __host__ __device__ inline Split1 split1_of(const int32_t *few, int32_t w, int32_t S1, bool fixed) {
@@ -188,6 +202,25 @@ __host__ __device__ inline Split1 split1_of(const int32_t *few, int32_t w, int32
   r.all = r.segs + (int32_t)(((int64_t)w - r.thinnest + r.uc - 1) / r.uc);
   return r;
 }
+
+#if defined(__HIPCC__)
+// A lane's share of a thin segment: row of the item (-1: none), column offset,
+// columns per step, log2 of the lanes side by side.
+struct ThinLane {
+  int row, col, step, lg;
+};
+__device__ __forceinline__ ThinLane thin_lane(uint64_t rows, int lane) {
+  const int n = __popcll(rows);
+  ThinLane t;
+  t.lg = n > 4 ? 3 : n > 2 ? 2 : n > 1 ? 1 : 0;
+  t.step = 64 >> t.lg;
+  t.col = lane >> t.lg;
+  const int q = lane & ((1 << t.lg) - 1);
+  for (int e = 0; e < q; ++e) rows &= rows - 1;
+  t.row = q < n ? __ffsll((unsigned long long)rows) - 1 : -1;
+  return t;
+}
+#endif
 
 // Arguments of the spMVM kernels (by value).
 struct SpmvArgs {
@@ -206,6 +239,9 @@ struct SpmvArgs {
   void *partial;
   int32_t seg_cols;     // chunk columns per segment (multiple of kSegAlign)
   const Unit1 *units1;  // single-vector product: its units, or nullptr (wave w handles item w)
+  const int32_t *tcol;  // thin segments' copies of their slots (tslots each), or nullptr
+  const void *tval;
+  int64_t tslots;
   const int32_t *rl;    // single-vector product: length of every row in sorted
                         // order (N_c * C entries), or nullptr
   // block form only
@@ -334,10 +370,11 @@ hipError_t build_invert(const int32_t *perm, int64_t n, int32_t *iperm, hipStrea
 struct PlanSizes {
   int64_t total_steps;  // wave steps of all items (from build_chunkwidth)
   int64_t nsplit, nsegs;            // block form: split slices, their segments
-  int64_t nsplit1, nsegs1, nwhole1;  // single-vector product
+  int64_t nsplit1, nsegs1, nwhole1, nthin1;  // single-vector product: nthin1 of the segments are thin
   int32_t max_width;    // widest chunk (from build_chunkwidth)
   int32_t pad;
 };
+constexpr int kPlanCounts = 6;
 struct PlanArgs {
   const int32_t *cl;
   int64_t nchunks, ncells;  // cells of grp chunks
@@ -347,7 +384,8 @@ struct PlanArgs {
   const int32_t *few;       // two per item (split1_of), or nullptr
   const int32_t *len, *perm;  // row lengths and order (perm nullptr: identity)
   int64_t nrows;
-  int64_t *blocks;          // 5 * plan_blocks(ncells)
+  int64_t *blocks;          // kPlanCounts * plan_blocks(ncells)
+  uint32_t *next_thin;      // zeroed: numbers the thin segments
   PlanSizes *sizes;         // total_steps and max_width set, the rest written
 };
 struct PlanOut {
@@ -362,6 +400,10 @@ hipError_t plan_count(const PlanArgs &a, hipStream_t s);
 hipError_t plan_emit(const PlanArgs &a, int32_t S, int32_t S1, const PlanSizes &z, const PlanOut &o, hipStream_t s);
 hipError_t plan_place(const PlanArgs &a, int C, const PlanSizes &z, const PlanOut &o, const int64_t *cs,
                       const int32_t *col, int64_t ncols, UnitCol *at, hipStream_t s);
+// The thin segments' slots (units: nunits of a single plan; of those with rows,
+// slots per segment) copied to tcol and tval, elements of esize bytes.
+hipError_t build_thin(const Unit1 *units, int64_t nunits, int C, const int64_t *cs, const int32_t *col, const void *val,
+                      int esize, int64_t slots, int32_t *tcol, void *tval, hipStream_t s);
 // rl[p] = length of the row in sorted position p (0 for p >= n), p < np
 hipError_t build_sorted_len(const int32_t *len, const int32_t *perm, int64_t n, int64_t np, int32_t *rl,
                             hipStream_t s);
@@ -440,6 +482,9 @@ struct sell_matrix {
   sell::Unit1 *units1 = nullptr;
   int64_t nunits1 = 0;
   sell::SplitDesc *splits1 = nullptr;
+  int32_t *tcol = nullptr;  // thin segments' copies of their slots
+  void *tval = nullptr;
+  int64_t tslots = 0;
   int64_t nsplit1 = 0, nsegs1 = 0;
   int64_t nsplit = 0;
   int64_t nsegs = 0;                  // total segments of split items

@@ -305,17 +305,15 @@ __device__ __forceinline__ void spmv_unit(const void *__restrict__ valv, const i
   for (int v = 0; v < VV; ++v) mine[v] = acc[v];
 }
 
-// A thin segment: columns [jb, je) of a slice of which only `rows` (one to eight
+// A thin segment: columns [jb, je) of a slice of which only u.rows (one to eight
 // bits) still hold entries. L = 1, 2, 4 or 8 lanes side by side take a column's
 // rows, 64 / L columns a step, so a step of one row covers 64 columns where
-// spmv_unit covers T; the other rows' sums are 0. Bound by the lines of val and
-// col that the rows lie in (one of each per column, whatever the row). Slots
-// holding 0 skip the gather.
+// spmv_unit covers T; the other rows' sums are 0. The slots come from the
+// segment's copy, 64 consecutive ones a step: in their places each row's entry
+// brings a line of val and one of col of its own (power-law 1M, sigma = 1024, FP32,
+// C = 32: 66 us so, 42 from the copies). Slots holding 0 skip the gather.
 template <int COMBO, int C>
-__device__ __forceinline__ void spmv_thin(const void *__restrict__ valv, const int32_t *__restrict__ col,
-                                          const int64_t *__restrict__ cs, const void *__restrict__ xv, int32_t item,
-                                          int32_t jb, int32_t je, uint64_t rows, int64_t part,
-                                          void *__restrict__ partial, int lane) {
+__device__ __forceinline__ void spmv_thin(const SpmvArgs &a, const Unit1 &u, int lane) {
   using V = typename Types<COMBO>::V;
   using X = typename Types<COMBO>::X;
   using A = typename Types<COMBO>::A;
@@ -323,38 +321,47 @@ __device__ __forceinline__ void spmv_thin(const void *__restrict__ valv, const i
   constexpr int RPW = C < 64 ? C : 64;
   constexpr int WPC = C > 64 ? C / 64 : 1;
   constexpr int U = 8;
-  const int n = __popcll(rows);
-  const int lg = n > 4 ? 3 : n > 2 ? 2 : n > 1 ? 1 : 0;
-  const int q = lane & ((1 << lg) - 1), step = 64 >> lg;
-  uint64_t m = rows;
-  for (int e = 0; e < q; ++e) m &= m - 1;  // the q-th row
-  const int r = q < n ? __ffsll((unsigned long long)m) - 1 : -1;
-  const int64_t chunk = item / WPC;
-  const int64_t off = cs[chunk] + (item - chunk * WPC) * RPW;
-  const X *x = static_cast<const X *>(xv);
+  const ThinLane t = thin_lane(u.rows, lane);
+  const X *x = static_cast<const X *>(a.x);
+  const int nstep = (u.je - u.jb + t.step - 1) >> (6 - t.lg);
+  // slot of step s: o0 + s * so (no copy: in its place, or slot 0 where the lane
+  // has none)
+  const int32_t *cp = a.col;
+  const V *vp = static_cast<const V *>(a.val);
+  int64_t o0, so = 64;
+  int nok = nstep;  // steps that hold a slot of this lane
+  if (a.tcol) {
+    cp = a.tcol;
+    vp = static_cast<const V *>(a.tval);
+    o0 = u.thin * a.tslots + lane;
+  } else {
+    const int64_t chunk = u.item / WPC;
+    so = (int64_t)t.step * C;
+    o0 = a.cs[chunk] + (u.item - chunk * WPC) * RPW + (int64_t)(u.jb + t.col) * C + t.row;
+    nok = t.row >= 0 ? (u.je - u.jb - t.col + t.step - 1) >> (6 - t.lg) : 0;
+  }
   A acc = 0;
-  for (int32_t j0 = jb + (lane >> lg); j0 - (lane >> lg) < je; j0 += U * step) {
+  for (int s = 0; s < nstep; s += U) {
     int32_t ci[U];
     R raw[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int32_t j = j0 + u * step;
-      const bool ok = r >= 0 && j < je;
-      const int64_t o = ok ? off + (int64_t)j * C + r : 0;
-      ci[u] = __builtin_nontemporal_load(col + o);
-      raw[u] = (R)__builtin_nontemporal_load(static_cast<const V *>(valv) + o);
-      if (!ok) raw[u] = 0;
+    for (int e = 0; e < U; ++e) {
+      const bool ok = s + e < nok;
+      const int64_t o = ok ? o0 + (s + e) * so : 0;
+      ci[e] = __builtin_nontemporal_load(cp + o);
+      raw[e] = (R)__builtin_nontemporal_load(vp + o);
+      if (!ok) raw[e] = 0;
     }
     X xg[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) xg[u] = raw[u] != 0 ? x[ci[u]] : (X)0;
+    for (int e = 0; e < U; ++e) xg[e] = raw[e] != 0 ? x[ci[e]] : (X)0;
 #pragma unroll
-    for (int u = 0; u < U; ++u) acc = fmac(cvt(raw[u]), xg[u], acc);
+    for (int e = 0; e < U; ++e) acc = fmac(cvt(raw[e]), xg[e], acc);
   }
-  for (int o = 32; o >= 1 << lg; o >>= 1) acc += __shfl_xor(acc, o);
+  for (int o = 32; o >= 1 << t.lg; o >>= 1) acc += __shfl_xor(acc, o);
   // row `lane` of the slice: the sum that its place among the set bits holds
-  const A sum = __shfl(acc, __popcll(rows & ((1ull << lane) - 1ull)) & 63);
-  if (lane < RPW) static_cast<A *>(partial)[part + lane] = rows >> lane & 1ull ? sum : (A)0;
+  const A sum = __shfl(acc, __popcll(u.rows & ((1ull << lane) - 1ull)) & 63);
+  if (lane < RPW) static_cast<A *>(a.partial)[u.part + lane] = u.rows >> lane & 1ull ? sum : (A)0;
 }
 
 // Raw buffer loads over the slots of one chunk. The descriptor (uniform over
@@ -681,7 +688,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) k_spmv(SpmvArgs a) {
     }
     if constexpr (C >= 16) {
       if (u.rows != 0) {
-        spmv_thin<COMBO, C>(a.val, a.col, a.cs, a.x, u.item, u.jb, u.je, u.rows, u.part, a.partial, lane);
+        spmv_thin<COMBO, C>(a, u, lane);
         return;
       }
     }

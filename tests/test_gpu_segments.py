@@ -76,3 +76,25 @@ def test_thin_segments(C, m):
             assert np.array_equal(spmv_gpu(r, x), spmv_gpu(h, x))
     h = build(A, C, 1, seg_cols=64, val_dtype="f32", acc_dtype="f32")
     check_reduced(A, h, x, "f32", "f32", C)
+
+
+@pytest.mark.parametrize("C", [16, 64, 128])
+def test_thin_segments_without_copies(C):
+    """Where no memory is left for the thin segments' copies the product takes
+    the slots from their places: the same sums in the same order."""
+    from paper_1307_6209_amd import sellcs
+    lens = [3] * (4 * C)
+    lens[5], lens[C + 1], lens[C + 9], lens[3 * C] = 1000, 65, 33, 300
+    A = lengths_crs(lens, 5000, 97)
+    x = synth.uniform(A.ncols, 98)
+    full = build(A, C, 1)
+    ref = spmv_gpu(full, x)
+    check_fp64(A, ref, x, m=chain_per_row(A, full, C))
+    for n in range(64):  # the first build that fails nowhere else
+        try:
+            h = build(A, C, 1, xwindow=-1, allocator=sellcs.TorchAllocator(fail_after=n))
+        except sellcs.SellError:
+            continue
+        break
+    assert h.info["device_bytes"] < full.info["device_bytes"]
+    assert np.array_equal(spmv_gpu(h, x), ref)
