@@ -985,7 +985,6 @@ struct sell_batch_s {
   std::vector<sell_handle> hs;
   int combo = 0, C = 0, U = 8;
   Geom g{};
-  int32_t seg_cols = 0;
   int64_t nunits = 0, nsplit = 0;
   bool persistent = false;
   int32_t nwaves = 0;  // persistent form only
@@ -1064,7 +1063,6 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
   }
   DeviceInfo di = device_info();
   const int32_t S = sell::auto_seg_cols(total, g.T, di.cus);
-  B->seg_cols = S;
   // work units of every matrix: the segments of its split chunks, then its
   // whole chunks; cost estimate of a unit: its wave steps plus a fixed charge
   std::vector<sell::BUnit> all;
@@ -1076,24 +1074,28 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
   int64_t off = 0;
   for (int32_t b = 0; b < count; ++b) {
     const ItemCols &s = st[b];
+    std::vector<int64_t> start(s.cols.size());  // first slot of each item's chunk
+    int64_t at = 0;
+    for (size_t it = 0; it < start.size(); ++it) {
+      start[it] = at;
+      if ((it + 1) % (size_t)g.wpc == 0) at += (int64_t)B->C * s.cols[it];
+    }
     for (size_t it = 0; it < s.cols.size(); ++it) {
       const int32_t w = s.cols[it];
       if (w <= S) continue;
       const int32_t nseg = (w + S - 1) / S;
-      const int32_t sid = (int32_t)splits.size();
       splits.push_back({b, (int32_t)it, nseg, 0, off});
-      off += (int64_t)nseg * g.rpw;
-      for (int32_t q = 0; q < nseg; ++q) {
-        all.push_back({b, (int32_t)it, q, nseg, sid, {0, 0, 0}});
+      for (int32_t q = 0; q < nseg; ++q, off += g.rpw) {
         const int64_t cols = std::min<int64_t>(S, (int64_t)w - (int64_t)q * S);
+        all.push_back({b, (int32_t)it, q * S, (int32_t)(q * S + cols), start[it], off});
         umat.push_back(b);
         ucost.push_back((cols + g.T - 1) / g.T + kFixed);
         usplit.push_back(1);
       }
     }
     // whole chunks; with C in 8..32 each run of 64 / C consecutive chunks at
-    // most 64 / C columns wide is one unit (nseg 0: one wave covers all their
-    // rows)
+    // most 64 / C columns wide is one unit (one wave covers all their
+    // rows, jb -1)
     const size_t grp = B->C >= 8 && B->C <= 32 ? (size_t)(64 / B->C) : 0;
     const int32_t wmax = (int32_t)grp;
     for (size_t it = 0; it < s.cols.size(); ++it) {
@@ -1103,7 +1105,9 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
         size_t e = it + 1;
         while (e < it + grp && s.cols[e] <= wmax) ++e;
         if (e == it + grp) {
-          all.push_back({b, (int32_t)it, 0, 0, 0, {0, 0, 0}});
+          uint32_t widths = 0;
+          for (size_t q = 0; q < grp; ++q) widths |= (uint32_t)s.cols[it + q] << (4 * q);
+          all.push_back({b, (int32_t)it, -1, (int32_t)widths, start[it], -1});
           umat.push_back(b);
           ucost.push_back(1 + kFixed);
           usplit.push_back(0);
@@ -1111,7 +1115,7 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
           continue;
         }
       }
-      all.push_back({b, (int32_t)it, 0, 1, 0, {0, 0, 0}});
+      all.push_back({b, (int32_t)it, 0, w, start[it], -1});
       umat.push_back(b);
       ucost.push_back((w + g.T - 1) / g.T + kFixed);
       usplit.push_back(0);
@@ -1136,7 +1140,7 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
                                             sell::kXcds, nwaves);
   std::vector<sell::BUnit> units(plan.order.size());
   for (size_t i = 0; i < plan.order.size(); ++i)
-    units[i] = plan.order[i] < 0 ? sell::BUnit{-1, 0, 0, 1, 0, {0, 0, 0}} : all[(size_t)plan.order[i]];
+    units[i] = plan.order[i] < 0 ? sell::BUnit{-1, 0, 0, 0, 0, -1} : all[(size_t)plan.order[i]];
   B->nunits = (int64_t)units.size();
   if (B->nunits >= ((int64_t)1 << 31)) return fail(SELL_ERR_UNSUPPORTED, "sell_batch_create: too many work units");
   std::vector<int32_t> slice = plan.slice;
@@ -1164,8 +1168,6 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
     sell::BatchMat &m = B->host_mats[(size_t)b];
     m.val = hs[b]->val;
     m.col = hs[b]->col;
-    m.cs = hs[b]->cs;
-    m.cl = hs[b]->cl;
     m.perm = hs[b]->sym ? nullptr : hs[b]->perm;
     m.x = nullptr;
     m.y = nullptr;
@@ -1182,7 +1184,6 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
   a.splits = B->splits;
   a.nsplit = B->nsplit;
   a.partial = B->partial;
-  a.seg_cols = B->seg_cols;
   hipStream_t cap = nullptr;
   SELL_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
   hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);

@@ -57,15 +57,18 @@ struct UnitCol {
   int32_t live;
 };
 
-// Work unit of the batched kernel (adds the matrix index; mat < 0: an empty
-// unit that only fills the grid).
+// Work unit of the batched kernel (mat < 0: an empty unit that only fills the
+// grid): columns [jb, je) of a row slice whose chunk starts at slot off, its sums
+// to y (part < 0) or to partial[part ...]; jb < 0: a group of short chunks from
+// item on, the width of its q-th chunk in bits 4q of je. With all of it here a
+// wave goes from its unit to the slots, not over the chunk's width and start (64
+// power-law matrices, sigma = 200: 327 us so, now 319; sigma = n: the same).
 struct BUnit {
   int32_t mat;
   int32_t item;
-  int32_t seg;
-  int32_t nseg;
-  int32_t sid;
-  int32_t pad[3];
+  int32_t jb, je;
+  int64_t off;
+  int64_t part;
 };
 
 // Geometry of a chunk height on a 64-lane wavefront whose lanes each hold
@@ -253,8 +256,6 @@ struct SpmvArgs {
 struct BatchMat {
   const void *val;
   const int32_t *col;
-  const int64_t *cs;
-  const int32_t *cl;
   const int32_t *perm;
   const void *x;
   void *y;
@@ -279,7 +280,6 @@ struct BatchArgs {
   const BSplitDesc *splits;
   int64_t nsplit;
   void *partial;
-  int32_t seg_cols;
 };
 
 // x window of a product workgroup (LDS staging): groups of G consecutive

@@ -142,7 +142,7 @@ __device__ __forceinline__ void opaque(T &v) {
 
 
 // One work unit: columns [jb, je) of the rows [h*rpw, (h+1)*rpw) of a chunk
-// (item: the chunk and h), jb a multiple of T. part < 0: all columns, y is
+// (item: the chunk and h; base: the chunk's first slot), jb a multiple of T. part < 0: all columns, y is
 // written; else a segment, whose row sums go to partial[part ...].
 //
 // Lane l holds the VV consecutive slots VV*l .. VV*l+VV-1 of every wave step
@@ -158,7 +158,7 @@ __device__ __forceinline__ void opaque(T &v) {
 // zero by zero -- and the result are those of the plain product.
 template <int COMBO, int C, int U, int VV, int ZS>
 __device__ __forceinline__ void spmv_unit(const void *__restrict__ valv, const int32_t *__restrict__ col,
-                                          const int64_t *__restrict__ cs, const int32_t *__restrict__ perm,
+                                          int64_t base, const int32_t *__restrict__ perm,
                                           const void *__restrict__ xv, void *__restrict__ yv, int64_t nrows,
                                           int32_t item, int32_t jb, int32_t je, int64_t part,
                                           void *__restrict__ partial, int lane,
@@ -178,7 +178,6 @@ __device__ __forceinline__ void spmv_unit(const void *__restrict__ valv, const i
   const int64_t chunk = item / WPC;
   const int h = item - (int)(chunk * WPC);
   const int rl0 = (VV * lane) % RPW, t = (VV * lane) / RPW;
-  const int64_t base = cs[chunk];
   const int sb = jb / T, se = (je + T - 1) / T;
   const int full = je / T;  // steps below this one hold a real column in every lane
   const int64_t off0 = base + (int64_t)t * C + h * RPW + rl0;
@@ -634,23 +633,17 @@ __global__ void __launch_bounds__(kCombineBlock) k_combine(SpmvArgs a) {
 // (a butterfly over lane offsets 32, 16, ..., C with the missing columns as
 // +0), so the result is the same bit for bit; slots holding 0 skip the
 // gather.
-template <int COMBO, int C, bool RL = false>
+// p: the lane's row in sorted order, w: its columns, base: its first slot.
+template <int COMBO, int C>
 __device__ __forceinline__ void spmv_group(const void *__restrict__ valv, const int32_t *__restrict__ col,
-                                           const int64_t *__restrict__ cs, const int32_t *__restrict__ clp,
-                                           const int32_t *__restrict__ perm, const void *__restrict__ xv,
-                                           void *__restrict__ yv, int64_t nrows, int32_t item, int lane,
-                                           const int32_t *__restrict__ rlp = nullptr) {
+                                           int64_t base, int w, const int32_t *__restrict__ perm,
+                                           const void *__restrict__ xv, void *__restrict__ yv, int64_t nrows,
+                                           int64_t p) {
   using V = typename Types<COMBO>::V;
   using X = typename Types<COMBO>::X;
   using A = typename Types<COMBO>::A;
   constexpr int T = 64 / C;
   static_assert(C >= 8 && C <= 32, "two to eight chunks per wave");
-  const int32_t c = item + lane / C;
-  const int r = lane % C;
-  const int64_t p = (int64_t)c * C + r;
-  // RL: only the row's own slots are loaded (the rest stay zero, as padding)
-  const int w = RL ? rlp[p] : clp[c];
-  const int64_t base = cs[c] + r;
   V v[T];
   int32_t ci[T];
 #pragma unroll
@@ -682,7 +675,11 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) k_spmv(SpmvArgs a) {
     u = a.units1[w];
     if constexpr (C >= 8 && C <= 32) {
       if (u.nseg == 0) {  // a group of short chunks
-        spmv_group<COMBO, C, ZS == 2>(a.val, a.col, a.cs, a.cl, a.perm, a.x, a.y, a.nrows, u.item, lane, a.rl);
+        // row lengths: only the row's own slots are loaded (the rest stay zero)
+        const int32_t c = u.item + lane / C;
+        const int64_t p = (int64_t)c * C + lane % C;
+        spmv_group<COMBO, C>(a.val, a.col, a.cs[c] + lane % C, ZS == 2 ? a.rl[p] : a.cl[c], a.perm, a.x, a.y, a.nrows,
+                             p);
         return;
       }
     }
@@ -695,8 +692,8 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) k_spmv(SpmvArgs a) {
   } else {
     u.je = a.cl[C > 64 ? w / (C / 64) : w];
   }
-  spmv_unit<COMBO, C, U, VV, ZS>(a.val, a.col, a.cs, a.perm, a.x, a.y, a.nrows, u.item, u.jb, u.je, u.part, a.partial,
-                                 lane, a.rl);
+  spmv_unit<COMBO, C, U, VV, ZS>(a.val, a.col, a.cs[C > 64 ? u.item / (C / 64) : u.item], a.perm, a.x, a.y, a.nrows,
+                                 u.item, u.jb, u.je, u.part, a.partial, lane, a.rl);
 }
 
 // Batched form: one launch over the concatenated work units of all
@@ -725,21 +722,18 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) k_batch(BatchArgs a) {
     if (u.mat < 0) continue;  // grid filler
     const BatchMat m = a.mats[u.mat];
     if constexpr (C >= 8 && C <= 32) {
-      if (u.nseg == 0) {  // a group of short chunks
-        spmv_group<COMBO, C>(m.val, m.col, m.cs, m.cl, m.perm, m.x, m.y, m.nrows, u.item, lane);
+      if (u.jb < 0) {  // a group of short chunks, their widths in je
+        const int g = lane / C;
+        int64_t base = u.off + lane % C;
+        for (int q = 0; q < 64 / C - 1; ++q)
+          if (q < g) base += ((uint32_t)u.je >> 4 * q & 15u) * C;
+        spmv_group<COMBO, C>(m.val, m.col, base, (int)((uint32_t)u.je >> 4 * g & 15u), m.perm, m.x, m.y, m.nrows,
+                             (int64_t)u.item * C + lane);
         continue;
       }
     }
-    constexpr int WPC = C > 64 ? C / 64 : 1, RPW = C < 64 ? C : 64;
-    int32_t jb = 0, je = m.cl[u.item / WPC];
-    int64_t part = -1;
-    if (u.nseg > 1) {
-      jb = u.seg * a.seg_cols;
-      je = jb + a.seg_cols < je ? jb + a.seg_cols : je;
-      part = a.splits[u.sid].poff + (int64_t)u.seg * RPW;
-    }
-    spmv_unit<COMBO, C, U, 1, true>(m.val, m.col, m.cs, m.perm, m.x, m.y, m.nrows, u.item, jb, je, part, a.partial,
-                                    lane);
+    spmv_unit<COMBO, C, U, 1, true>(m.val, m.col, u.off, m.perm, m.x, m.y, m.nrows, u.item, u.jb, u.je, u.part,
+                                    a.partial, lane);
   }
 }
 
