@@ -140,6 +140,16 @@ __device__ __forceinline__ void opaque(T &v) {
   asm volatile("" : "+v"(v));
 }
 
+// y of the row at sorted position p. Permuted rows are stored one by one, several
+// to a line: the L2 gathers a line's rows (64 power-law matrices, sigma = n,
+// C = 32: 111 us with streaming stores, which leave half of the writes to memory
+// partial, 107; 200k, sigma = n 13.1 / 12.0; 50k, sigma = 1024 10.8 / 10.1). Not
+// where y alone would fill the L2s and turn x out: 2M, sigma = 2^14 119 / 121.
+template <typename A>
+__device__ __forceinline__ void put_row(A *y, const int32_t *__restrict__ perm, int64_t p, int64_t nrows, A v) {
+  if (perm && nrows <= (int64_t)((8 << 20) / sizeof(A))) y[perm[p]] = v;
+  else __builtin_nontemporal_store(v, y + (perm ? (int64_t)perm[p] : p));
+}
 
 // One work unit: columns [jb, je) of the rows [h*rpw, (h+1)*rpw) of a chunk
 // (item: the chunk and h; base: the chunk's first slot), jb a multiple of T. part < 0: all columns, y is
@@ -294,7 +304,7 @@ __device__ __forceinline__ void spmv_unit(const void *__restrict__ valv, const i
 #pragma unroll
     for (int v = 0; v < VV; ++v) {
       const int64_t p = p0 + v;
-      if (p < nrows) __builtin_nontemporal_store(acc[v], y + (perm ? (int64_t)perm[p] : p));
+      if (p < nrows) put_row(y, perm, p, nrows, acc[v]);
     }
     return;
   }
@@ -662,7 +672,7 @@ __device__ __forceinline__ void spmv_group(const void *__restrict__ valv, const 
   for (int d = T / 2; d >= 1; d >>= 1)
 #pragma unroll
     for (int t = 0; t < d; ++t) s[t] = s[t] + s[t + d];
-  if (p < nrows) __builtin_nontemporal_store(s[0], static_cast<A *>(yv) + (perm ? (int64_t)perm[p] : p));
+  if (p < nrows) put_row(static_cast<A *>(yv), perm, p, nrows, s[0]);
 }
 
 template <int COMBO, int C, int U, int VV, int ZS>
