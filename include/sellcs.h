@@ -143,8 +143,9 @@ typedef struct {
   int32_t unroll;        /* slots in flight per lane of the product that runs */
   int32_t vec;
   int32_t seg_cols;      /* split threshold in chunk columns */
-  int64_t nunits;        /* work units of one sell_spmv launch */
-  int64_t nsplit;        /* row slices whose chunk is split over several waves */
+  int64_t nunits;        /* row slices, those wider than seg_cols as segments of that many columns
+                            (sell_spmv's own segments may be finer) */
+  int64_t nsplit;        /* row slices wider than seg_cols */
   int32_t has_perm;      /* 0 when the row order is the identity (sigma == 1) */
   int32_t permuted_columns; /* 1 when built with permute_columns */
   int64_t device_bytes;  /* device memory held by the handle */
@@ -173,8 +174,8 @@ typedef struct {
  * opts:   NULL for defaults. Supported (val, acc) pairs: (F64, F64),
  *         (F32, F32), (F32, F64), (BF16, F32), (BF16, F64); x is F64 for F64
  *         values and F32 otherwise. Values are rounded to nearest-even.
- * stream: all device work runs on it; the call synchronises it once to read
- *         the padded size and the validation flags.
+ * stream: all device work runs on it; the call synchronises it to read the
+ *         sizes and the validation flags, and before it returns.
  * out:    receives the new handle; it owns every device array it holds.
  * Errors: SELL_ERR_BAD_CRS when rpt[0] != 0, rpt decreases, rpt[nrows] !=
  *         nnz, a row is longer than 2^31 - 1, or a column lies outside

@@ -236,11 +236,11 @@ struct SpmvArgs {
   void *y;
   int64_t nrows;
   int64_t nwork;        // items (no unit list) or units
-  const Unit *units;    // nullptr: wave w handles item w whole
+  const Unit *units;    // block form: its units, or nullptr (wave w handles item w whole)
   const SplitDesc *splits;
   int64_t nsplit;
   void *partial;
-  int32_t seg_cols;     // chunk columns per segment (multiple of kSegAlign)
+  int32_t seg_cols;     // block form: chunk columns per segment (multiple of kSegAlign)
   const Unit1 *units1;  // single-vector product: its units, or nullptr (wave w handles item w)
   const int32_t *tcol;  // thin segments' copies of their slots (tslots each), or nullptr
   const void *tval;

@@ -25,7 +25,9 @@
 // a partial buffer and a second, small kernel adds them in segment order and
 // writes y. The result does not depend on the order the waves ran in, and no
 // cross-wave synchronisation (with its cache write-back and invalidation) is
-// needed inside the product kernel.
+// needed inside the product kernel. The single-vector product has segments of
+// its own (Unit1), finer and cut where few rows of a slice are left; the block
+// form and the batch use seg_cols columns throughout.
 #pragma once
 
 #include "sell_internal.h"
