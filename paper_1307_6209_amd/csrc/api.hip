@@ -498,6 +498,7 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
     // the product takes the slots from their places
     if (z.nthin1 > 0) {
       h->tslots = sell::thin_slots(S1, o.seg_cols > 0);
+      h->auto_seg = o.seg_cols == 0;
       const size_t slots = (size_t)z.nthin1 * (size_t)h->tslots, cb = sizeof(int32_t) * slots;
       void *tc = mem.get(cb + dtype_size(h->vdt) * slots);
       if (tc) {
@@ -1080,14 +1081,49 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
       start[it] = at;
       if ((it + 1) % (size_t)g.wpc == 0) at += (int64_t)B->C * s.cols[it];
     }
+    // a matrix with thin segments brings its own cuts, its dense segments joined
+    // to the batch's width (with a width that the caller gave they are as wide as
+    // that, which is not meant for the batch). us cut at S only / slices wider than
+    // S cut so / all: 64 power-law matrices of up to 200,000 rows, sigma = 200, C = 32
+    // 303 / 180 / 131; sigma = 1024, C = 16, 32, 64 163, 237, 383 / 109, 118, 144 /
+    // 107, 103, 112; sigma = n 107, 111, 144 / 103, 106, 111 / 100, 105, 113
+    std::vector<uint8_t> cut(s.cols.size(), 0);
+    if (hs[b]->tcol && hs[b]->auto_seg) {
+      std::vector<sell::Unit1> seg((size_t)hs[b]->nsegs1);
+      SELL_HIP(hipMemcpy(seg.data(), hs[b]->units1, sizeof(sell::Unit1) * seg.size(), hipMemcpyDeviceToHost));
+      std::sort(seg.begin(), seg.end(),
+                [](const sell::Unit1 &p, const sell::Unit1 &q) { return p.part < q.part; });
+      for (size_t i = 0; i < seg.size();) {
+        const size_t e = i + (size_t)seg[i].nseg;
+        const size_t it = (size_t)seg[i].item;
+        if (seg[e - 1].rows == 0 && seg[e - 1].je <= S) {  // one segment: a whole chunk below
+          i = e;
+          continue;
+        }
+        cut[it] = 1;
+        splits.push_back({b, (int32_t)it, 0, 0, off});
+        for (; i < e; off += g.rpw) {
+          sell::Unit1 u = seg[i++];
+          while (u.rows == 0 && i < e && seg[i].rows == 0 && seg[i].je - u.jb <= S) u.je = seg[i++].je;
+          ++splits.back().nseg;
+          all.push_back({b, u.item, u.jb, u.je, start[it], off, u.rows, u.thin, 0});
+          const int n = __builtin_popcountll(u.rows);
+          const int step = n == 0 ? g.T : n > 4 ? 8 : n > 2 ? 16 : n > 1 ? 32 : 64;
+          umat.push_back(b);
+          ucost.push_back((u.je - u.jb + step - 1) / step + kFixed);
+          usplit.push_back(1);
+        }
+      }
+    }
     for (size_t it = 0; it < s.cols.size(); ++it) {
       const int32_t w = s.cols[it];
-      if (w <= S) continue;
+      if (w <= S || cut[it]) continue;
+      cut[it] = 1;
       const int32_t nseg = (w + S - 1) / S;
       splits.push_back({b, (int32_t)it, nseg, 0, off});
       for (int32_t q = 0; q < nseg; ++q, off += g.rpw) {
         const int64_t cols = std::min<int64_t>(S, (int64_t)w - (int64_t)q * S);
-        all.push_back({b, (int32_t)it, q * S, (int32_t)(q * S + cols), start[it], off});
+        all.push_back({b, (int32_t)it, q * S, (int32_t)(q * S + cols), start[it], off, 0, 0, 0});
         umat.push_back(b);
         ucost.push_back((cols + g.T - 1) / g.T + kFixed);
         usplit.push_back(1);
@@ -1100,14 +1136,14 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
     const int32_t wmax = (int32_t)grp;
     for (size_t it = 0; it < s.cols.size(); ++it) {
       const int32_t w = s.cols[it];
-      if (w > S) continue;
+      if (cut[it]) continue;
       if (grp && w <= wmax && it + grp <= s.cols.size()) {
         size_t e = it + 1;
         while (e < it + grp && s.cols[e] <= wmax) ++e;
         if (e == it + grp) {
           uint32_t widths = 0;
           for (size_t q = 0; q < grp; ++q) widths |= (uint32_t)s.cols[it + q] << (4 * q);
-          all.push_back({b, (int32_t)it, -1, (int32_t)widths, start[it], -1});
+          all.push_back({b, (int32_t)it, -1, (int32_t)widths, start[it], -1, 0, 0, 0});
           umat.push_back(b);
           ucost.push_back(1 + kFixed);
           usplit.push_back(0);
@@ -1115,7 +1151,7 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
           continue;
         }
       }
-      all.push_back({b, (int32_t)it, 0, w, start[it], -1});
+      all.push_back({b, (int32_t)it, 0, w, start[it], -1, 0, 0, 0});
       umat.push_back(b);
       ucost.push_back((w + g.T - 1) / g.T + kFixed);
       usplit.push_back(0);
@@ -1140,7 +1176,7 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
                                             sell::kXcds, nwaves);
   std::vector<sell::BUnit> units(plan.order.size());
   for (size_t i = 0; i < plan.order.size(); ++i)
-    units[i] = plan.order[i] < 0 ? sell::BUnit{-1, 0, 0, 0, 0, -1} : all[(size_t)plan.order[i]];
+    units[i] = plan.order[i] < 0 ? sell::BUnit{-1, 0, 0, 0, 0, -1, 0, 0, 0} : all[(size_t)plan.order[i]];
   B->nunits = (int64_t)units.size();
   if (B->nunits >= ((int64_t)1 << 31)) return fail(SELL_ERR_UNSUPPORTED, "sell_batch_create: too many work units");
   std::vector<int32_t> slice = plan.slice;
@@ -1172,6 +1208,9 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
     m.x = nullptr;
     m.y = nullptr;
     m.nrows = hs[b]->nrows;
+    m.tcol = hs[b]->tcol;
+    m.tval = hs[b]->tval;
+    m.tslots = hs[b]->tslots;
   }
 
   // capture the batched launch once

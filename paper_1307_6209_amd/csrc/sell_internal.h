@@ -62,13 +62,17 @@ struct UnitCol {
 // to y (part < 0) or to partial[part ...]; jb < 0: a group of short chunks from
 // item on, the width of its q-th chunk in bits 4q of je. With all of it here a
 // wave goes from its unit to the slots, not over the chunk's width and start (64
-// power-law matrices, sigma = 200: 327 us so, now 319; sigma = n: the same).
+// power-law matrices, sigma = 200, before thin segments: 327 us so, 319 from the
+// unit; sigma = n: the same).
 struct BUnit {
   int32_t mat;
   int32_t item;
   int32_t jb, je;
   int64_t off;
   int64_t part;
+  uint64_t rows;  // thin segment: its rows, and its number among the matrix's
+  int32_t thin;
+  int32_t pad;
 };
 
 // Geometry of a chunk height on a 64-lane wavefront whose lanes each hold
@@ -260,6 +264,9 @@ struct BatchMat {
   const void *x;
   void *y;
   int64_t nrows;
+  const int32_t *tcol;  // thin segments' copies
+  const void *tval;
+  int64_t tslots;
 };
 
 // Split row slice of the batched kernel.
@@ -485,6 +492,7 @@ struct sell_matrix {
   int32_t *tcol = nullptr;  // thin segments' copies of their slots
   void *tval = nullptr;
   int64_t tslots = 0;
+  bool auto_seg = false;    // segment widths chosen here, not by the caller
   int64_t nsplit1 = 0, nsegs1 = 0;
   int64_t nsplit = 0;
   int64_t nsegs = 0;                  // total segments of split items

@@ -27,7 +27,7 @@
 // cross-wave synchronisation (with its cache write-back and invalidation) is
 // needed inside the product kernel. The single-vector product has segments of
 // its own (Unit1), finer and cut where few rows of a slice are left; the block
-// form and the batch use seg_cols columns throughout.
+// form uses seg_cols columns throughout; the batch takes the thin segments.
 #pragma once
 
 #include "sell_internal.h"
@@ -144,8 +144,8 @@ __device__ __forceinline__ void opaque(T &v) {
 
 // y of the row at sorted position p. Permuted rows are stored one by one, several
 // to a line: the L2 gathers a line's rows (64 power-law matrices, sigma = n,
-// C = 32: 111 us with streaming stores, which leave half of the writes to memory
-// partial, 107; 200k, sigma = n 13.1 / 12.0; 50k, sigma = 1024 10.8 / 10.1). Not
+// C = 32, before thin segments: 111 us with streaming stores, which leave half of
+// the writes to memory partial, 107 so; 200k, sigma = n 13.1 / 12.0; 50k, sigma = 1024 10.8 / 10.1). Not
 // where y alone would fill the L2s and turn x out: 2M, sigma = 2^14 119 / 121.
 template <typename A>
 __device__ __forceinline__ void put_row(A *y, const int32_t *__restrict__ perm, int64_t p, int64_t nrows, A v) {
@@ -741,6 +741,18 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) k_batch(BatchArgs a) {
           if (q < g) base += ((uint32_t)u.je >> 4 * q & 15u) * C;
         spmv_group<COMBO, C>(m.val, m.col, base, (int)((uint32_t)u.je >> 4 * g & 15u), m.perm, m.x, m.y, m.nrows,
                              (int64_t)u.item * C + lane);
+        continue;
+      }
+    }
+    if constexpr (C >= 16) {
+      if (u.rows != 0) {
+        SpmvArgs t{};
+        t.x = m.x;
+        t.tcol = m.tcol;
+        t.tval = m.tval;
+        t.tslots = m.tslots;
+        t.partial = static_cast<typename Types<COMBO>::A *>(a.partial) + u.part;
+        spmv_thin<COMBO, C>(t, Unit1{u.item, 0, u.jb, u.je, 0, u.thin, u.rows}, lane);
         continue;
       }
     }

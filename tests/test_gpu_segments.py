@@ -98,3 +98,39 @@ def test_thin_segments_without_copies(C):
         break
     assert h.info["device_bytes"] < full.info["device_bytes"]
     assert np.array_equal(spmv_gpu(h, x), ref)
+
+
+@pytest.mark.parametrize("persistent", [False, True])
+@pytest.mark.parametrize("C", [16, 32, 64, 128])
+def test_batch_thin_segments(C, persistent):
+    """The batch with matrices that bring thin segments, one without copies of
+    them, one of a given segment width and one that is not split."""
+    import torch
+
+    from gpu_util import batch_chain_per_row
+    from paper_1307_6209_amd import sellcs
+
+    mats = []
+    for b in range(6):
+        lens = [1 + b % 3] * (5 * C + 3 * b)
+        for r, w in enumerate([40, 33, 0, 97, 300, 65, 5000, 129, 34, 64, 45, 2]):
+            lens[(r * (7 + 5 * b)) % len(lens)] = w if b != 3 else 5
+        mats.append(lengths_crs(lens, 6000 + b, 101 + b))
+    hs = [build(A, C, s) for A, s in zip(mats[:4], (1, 64, mats[2].nrows, 1))]
+    hs.append(build(mats[4], C, 1, seg_cols=128))
+    for n in range(64):
+        try:
+            hs.append(build(mats[5], C, 1, xwindow=-1, allocator=sellcs.TorchAllocator(fail_after=n)))
+        except sellcs.SellError:
+            continue
+        break
+    make = sellcs.sell_batch_create_persistent if persistent else sellcs.sell_batch_create
+    xs = [synth.uniform(A.ncols, 111 + b) for b, A in enumerate(mats)]
+    xd = [torch.from_numpy(x).cuda() for x in xs]
+    yd = [torch.full((A.nrows,), float("nan"), dtype=torch.float64, device="cuda") for A in mats]
+    b = make(hs)
+    sellcs.sell_batch_spmv(b, sellcs.BatchVectors(b, xd, yd))
+    torch.cuda.synchronize()
+    for A, h, x, y in zip(mats, hs, xs, yd):
+        say("batch thin C", C, "rows", A.nrows)
+        check_fp64(A, y.cpu().numpy(), x, m=batch_chain_per_row(A, h, C))
