@@ -200,10 +200,10 @@ struct ItemCols {
   int32_t max = 0;
 };
 
-ItemCols item_cols(const std::vector<int32_t> &cl, const Geom &g) {
+ItemCols item_cols(const int32_t *cl, int64_t nchunks, const Geom &g) {
   ItemCols r;
-  r.cols.resize(cl.size() * (size_t)g.wpc);
-  for (size_t c = 0; c < cl.size(); ++c) {
+  r.cols.resize((size_t)nchunks * (size_t)g.wpc);
+  for (size_t c = 0; c < (size_t)nchunks; ++c) {
     for (int h = 0; h < g.wpc; ++h) r.cols[c * g.wpc + h] = cl[c];
     r.total_steps += (int64_t)((cl[c] + g.T - 1) / g.T) * g.wpc;
     r.max = std::max(r.max, cl[c]);
@@ -246,14 +246,41 @@ int xw_block_width(const sell_matrix *h, int64_t maxwin, int64_t maxseg, int64_t
   return 0;
 }
 
-// The handle's chunk widths on the host, copied on the first call.
-hipError_t host_widths(sell_matrix *h) {
-  std::lock_guard<std::mutex> lock(h->cl_mu);
-  if ((int64_t)h->h_cl.size() == h->nchunks) return hipSuccess;
-  std::vector<int32_t> v((size_t)h->nchunks);
-  const hipError_t e = hipMemcpy(v.data(), h->cl, sizeof(int32_t) * v.size(), hipMemcpyDeviceToHost);
-  if (e == hipSuccess) h->h_cl.swap(v);
-  return e;
+// What a batch plans with, on the host: of each handle its chunk widths and, where
+// it has thin segments of automatic widths, its segments. Gathered on the device,
+// so that the host waits for one copy (64 matrices, sell_batch_create: two copies
+// each 2.9 ms, so 1.5).
+struct HostPlan {
+  std::vector<char> data;
+  std::vector<size_t> widths, segs;  // each handle's offsets in data; no segments: 0
+  const int32_t *cl(size_t b) const { return reinterpret_cast<const int32_t *>(data.data() + widths[b]); }
+  const sell::Unit1 *seg(size_t b) const { return reinterpret_cast<const sell::Unit1 *>(data.data() + segs[b]); }
+};
+
+hipError_t host_plan(const sell_handle *hs, int32_t count, HostPlan *p) {
+  size_t n = 64;
+  for (int32_t b = 0; b < count; ++b) {
+    const bool own = hs[b]->tcol && hs[b]->auto_seg;
+    p->segs.push_back(own ? n : 0);
+    if (own) n += sizeof(sell::Unit1) * (size_t)hs[b]->nsegs1;
+    p->widths.push_back(n);
+    n += (sizeof(int32_t) * (size_t)hs[b]->nchunks + 63) / 64 * 64;
+  }
+  p->data.resize(n);
+  char *d = nullptr;
+  hipError_t e = hipMalloc(reinterpret_cast<void **>(&d), n);
+  if (e != hipSuccess) return e;
+  for (int32_t b = 0; b < count && e == hipSuccess; ++b) {
+    if (p->segs[(size_t)b])
+      e = hipMemcpyAsync(d + p->segs[(size_t)b], hs[b]->units1, sizeof(sell::Unit1) * (size_t)hs[b]->nsegs1,
+                         hipMemcpyDeviceToDevice, nullptr);
+    if (e == hipSuccess && hs[b]->nchunks > 0)
+      e = hipMemcpyAsync(d + p->widths[(size_t)b], hs[b]->cl, sizeof(int32_t) * (size_t)hs[b]->nchunks,
+                         hipMemcpyDeviceToDevice, nullptr);
+  }
+  if (e == hipSuccess) e = hipMemcpy(p->data.data(), d, n, hipMemcpyDeviceToHost);
+  const hipError_t f = hipFree(d);
+  return e != hipSuccess ? e : f;
 }
 
 }  // namespace
@@ -765,8 +792,10 @@ sell_status spmmv_run(sell_handle h, const void *X, void *Y, int32_t k, void *st
                                           " bytes of scratch, more than its " + std::to_string(scratch_bytes));
   };
   if (k == 1) {
-    // (with an automatic split width a plan has at most two segments per
-    // resident wave and split slice: well below the scratch)
+    // (an automatic width splits slices of more than a (2 CUs * 32)-th of all
+    // steps, so no more than that many, into that many full segments and at most
+    // three shorter ones a slice: 256 CUs, 65,536 segments of 64 rows, 32 MiB. A
+    // given width makes as many segments as the block form's plan has.)
     const int64_t doubles = h->nsegs1 * (int64_t)h->g.rpw;
     if (scratch && doubles * (int64_t)sizeof(double) > (int64_t)scratch_bytes) return too_big(doubles);
     return spmv_run(h, X, Y, stream, scratch, who);
@@ -1055,11 +1084,17 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
   const Geom &g = B->g;
 
   // work of every matrix, one segment width for the whole batch
+  HostPlan plan_in;
+  const hipError_t pe = host_plan(hs, count, &plan_in);
+  if (pe == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    return fail(SELL_ERR_OOM, "sell_batch_create: allocation failed");
+  }
+  SELL_HIP(pe);
   std::vector<ItemCols> st(count);
   int64_t total = 0;
   for (int32_t b = 0; b < count; ++b) {
-    SELL_HIP(host_widths(hs[b]));
-    st[b] = item_cols(hs[b]->h_cl, g);
+    st[b] = item_cols(plan_in.cl((size_t)b), hs[b]->nchunks, g);
     total += st[b].total_steps;
   }
   DeviceInfo di = device_info();
@@ -1088,9 +1123,8 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
     // 303 / 180 / 131; sigma = 1024, C = 16, 32, 64 163, 237, 383 / 109, 118, 144 /
     // 107, 103, 112; sigma = n 107, 111, 144 / 103, 106, 111 / 100, 105, 113
     std::vector<uint8_t> cut(s.cols.size(), 0);
-    if (hs[b]->tcol && hs[b]->auto_seg) {
-      std::vector<sell::Unit1> seg((size_t)hs[b]->nsegs1);
-      SELL_HIP(hipMemcpy(seg.data(), hs[b]->units1, sizeof(sell::Unit1) * seg.size(), hipMemcpyDeviceToHost));
+    if (plan_in.segs[(size_t)b]) {
+      std::vector<sell::Unit1> seg(plan_in.seg((size_t)b), plan_in.seg((size_t)b) + hs[b]->nsegs1);
       std::sort(seg.begin(), seg.end(),
                 [](const sell::Unit1 &p, const sell::Unit1 &q) { return p.part < q.part; });
       for (size_t i = 0; i < seg.size();) {

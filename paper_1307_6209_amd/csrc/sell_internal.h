@@ -508,8 +508,6 @@ struct sell_matrix {
   int32_t xw_gc = 0;            // chunks per window group
   int32_t xw_block = 0;         // block form: right-hand sides staged at a time, at most (0: none)
 
-  std::mutex cl_mu;
-  std::vector<int32_t> h_cl;    // host copy of the chunk widths, made when a batch is first planned with them
 
   sell_allocator alloc{};
   bool custom_alloc = false;
