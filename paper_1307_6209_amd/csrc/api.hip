@@ -111,6 +111,12 @@ size_t cache_limit() {
   return limit;
 }
 
+// Plain device memory. Where there is none, the kept blocks are given up for it.
+void *plain_alloc(size_t bytes) {
+  void *p = raw_alloc(bytes);
+  return p || !block_cache().flush(current_device()) ? p : raw_alloc(bytes);
+}
+
 // Device memory through the caller's allocator, from the block cache, or (kept
 // false) plain. Blocks are put back idle.
 struct Mem {
@@ -119,8 +125,11 @@ struct Mem {
   bool kept = true;
   void *get(size_t bytes) {
     if (bytes == 0) bytes = 256;
-    if (custom) return alloc.alloc(bytes, alloc.ctx);
-    return kept ? block_cache().get(current_device(), bytes, cache_limit()) : raw_alloc(bytes);
+    if (custom) {
+      void *p = alloc.alloc(bytes, alloc.ctx);
+      return p || !block_cache().flush(current_device()) ? p : alloc.alloc(bytes, alloc.ctx);
+    }
+    return kept ? block_cache().get(current_device(), bytes, cache_limit()) : plain_alloc(bytes);
   }
   void put(void *p) {
     if (!p) return;
@@ -267,9 +276,9 @@ hipError_t host_plan(const sell_handle *hs, int32_t count, HostPlan *p) {
     n += (sizeof(int32_t) * (size_t)hs[b]->nchunks + 63) / 64 * 64;
   }
   p->data.resize(n);
-  char *d = nullptr;
-  hipError_t e = hipMalloc(reinterpret_cast<void **>(&d), n);
-  if (e != hipSuccess) return e;
+  char *d = static_cast<char *>(plain_alloc(n));
+  if (!d) return hipErrorOutOfMemory;
+  hipError_t e = hipSuccess;
   for (int32_t b = 0; b < count && e == hipSuccess; ++b) {
     if (p->segs[(size_t)b])
       e = hipMemcpyAsync(d + p->segs[(size_t)b], hs[b]->units1, sizeof(sell::Unit1) * (size_t)hs[b]->nsegs1,
@@ -1040,12 +1049,8 @@ void batch_free(sell_batch_s *b) {
 }
 
 void *batch_alloc(sell_batch_s *b, size_t bytes) {
-  void *p = nullptr;
-  if (hipMalloc(&p, bytes ? bytes : 256) != hipSuccess) {
-    (void)hipGetLastError();
-    return nullptr;
-  }
-  b->owned.push_back(p);
+  void *p = plain_alloc(bytes ? bytes : 256);
+  if (p) b->owned.push_back(p);
   return p;
 }
 
@@ -1086,10 +1091,7 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
   // work of every matrix, one segment width for the whole batch
   HostPlan plan_in;
   const hipError_t pe = host_plan(hs, count, &plan_in);
-  if (pe == hipErrorOutOfMemory) {
-    (void)hipGetLastError();
-    return fail(SELL_ERR_OOM, "sell_batch_create: allocation failed");
-  }
+  if (pe == hipErrorOutOfMemory) return fail(SELL_ERR_OOM, "sell_batch_create: allocation failed");
   SELL_HIP(pe);
   std::vector<ItemCols> st(count);
   int64_t total = 0;

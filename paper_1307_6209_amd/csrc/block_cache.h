@@ -112,8 +112,8 @@ class BlockCache {
     for (void *q : gone) free_(q);
   }
 
-  // Frees the kept blocks of a device, or of all (-1).
-  void flush(int device = -1) {
+  // Frees the kept blocks of a device, or of all (-1); false: there were none.
+  bool flush(int device = -1) {
     std::vector<void *> gone;
     {
       std::lock_guard<std::mutex> lock(mu_);
@@ -123,6 +123,7 @@ class BlockCache {
       }
     }
     for (void *q : gone) free_(q);
+    return !gone.empty();
   }
 
  private:
