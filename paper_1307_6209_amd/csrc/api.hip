@@ -117,8 +117,15 @@ void *plain_alloc(size_t bytes) {
   return p || !block_cache().flush(current_device()) ? p : raw_alloc(bytes);
 }
 
+// Whether a wait for the device succeeded; an error of it is not left behind for
+// the next launch to report.
+bool waited(hipError_t e) {
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e == hipSuccess;
+}
+
 // Device memory through the caller's allocator, from the block cache, or (kept
-// false) plain. Blocks are put back idle.
+// false) plain.
 struct Mem {
   sell_allocator alloc{};
   bool custom = false;
@@ -131,10 +138,11 @@ struct Mem {
     }
     return kept ? block_cache().get(current_device(), bytes, cache_limit()) : plain_alloc(bytes);
   }
-  void put(void *p) {
+  // idle: a wait for all work on p succeeded
+  void put(void *p, bool idle) {
     if (!p) return;
     if (custom) alloc.free(p, alloc.ctx);
-    else if (kept) block_cache().put(current_device(), p, cache_limit());
+    else if (kept) block_cache().put(current_device(), p, cache_limit(), idle);
     else raw_free(p);
   }
 };
@@ -161,8 +169,9 @@ struct Temp {
   // p is no longer released here
   void release(void *p) { ptrs.erase(std::remove(ptrs.begin(), ptrs.end(), p), ptrs.end()); }
   ~Temp() {
-    if (!idle && !ptrs.empty()) (void)hipStreamSynchronize(stream);
-    for (void *p : ptrs) mem.put(p);
+    if (ptrs.empty()) return;
+    const bool ok = idle || waited(hipStreamSynchronize(stream));
+    for (void *p : ptrs) mem.put(p, ok);
   }
 };
 
@@ -193,11 +202,11 @@ void *owned_alloc(sell_matrix *h, const Mem &mem, size_t bytes) {
   return p;
 }
 
-void free_owned(sell_matrix *h) {
+void free_owned(sell_matrix *h, bool idle) {
   Mem m;
   m.alloc = h->alloc;
   m.custom = h->custom_alloc;
-  for (auto &pr : h->owned) m.put(pr.first);
+  for (auto &pr : h->owned) m.put(pr.first, idle);
   h->owned.clear();
 }
 
@@ -370,8 +379,7 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
     bool armed = true;
     ~Guard() {
       if (!armed || !h) return;
-      (void)hipStreamSynchronize(s);  // kernels may still use what is freed
-      free_owned(h);
+      free_owned(h, waited(hipStreamSynchronize(s)));  // kernels may still use what is freed
     }
   } guard{h.get(), s};
 
@@ -1011,8 +1019,7 @@ extern "C" sell_status sell_destroy(sell_handle h) {
     block_cache().flush();
     return SELL_OK;
   }
-  (void)hipDeviceSynchronize();
-  free_owned(h);
+  free_owned(h, waited(hipDeviceSynchronize()));
   delete h;
   return SELL_OK;
 }

@@ -11,9 +11,11 @@
 //   - a block that kKeep constructions in a row did not use is freed;
 //   - when an allocation fails, every kept block of that device is freed and
 //     the allocation tried again; flush() frees them all on request.
-// A block must be idle when it is given back (the callers synchronise first),
-// so whoever takes it next may use it on any stream. A block serves the device
-// it was taken on only.
+// Only a block that is idle is kept, so whoever takes it next may use it on any
+// stream: the callers wait for the device first and say whether that succeeded.
+// After a wait that was refused (a stream under capture, an earlier error) the
+// block is freed, which leaves the waiting to the runtime. A block serves the
+// device it was taken on only.
 #pragma once
 
 #include <cstddef>
@@ -76,8 +78,8 @@ class BlockCache {
     return p;
   }
 
-  // Gives p (from get, idle) back. device: the current one.
-  void put(int device, void *p, size_t limit) {
+  // Gives p (from get) back. device: the current one; idle: nothing uses p any more.
+  void put(int device, void *p, size_t limit, bool idle = true) {
     if (!p) return;
     std::vector<void *> gone;
     {
@@ -86,7 +88,7 @@ class BlockCache {
       if (it == used_.end()) return;
       Block b = it->second;
       used_.erase(it);
-      if (b.device != device || b.bytes > limit) {
+      if (!idle || b.device != device || b.bytes > limit) {
         gone.push_back(p);
       } else {
         b.since = epoch_;
