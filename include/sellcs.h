@@ -284,7 +284,7 @@ sell_status sell_export_xwindow(sell_handle h, int64_t *segoff, int32_t *seg, ui
 /* sell_destroy -- release the handle and its device memory (synchronises
  * the device first). Memory that the library allocated itself (no alloc in the
  * build options) is kept for later sell_build calls, up to 1/64 of the device's
- * memory; blocks that 256 builds in a row do not use are freed, and all of a
+ * memory and 4096 blocks; blocks that 256 builds in a row do not use are freed, and all of a
  * device's when an allocation of the library fails. NULL is accepted: no handle,
  * and every kept block is freed. */
 sell_status sell_destroy(sell_handle h);
