@@ -148,7 +148,8 @@ typedef struct {
   int64_t nsplit;        /* row slices wider than seg_cols */
   int32_t has_perm;      /* 0 when the row order is the identity (sigma == 1) */
   int32_t permuted_columns; /* 1 when built with permute_columns */
-  int64_t device_bytes;  /* device memory held by the handle */
+  int64_t device_bytes;  /* device memory held by the handle: its blocks as allocated (the library
+                            takes them up to a sixteenth larger than what they hold) */
   int32_t xwindow;       /* 1 when sell_spmv stages x windows in LDS */
   int32_t xwindow_max;   /* largest window, in x elements */
   int64_t xsegments;     /* runs of consecutive columns over all windows */

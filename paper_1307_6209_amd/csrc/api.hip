@@ -130,13 +130,15 @@ struct Mem {
   sell_allocator alloc{};
   bool custom = false;
   bool kept = true;
-  void *get(size_t bytes) {
+  // *got: what the block holds, at least `bytes` (the caller's blocks: as asked for)
+  void *get(size_t bytes, size_t *got = nullptr) {
     if (bytes == 0) bytes = 256;
+    if (got) *got = bytes;
     if (custom) {
       void *p = alloc.alloc(bytes, alloc.ctx);
       return p || !block_cache().flush(current_device()) ? p : alloc.alloc(bytes, alloc.ctx);
     }
-    return kept ? block_cache().get(current_device(), bytes, cache_limit()) : plain_alloc(bytes);
+    return kept ? block_cache().get(current_device(), bytes, cache_limit(), got) : plain_alloc(bytes);
   }
   // idle: a wait for all work on p succeeded
   void put(void *p, bool idle) {
@@ -161,8 +163,8 @@ struct Temp {
   bool idle = false;
   std::vector<void *> ptrs;
   Temp(const Mem &m, hipStream_t s) : mem(m), stream(s) {}
-  void *get(size_t bytes) {
-    void *p = mem.get(bytes);
+  void *get(size_t bytes, size_t *got = nullptr) {
+    void *p = mem.get(bytes, got);
     if (p) ptrs.push_back(p);
     return p;
   }
@@ -189,16 +191,17 @@ struct EventPair {
   }
 };
 
-// Makes p (bytes of device memory) the handle's.
+// Makes p (a block of `bytes` bytes) the handle's.
 void own(sell_matrix *h, void *p, size_t bytes) {
   h->owned.push_back({p, bytes});
-  h->device_bytes += (int64_t)(bytes ? bytes : 256);
+  h->device_bytes += (int64_t)bytes;
 }
 
 void *owned_alloc(sell_matrix *h, const Mem &mem, size_t bytes) {
   Mem m = mem;
-  void *p = m.get(bytes);
-  if (p) own(h, p, bytes);
+  size_t got = 0;
+  void *p = m.get(bytes, &got);
+  if (p) own(h, p, got);
   return p;
 }
 
@@ -544,9 +547,8 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
       h->tslots = sell::thin_slots(S1, o.seg_cols > 0);
       h->auto_seg = o.seg_cols == 0;
       const size_t slots = (size_t)z.nthin1 * (size_t)h->tslots, cb = sizeof(int32_t) * slots;
-      void *tc = mem.get(cb + dtype_size(h->vdt) * slots);
+      void *tc = owned_alloc(h.get(), mem, cb + dtype_size(h->vdt) * slots);
       if (tc) {
-        own(h.get(), tc, cb + dtype_size(h->vdt) * slots);
         h->tcol = static_cast<int32_t *>(tc);
         h->tval = static_cast<char *>(tc) + cb;
         SELL_HIP(sell::build_thin(h->units1, z.nsegs1, C, h->cs, h->col, h->val, (int)dtype_size(h->vdt), h->tslots,
@@ -608,7 +610,8 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
       // the one-pass construction writes the positions before it is known
       // whether the windows fit; without room for them there are two passes
       const size_t lcol_bytes = sizeof(uint16_t) * (size_t)h->padded;
-      uint16_t *lcol = static_cast<uint16_t *>(tmp.get(lcol_bytes));
+      size_t lcol_got = 0;
+      uint16_t *lcol = static_cast<uint16_t *>(tmp.get(lcol_bytes, &lcol_got));
       bool packed = false;  // xs describes tables that build_xw_fast left
       auto read_back = [&]() -> hipError_t {
         hipError_t e = sell::build_scan(cnt, offs, ngroups + 1, stmp, s);
@@ -651,10 +654,10 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
       } else {
         h->xsegoff = static_cast<int64_t *>(owned_alloc(h.get(), mem, sizeof(int64_t) * (size_t)(ngroups + 1)));
         h->xseg = static_cast<int32_t *>(owned_alloc(h.get(), mem, sizeof(int32_t) * 3 * (size_t)xs.nseg));
-        if (!lcol) lcol = static_cast<uint16_t *>(tmp.get(lcol_bytes));
+        if (!lcol) lcol = static_cast<uint16_t *>(tmp.get(lcol_bytes, &lcol_got));
         if (!h->xsegoff || !h->xseg || !lcol) return fail(SELL_ERR_OOM, "sell_build: x window arrays");
         tmp.release(lcol);
-        own(h.get(), lcol, lcol_bytes);
+        own(h.get(), lcol, lcol_got);
         h->lcol = lcol;
         SELL_HIP(hipMemcpyAsync(h->xsegoff, offs, sizeof(int64_t) * (size_t)(ngroups + 1), hipMemcpyDeviceToDevice,
                                 s));

@@ -44,24 +44,27 @@ class BlockCache {
   static constexpr size_t kMaxBlocks = 16 * kKeep;  // a construction takes about 15
 
   // Sizes within a sixteenth of each other share a size, so that matrices of
-  // about the same size reuse each other's blocks.
+  // about the same size reuse each other's blocks. A block serves its own size
+  // only: what a matrix holds follows from its layout, not from what was kept.
   static size_t rounded(size_t bytes) {
     size_t step = 512;
     while (step * 32 <= bytes) step *= 2;
     return (bytes + step - 1) / step * step;
   }
 
-  // A block of at least `bytes` bytes on `device`, which is the current one.
-  void *get(int device, size_t bytes, size_t limit) {
+  // A block of at least `bytes` bytes on `device`, which is the current one; *got
+  // (if asked for): its size.
+  void *get(int device, size_t bytes, size_t limit, size_t *got = nullptr) {
     const size_t need = bytes <= limit ? rounded(bytes) : bytes;
+    if (got) *got = need;
     {
       std::lock_guard<std::mutex> lock(mu_);
-      for (auto it = sizes_.lower_bound({device, need});
-           it != sizes_.end() && it->first.first == device && it->first.second <= need + need / 8; ++it)
-        if (Block *b = it->second) {
-          unlink(b);
-          return b->p;
-        }
+      const auto it = sizes_.find({device, need});
+      if (it != sizes_.end() && it->second) {
+        Block *b = it->second;
+        unlink(b);
+        return b->p;
+      }
     }
     size_t size = need;
     void *p = alloc_(size);
@@ -69,6 +72,7 @@ class BlockCache {
       flush(device);
       size = bytes;
       p = alloc_(size);
+      if (got) *got = size;
     }
     if (!p) return nullptr;
     try {
