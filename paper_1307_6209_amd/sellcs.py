@@ -375,8 +375,13 @@ def sell_crs_spmv(rpt, col, val, x, y, ncols: int, lanes_per_row: int = 0, strea
     return y
 
 
-def sell_destroy(h: SellMatrix):
-    h.close()
+def sell_destroy(h: SellMatrix | None):
+    """Release a matrix. None: no matrix, but the device memory that the library
+    keeps of released ones for later builds is freed."""
+    if h is None:
+        _check(lib().sell_destroy(None), "sell_destroy")
+    else:
+        h.close()
 
 
 class SellBatch:
