@@ -101,8 +101,9 @@ int current_device() {
   return dev;
 }
 
-// Most bytes kept for later constructions: 1/64 of the device's memory.
-size_t cache_limit() {
+// 1/64 of the device's memory: the most that is kept for later constructions, and
+// the most that a matrix takes for the copies of its thin segments.
+size_t memory_share() {
   static const size_t limit = [] {
     size_t free_bytes = 0, total = 0;
     if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) total = 0;
@@ -138,13 +139,13 @@ struct Mem {
       void *p = alloc.alloc(bytes, alloc.ctx);
       return p || !block_cache().flush(current_device()) ? p : alloc.alloc(bytes, alloc.ctx);
     }
-    return kept ? block_cache().get(current_device(), bytes, cache_limit(), got) : plain_alloc(bytes);
+    return kept ? block_cache().get(current_device(), bytes, memory_share(), got) : plain_alloc(bytes);
   }
   // idle: a wait for all work on p succeeded
   void put(void *p, bool idle) {
     if (!p) return;
     if (custom) alloc.free(p, alloc.ctx);
-    else if (kept) block_cache().put(current_device(), p, cache_limit(), idle);
+    else if (kept) block_cache().put(current_device(), p, memory_share(), idle);
     else raw_free(p);
   }
 };
@@ -542,12 +543,15 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
       SELL_HIP(sell::plan_place(pa, C, z, po, h->cs, h->col, h->ncols,
                                 reinterpret_cast<sell::UnitCol *>(segs + z.nsegs1), s));
     // the thin segments' slots once more, side by side; without room for them
-    // the product takes the slots from their places
+    // the product takes the slots from their places, as it does where the copies,
+    // which may be as large as col and val together, would crowd a card that the
+    // matrix itself still fits (the times of both are at thin_rows)
     if (z.nthin1 > 0) {
       h->tslots = sell::thin_slots(S1, o.seg_cols > 0);
       h->auto_seg = o.seg_cols == 0;
       const size_t slots = (size_t)z.nthin1 * (size_t)h->tslots, cb = sizeof(int32_t) * slots;
-      void *tc = owned_alloc(h.get(), mem, cb + dtype_size(h->vdt) * slots);
+      const size_t bytes = cb + dtype_size(h->vdt) * slots;
+      void *tc = bytes <= memory_share() ? owned_alloc(h.get(), mem, bytes) : nullptr;
       if (tc) {
         h->tcol = static_cast<int32_t *>(tc);
         h->tval = static_cast<char *>(tc) + cb;
