@@ -419,7 +419,7 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
       if (!sort_tmp) return fail(SELL_ERR_OOM, "sell_build: sort buffers");
     }
     if (!h->perm) return fail(SELL_ERR_OOM, "sell_build: perm");
-    SELL_HIP(sell::build_sort(len, n, sig, sort_tmp, h->perm, s));
+    SELL_HIP(sell::build_sort(len, &dsmall->flags, &dsmall->maxlen, n, sig, sort_tmp, h->perm, s));
   }
 
   // chunk widths and offsets

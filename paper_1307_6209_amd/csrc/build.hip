@@ -140,11 +140,10 @@ __global__ void __launch_bounds__(kBlock) k_colcheck(const int32_t *__restrict__
 // sigma > kTile: two stable counting passes over tiles of kTile rows of one
 // window, by the low byte of the length and then by the rest of it (255 for all
 // of 65,280 or more), longest first: counts per (window, digit, tile), their
-// exclusive prefix, ranks inside the tile. Rows of 65,280 entries or more, at most
-// nnz / 65,280, then stand in front of their window in the order of their low
-// byte; k_sort_longest puts them right. (Sorted tiles merged pairwise, log2(sigma
-// / kTile) passes of binary searches: 191 us on one window of 1M rows, now
-// 47.)
+// exclusive prefix, ranks inside the tile. Rows of 65,280 entries or more then
+// stand in front of their window in the order of their low byte; k_sort_longest
+// goes on with the higher ones. (Sorted tiles merged pairwise, log2(sigma /
+// kTile) passes of binary searches: 191 us on one window of 1M rows, now 47.)
 // ---------------------------------------------------------------------------
 constexpr int kTile = 4096;
 constexpr int kSortBlock = 512;
@@ -290,25 +289,89 @@ __global__ void __launch_bounds__(kSortBlock) k_sort_place(const int32_t *__rest
   }
 }
 
-// One workgroup per window: its rows of 65,280 entries or more by length and
-// row, each row's place counted among them; tmp: n int32.
-__global__ void __launch_bounds__(kBlock) k_sort_longest(const int32_t *__restrict__ len, int64_t sigma,
-                                                         int64_t per_window, const int64_t *__restrict__ places,
-                                                         int32_t *__restrict__ tmp, int32_t *__restrict__ perm) {
+// One workgroup per window: its rows of 65,280 entries or more, which stand in
+// front in the order of their low byte, by the bytes above it, one stable counting
+// pass each (the longest row says how many). A pass counts the digits, then takes
+// the rows kSortBlock at a time: a row's place is its digit's, plus the rows of the
+// digit in the turns and waves before, plus its rank in its wave. Linear in their
+// number, which is no small one where rows are dense: 1,000 take 5 us, 8,000 take 26
+// and 20,000 take 63 (before, each was counted against every other: 256,000 steps of
+// two dependent loads a thread for 8,000). Nothing to do where the row pointers are
+// malformed: any length may stand there, and no order is needed. tmp: n int32.
+__global__ void __launch_bounds__(kSortBlock) k_sort_longest(const int32_t *__restrict__ len,
+                                                             const uint32_t *__restrict__ flags,
+                                                             const int32_t *__restrict__ maxlen, int64_t sigma,
+                                                             int64_t per_window, const int64_t *__restrict__ places,
+                                                             int32_t *tmp, int32_t *perm) {
+  constexpr int WAVES = kSortBlock / 64;
+  __shared__ int32_t place[256];  // where the next row of each digit goes
+  __shared__ int32_t next[WAVES][256];
   const int64_t w0 = (int64_t)blockIdx.x * sigma;
   const int64_t m = places[((int64_t)blockIdx.x * 256 + 1) * per_window] - w0;  // rows of digit 0
-  if (m <= 1) return;
-  for (int64_t e = threadIdx.x; e < m; e += kBlock) {
-    const int32_t row = perm[w0 + e], l = len[row];
-    int64_t at = 0;
-    for (int64_t q = 0; q < m; ++q) {
-      const int32_t r2 = perm[w0 + q], l2 = len[r2];
-      at += l2 > l || (l2 == l && r2 < row);
+  if (m <= 1 || *flags != 0) return;  // uniform over the block
+  const int lane = lane_id(), v = threadIdx.x >> 6;
+  const int32_t longest = *maxlen;
+  int32_t *in = perm + w0, *out = tmp + w0;
+  for (int shift = 8; shift < 32 && longest >> shift != 0; shift += 8) {
+    if (threadIdx.x < 256) place[threadIdx.x] = 0;
+    __syncthreads();
+    for (int64_t e = threadIdx.x; e < m; e += kSortBlock) atomicAdd(&place[255 - ((len[in[e]] >> shift) & 255)], 1);
+    __syncthreads();
+    if (v == 0) {  // exclusive prefix, four digits a lane
+      int32_t c[4], sum = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        c[k] = place[4 * lane + k];
+        sum += c[k];
+      }
+      int32_t at = sum;
+      for (int off = 1; off < 64; off <<= 1) {
+        const int32_t o = __shfl_up(at, off);
+        if (lane >= off) at += o;
+      }
+      at -= sum;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        place[4 * lane + k] = at;
+        at += c[k];
+      }
     }
-    tmp[w0 + at] = row;
+    for (int64_t t0 = 0; t0 < m; t0 += kSortBlock) {
+      const bool real = t0 + threadIdx.x < m;
+      const int32_t row = real ? in[t0 + threadIdx.x] : 0;
+      const int d = real ? 255 - ((len[row] >> shift) & 255) : 0;
+      for (int q = lane; q < 256; q += 64) next[v][q] = 0;
+      unsigned long long same = __ballot(real);  // lanes with this lane's digit
+#pragma unroll
+      for (int bit = 0; bit < 8; ++bit) {
+        const unsigned long long b = __ballot((d >> bit) & 1);
+        same &= (d >> bit) & 1 ? b : ~b;
+      }
+      const int rank = __popcll(same & ((1ull << lane) - 1ull));
+      wave_sync();
+      if (real && rank == 0) next[v][d] = __popcll(same);
+      __syncthreads();
+      if (threadIdx.x < 256) {
+        int32_t at = place[threadIdx.x];
+#pragma unroll
+        for (int u = 0; u < WAVES; ++u) {
+          const int32_t c = next[u][threadIdx.x];
+          next[u][threadIdx.x] = at;
+          at += c;
+        }
+        place[threadIdx.x] = at;
+      }
+      __syncthreads();
+      if (real) out[next[v][d] + rank] = row;
+      wave_sync();
+    }
+    __syncthreads();
+    int32_t *const t = in;
+    in = out;
+    out = t;
   }
-  __syncthreads();
-  for (int64_t e = threadIdx.x; e < m; e += kBlock) perm[w0 + e] = tmp[w0 + e];
+  if (in != perm + w0)
+    for (int64_t e = threadIdx.x; e < m; e += kSortBlock) perm[w0 + e] = in[e];
 }
 
 // Chunks up to this width are never split: their few[] is not looked at.
@@ -784,7 +847,8 @@ int64_t sort_tmp_elems(int64_t n, int64_t sigma) {
   return n + counts + scan_tmp_elems(counts);
 }
 
-hipError_t build_sort(const int32_t *len, int64_t n, int64_t sigma, int64_t *tmp, int32_t *perm, hipStream_t s) {
+hipError_t build_sort(const int32_t *len, const uint32_t *flags, const int32_t *maxlen, int64_t n, int64_t sigma,
+                      int64_t *tmp, int32_t *perm, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   if (sigma > n) sigma = n;
   if (sigma <= kTile) {
@@ -805,7 +869,7 @@ hipError_t build_sort(const int32_t *len, int64_t n, int64_t sigma, int64_t *tmp
   if ((e = hipGetLastError()) != hipSuccess || (e = build_scan(counts, counts, ncounts, stmp, s)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_sort_place<1>, tiles, dim3(kSortBlock), 0, s, len, items, n, sigma, per, counts, nullptr, perm);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_sort_longest, dim3((unsigned)nwin), dim3(kBlock), 0, s, len, sigma, per, counts,
+  hipLaunchKernelGGL(k_sort_longest, dim3((unsigned)nwin), dim3(kSortBlock), 0, s, len, flags, maxlen, sigma, per, counts,
                      reinterpret_cast<int32_t *>(items), perm);
   return hipGetLastError();
 }

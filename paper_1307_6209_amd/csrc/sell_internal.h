@@ -355,9 +355,11 @@ int batch_waves_per_cu(int combo, int C, int U);
 hipError_t build_rowlen(const int64_t *rpt, int64_t n, int64_t nnz, int32_t *len, uint32_t *flags,
                         unsigned long long *sumsq, int32_t *maxlen, hipStream_t s);
 hipError_t build_colcheck(const int32_t *col, int64_t nnz, int64_t ncols, uint32_t *flags, hipStream_t s);
-// Sorted row order for sigma > 1; tmp needs sort_tmp_elems(n, sigma) int64.
+// Sorted row order for sigma > 1; tmp needs sort_tmp_elems(n, sigma) int64; flags and
+// maxlen are build_rowlen's.
 int64_t sort_tmp_elems(int64_t n, int64_t sigma);
-hipError_t build_sort(const int32_t *len, int64_t n, int64_t sigma, int64_t *tmp, int32_t *perm, hipStream_t s);
+hipError_t build_sort(const int32_t *len, const uint32_t *flags, const int32_t *maxlen, int64_t n, int64_t sigma,
+                      int64_t *tmp, int32_t *perm, hipStream_t s);
 // padded, total_steps: += the slots, the wave steps of T columns over all items
 // (wpc per chunk); max_width: the widest chunk (all zeroed by the caller). few
 // (or nullptr): per item, the lengths of its (thin_rows + 1)-th and its
