@@ -246,28 +246,6 @@ int default_vec(int C, sell_dtype v, int64_t nnz, int64_t nrows) {
   return V;
 }
 
-// The most right-hand sides that the block form stages in LDS at a time: 8, 4
-// or (0) none. Two workgroups have to fit a CU: us at one / two a CU, 27-point
-// stencil, C = 32, k = 8 at once: 96^3 (86 KB) 130, 80^3 (80 KB) 53; k_spmmv 122
-// and 77. The windows have to be worth it: each element read by 2.5 slots or
-// more, in runs of 8 or more. k_spmmv_xw against the other kernels, C = 16, 32,
-// 64, stencil 96^3: k = 4 73, 57, 62 / 140, 86, 76; k = 8 115, 90, 133 / 150, 122,
-// 151; k = 12 178, 157, 247 / 217, 196, 196; 80^3: k = 16 132, 103, 180 / 144, 143,
-// 142; k = 32 259, 201, 376 / 258, 257, 255 (in eights; in fours k = 16 takes 252
-// on 96^3, C = 32, the other kernel 226). 5-point Laplacian 1000^2 (1.7 slots per
-// element) k = 4 50, 45, 40 / 44, 29, 26; 60,000 rows of up to 40 random columns
-// of 2,000 (2.6 slots, runs of one or two) k = 8 28 / 19 at C = 16.
-int xw_block_width(const sell_matrix *h, int64_t maxwin, int64_t maxseg, int64_t runs, int64_t ngroups, int gc,
-                   size_t lds) {
-  if (h->combo != sell::COMBO_F64_F64 || h->C < 16) return 0;
-  const double elems = (double)maxwin * (double)ngroups;
-  if ((double)h->padded < 2.5 * elems || elems < 8.0 * (double)runs) return 0;
-  const sell::XwArgs w{nullptr, nullptr, nullptr, (int32_t)maxwin, gc};
-  for (int kb = 8; kb >= 4; kb /= 2)
-    if (2 * sell::spmmv_xw_lds(kb, w, (int)maxseg) <= lds) return kb;
-  return 0;
-}
-
 // What a batch plans with, on the host: of each handle its chunk widths and, where
 // it has thin segments of automatic widths, its segments. Gathered on the device,
 // so that the host waits for one copy (64 matrices, sell_batch_create: two copies
@@ -669,7 +647,8 @@ sell_status build_impl(const sell_crs *A, int32_t C, int64_t sigma, const sell_b
         else SELL_HIP(sell::build_xw_fill(h->col, h->cs, nc, gc, h->xsegoff, h->xseg, h->lcol, s));
         SELL_HIP(hipStreamSynchronize(s));
         h->xw_gc = gc;
-        h->xw_block = xw_block_width(h.get(), xs.maxwin, xs.maxseg, xs.nseg, ngroups, gc, di.lds_per_block);
+        if (h->combo == sell::COMBO_F64_F64)
+          h->xw_block = sell::block_windows(C, gc, nc, h->padded, xs.maxwin, xs.maxseg, xs.nseg, di.lds_per_block, di.cus);
         h->nxseg = xs.nseg;
         h->xwin_max = xs.maxwin;
         h->xseg_max = xs.maxseg;
@@ -826,18 +805,17 @@ sell_status spmmv_run(sell_handle h, const void *X, void *Y, int32_t k, void *st
   }
   if (h->C < 8) return fail(SELL_ERR_UNSUPPORTED, w + ": C must be >= 8 for k > 1");
   if (!scratch && h->units && k > h->kmax) return fail(SELL_ERR_INVALID_ARG, w + ": k exceeds the kmax given at build");
-  // Automatic width on a layout with x windows whose rows share them (a slot in
-  // 2.5 is new to its window, the windows lie in runs): X through LDS.
-  if (h->ktile == 0 && h->xw_block > 0) {
-    int kb = 4, turns = k <= 4 ? 1 : k <= 8 ? 2 : 4;
-    if (k > 12) kb = 8, turns = 2;
-    if (k <= (h->C == 64 ? 8 : h->xw_block == 8 ? 32 : 12)) {
+  // Automatic width on a layout with x windows whose rows share them: X through LDS.
+  if (h->ktile == 0) {
+    const sell::BlockTurns t = sell::block_turns(h->xw_block, k);
+    if (t.kb > 0) {
       const sell::XwArgs xw{h->lcol, h->xsegoff, h->xseg, h->xwin_max, h->xw_gc};
       sell::SpmvArgs a = args_of(h, X, Y);
       a.k = k;
       a.kt = k;
-      const hipError_t e = sell::launch_spmmv_xw(h->C, kb, turns, a, xw, sell::spmmv_xw_lds(kb, xw, h->xseg_max),
-                                                 static_cast<hipStream_t>(stream));
+      const hipError_t e =
+          sell::launch_spmmv_xw(h->C, t.kb, t.turns, a, xw, sell::block_window_lds(t.kb, h->xwin_max, h->xseg_max),
+                                static_cast<hipStream_t>(stream));
       if (e != hipSuccess) return hip_fail((w + " launch").c_str(), e);
       return SELL_OK;
     }

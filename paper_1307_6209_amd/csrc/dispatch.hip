@@ -133,10 +133,6 @@ hipError_t launch_spmmv_any(int C, bool local, const SpmvArgs &a, hipStream_t s)
   return hipGetLastError();
 }
 
-size_t spmmv_xw_lds(int kb, const XwArgs &w, int maxseg) {
-  return (size_t)w.wcap * (size_t)kb * sizeof(double) + sizeof(int2) * (size_t)maxseg;
-}
-
 hipError_t launch_spmmv_xw(int C, int kb, int turns, const SpmvArgs &a, const XwArgs &w, size_t lds, hipStream_t s) {
   const dim3 nb((unsigned)((a.nwork + w.gc - 1) / w.gc), (unsigned)((a.k + kb * turns - 1) / (kb * turns)));
 #define SELL_L(CC, GG, KK, HH)                                                                       \

@@ -9,6 +9,7 @@
 #include <string>
 #include <vector>
 
+#include "block_rule.h"
 #include "sellcs.h"
 
 namespace sell {
@@ -337,9 +338,8 @@ inline int spmmv_any_lanes(int C, int k, bool local) {
 }
 hipError_t launch_spmmv_any(int C, bool local, const SpmvArgs &a, hipStream_t s);
 // Block form with the x windows in LDS (C 16, 32 or 64, any k; no split chunks):
-// kb right-hand sides at a time (4 or 8), `turns` (1, 2; 4 for kb = 4) times for
-// one reading of the matrix; lds_bytes: spmmv_xw_lds.
-size_t spmmv_xw_lds(int kb, const XwArgs &w, int maxseg);
+// kb right-hand sides at a time (4 or 8), `turns` (1, 2; 4 for kb = 4) times in a
+// launch column (block_turns); lds_bytes: block_window_lds.
 hipError_t launch_spmmv_xw(int C, int kb, int turns, const SpmvArgs &a, const XwArgs &w, size_t lds_bytes,
                            hipStream_t s);
 // Product with the x window staged in LDS (C in 8..64, V 1 or 2, no split
@@ -508,8 +508,7 @@ struct sell_matrix {
   int32_t xwin_max = 0;         // largest window, in x elements
   int32_t xseg_max = 0;         // most segments of one window
   int32_t xw_gc = 0;            // chunks per window group
-  int32_t xw_block = 0;         // block form: right-hand sides staged at a time, at most (0: none)
-
+  sell::BlockWindows xw_block;  // the windows, where the block form may use them
 
   sell_allocator alloc{};
   bool custom_alloc = false;

@@ -1242,23 +1242,24 @@ __device__ __forceinline__ double from_lane(double v, int q, int lane) {
 
 // Block form on layouts with x windows (FP64): workgroup g (GC waves, one chunk
 // each) stages its window of X in LDS, KB right-hand sides at a time, H times
-// over, and every slot finds its row of X by its 16-bit window position; the
-// first 28 columns of a chunk stay in registers meanwhile, so the matrix is read
-// once for KB * H right-hand sides (from blockIdx.y * KB * H on). In the other
-// block kernels each nonzero reads its row of X through L1, which holds little
-// of it, so that on a stencil the L2s' rate bounds them (27 rows of 64 bytes per
-// row of Y at k = 8, 1.5 GB on 96^3). KB = 4 keeps the window of 256 stencil rows
+// over, and every slot finds its row of X by its 16-bit window position. The
+// first kBlockRegCols columns of a chunk stay in registers meanwhile: they are read
+// once for KB * H right-hand sides (from blockIdx.y * KB * H on), those of wider
+// chunks again in every turn, 10 bytes a slot (block_turns says where that pays). In
+// the other block kernels each nonzero reads its row of X through L1, which holds
+// little of it, so that on a stencil the L2s' rate bounds them (27 rows of 64 bytes
+// per row of Y at k = 8, 1.5 GB on 96^3). KB = 4 keeps the window of 256 stencil rows
 // at 43 KB and three workgroups on a CU; k = 8 takes 90 us there with H = 2, 130
-// with 8 at once (86 KB, one workgroup), 122 in k_spmmv. U = 28 / G steps in
-// flight hold a chunk of the stencil in 76 VGPRs, six waves per SIMD; with 32 it
-// was 82, five waves and 106 us. G = 64 / C lanes share a row,
-// KV = KB / G right-hand sides each; a lane loads one of the G columns of a step,
-// its neighbours get it by a lane move. Per row the products are added in column
-// order and slots holding 0 skip X, as in k_spmmv: the same bits.
+// with 8 at once (86 KB, one workgroup), 122 in k_spmmv. U = kBlockRegCols / G steps
+// in flight hold a chunk of the stencil in 76 VGPRs, six waves per SIMD; with 32 it
+// was 82, five waves and 106 us. G = 64 / C lanes share a row, KV = KB / G right-hand
+// sides each; a lane loads one of the G columns of a step, its neighbours get it by a
+// lane move. Per row the products are added in column order and slots holding 0 skip
+// X, as in k_spmmv: the same bits.
 template <int C, int GC, int KB, int H>
 __global__ void __launch_bounds__(64 * GC) k_spmmv_xw(SpmvArgs a, XwArgs xa) {
   constexpr int G = 64 / C, KV = KB / G;
-  constexpr int U = 28 / G;       // steps of G columns in flight
+  constexpr int U = kBlockRegCols / G;  // steps of G columns in flight
   constexpr int PP = KB / 2;      // pairs of right-hand sides of a window row
   static_assert(KV >= 1 && KB % 2 == 0, "a lane holds at least one right-hand side");
   extern __shared__ __align__(16) unsigned char xw_lds[];
@@ -1357,7 +1358,7 @@ __global__ void __launch_bounds__(64 * GC) k_spmmv_xw(SpmvArgs a, XwArgs xa) {
     };
 #pragma unroll
     for (int u = 0; u < U; ++u) add(vv[u][0], (int)ci[u][0]);
-    constexpr int U2 = 8 / G > 0 ? 8 / G : 1;  // the columns past 28, read once per turn
+    constexpr int U2 = 8 / G > 0 ? 8 / G : 1;  // the columns past those, read once per turn
     for (int s = U; s * G < cl; s += U2) {
       uint16_t c2[U2][1];
       double w2[U2][1];
