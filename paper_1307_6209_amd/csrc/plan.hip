@@ -9,6 +9,7 @@
 // chunks at most 64 / C columns wide are one unit, which one wave covers). A
 // "cell" is such a run, aligned: 64 / C chunks for C in 8..32, else one.
 #include "sell_internal.h"
+#include "xcd_place.h"
 
 namespace sell {
 namespace {
@@ -270,9 +271,8 @@ __global__ void __launch_bounds__(kPlanBlock) k_unit_cols(const Unit1 *__restric
 // One workgroup: the n segments of `segs` to their launch places in `out`.
 // Where most rows of the segments hold entries, in the order of their columns
 // (to kOrderBins bins; inside a bin in any order: a segment's sums have a place
-// of their own, so the results do not depend on it), each XCD an eighth of them:
-// with W units per workgroup, eighth q goes to workgroups q, q + X, q + 2X, ...
-// The last n mod (W * X) follow.
+// of their own, so the results do not depend on it), each XCD an eighth of them
+// (xcd_place).
 constexpr int kOrderBlock = 1024;
 constexpr int kOrderBins = 4096;
 
@@ -318,16 +318,9 @@ __global__ void __launch_bounds__(kOrderBlock) k_order_segs(const Unit1 *__restr
     before += v[k];
   }
   __syncthreads();
-  constexpr int64_t W = kWavesPerBlock, X = kXcds;
-  const int64_t per = n / (W * X) * W;  // segments of an XCD, whole workgroups
   for (int64_t i = tid; i < n; i += kOrderBlock) {
     const int64_t k = atomicAdd(&bin[(int64_t)at[i].col * kOrderBins / ncols], 1);
-    int64_t p = k;
-    if (k < per * X) {
-      const int64_t q = k / per, t = k - q * per;
-      p = (t / W * X + q) * W + t % W;
-    }
-    out[p] = segs[i];
+    out[xcd_place(k, n, kWavesPerBlock, kXcds)] = segs[i];
   }
 }
 
