@@ -219,7 +219,6 @@ void free_owned(sell_matrix *h, bool idle) {
 struct ItemCols {
   std::vector<int32_t> cols;  // per item
   int64_t total_steps = 0;
-  int32_t max = 0;
 };
 
 ItemCols item_cols(const int32_t *cl, int64_t nchunks, const Geom &g) {
@@ -228,7 +227,6 @@ ItemCols item_cols(const int32_t *cl, int64_t nchunks, const Geom &g) {
   for (size_t c = 0; c < (size_t)nchunks; ++c) {
     for (int h = 0; h < g.wpc; ++h) r.cols[c * g.wpc + h] = cl[c];
     r.total_steps += (int64_t)((cl[c] + g.T - 1) / g.T) * g.wpc;
-    r.max = std::max(r.max, cl[c]);
   }
   return r;
 }

@@ -140,9 +140,10 @@ hipError_t launch_spmmv_xw(int C, int kb, int turns, const SpmvArgs &a, const Xw
     hipLaunchKernelGGL((dev::k_spmmv_xw<CC, GG, KK, HH>), nb, dim3(64 * GG), lds, s, a, w);         \
     return hipGetLastError();                                                                       \
   }
-#define SELL_LG(GG, KK, HH) SELL_L(16, GG, KK, HH) SELL_L(32, GG, KK, HH) SELL_L(64, GG, KK, HH)
-  SELL_LG(4, 4, 1) SELL_LG(4, 4, 2) SELL_LG(4, 4, 4) SELL_LG(8, 4, 1) SELL_LG(8, 4, 2) SELL_LG(8, 4, 4)
-  SELL_LG(4, 8, 1) SELL_LG(4, 8, 2) SELL_LG(8, 8, 1) SELL_LG(8, 8, 2)
+#define SELL_LG(CC, KK, HH) SELL_L(CC, 4, KK, HH) SELL_L(CC, 8, KK, HH)
+  SELL_LG(16, 4, 1) SELL_LG(16, 4, 2) SELL_LG(16, 4, 4) SELL_LG(16, 8, 2)
+  SELL_LG(32, 4, 1) SELL_LG(32, 4, 2) SELL_LG(32, 4, 4) SELL_LG(32, 8, 2)
+  SELL_LG(64, 4, 1) SELL_LG(64, 4, 2)
 #undef SELL_LG
 #undef SELL_L
   return hipErrorInvalidValue;

@@ -338,8 +338,8 @@ inline int spmmv_any_lanes(int C, int k, bool local) {
 }
 hipError_t launch_spmmv_any(int C, bool local, const SpmvArgs &a, hipStream_t s);
 // Block form with the x windows in LDS (C 16, 32 or 64, any k; no split chunks):
-// kb right-hand sides at a time (4 or 8), `turns` (1, 2; 4 for kb = 4) times in a
-// launch column (block_turns); lds_bytes: block_window_lds.
+// kb right-hand sides at a time, `turns` times in a launch column, as block_turns
+// says; lds_bytes: block_window_lds.
 hipError_t launch_spmmv_xw(int C, int kb, int turns, const SpmvArgs &a, const XwArgs &w, size_t lds_bytes,
                            hipStream_t s);
 // Product with the x window staged in LDS (C in 8..64, V 1 or 2, no split
