@@ -111,16 +111,19 @@ constexpr int kXcds = 8;
 constexpr int kSegAlign = 64;
 
 // Split segments are placed on the XCDs by their columns from this size of x on
-// (one XCD's L2) and from this share of rows that hold an entry on. Measured in
-// chunk order / by column, us: 4,284 x 1,092,610, 2,633 entries per row, C = 16,
-// 32, 64 (shares 0.95, 0.90, 0.80) 111, 118, 124 / 65, 70, 100 (L2 misses 6.1 M
-// -> 1.6 M lines, of which 1.1 M are the matrix); power-law 2M, sigma = n (0.95)
-// 115 / 111. A row's entries are usually sorted, so a segment reads a range of
-// x, and an eighth of x stays in an L2. Where most of a segment is padding the
-// order of the chunks, whose rows lie near each other, wins: power-law 1M at
-// sigma = 1024 (0.07) 104 / 109, 2M at sigma = 2^14 (0.21) 144 / 159.
+// (one XCD's L2) and from this share of slots that hold an entry on (thin segments
+// count with all rows of the slice). A row's entries are usually sorted, so a
+// segment reads a range of x, and an eighth of x stays in an L2. Measured in chunk
+// order / by column, us (share): 4,284 x 1,092,610, 2,633 entries per row, sigma = n,
+// C = 16, 32, 64 113 / 73 (0.86), 119 / 79 (0.74), 134 / 102 (0.58; L2 misses at C = 16
+// before thin segments 6.1 M -> 1.6 M lines, of which 1.1 M are the matrix), sigma = 512,
+// C = 32 133 / 103 (0.48), 2,000 x 700,000, 600 per row, C = 64 22.0 / 18.2 (0.39);
+// power-law 2M, C = 32, sigma = n, 2^17, 2^16 120 / 111 (0.96), 118 / 113 (0.56),
+// 120 / 118 (0.41). Where most of a segment is padding the order of the chunks, whose
+// rows lie near each other, wins: power-law 2M, C = 64, sigma = 2^17, 2^16 127 / 135
+// (0.37), 129 / 149 (0.24), C = 32, sigma = 2^14, 1024 121 / 133 (0.20), 131 / 140 (0.08).
 constexpr size_t kXcdMinX = 4 << 20;
-constexpr double kXcdMinLive = 0.6;
+constexpr double kXcdMinLive = 0.4;
 // Most segments that one workgroup orders (automatic widths: some 30,000).
 constexpr int64_t kXcdMaxSegs = 1 << 17;
 
