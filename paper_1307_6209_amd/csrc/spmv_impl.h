@@ -570,8 +570,23 @@ __global__ void __launch_bounds__(64 * GC) k_spmv_xw(SpmvArgs a, XwArgs xa) {
   }
 }
 
-// Adds the segment sums of split row slices in segment order and writes y.
-// One wave per split slice.
+// The sum of sixteen values in pairs: four additions in a row instead of sixteen. Fine
+// segments mean many sums per row; added one after another, these outweighed what the
+// short chains inside the segments save (mean error of rows of 3,000 and 20,000 like
+// signs in FP32, segments of seg_cols / finer ones one after another / in pairs, 1e-8:
+// C = 1 3.9, 4.8 / 3.9, 10.4 / 3.9, 4.4; C = 8 4.7, 10.3 / 10.7, 12.1 / 3.8, 4.3; C = 32
+// 8.2, 19.7 / 6.7, 7.2 / 3.7, 4.5).
+template <typename A>
+__device__ __forceinline__ A sum16(A (&t)[16]) {
+#pragma unroll
+  for (int d = 8; d >= 1; d >>= 1)
+#pragma unroll
+    for (int e = 0; e < d; ++e) t[e] += t[e + d];
+  return t[0];
+}
+
+// Adds the segment sums of a split row slice, sixteen at a time, and writes y. One
+// wave per split slice.
 template <int COMBO, int C>
 __device__ __forceinline__ void combine_split(const SplitDesc d, const int32_t *__restrict__ perm,
                                               const void *__restrict__ partial, void *__restrict__ yv,
@@ -585,16 +600,15 @@ __device__ __forceinline__ void combine_split(const SplitDesc d, const int32_t *
   const int64_t p = chunk * C + h * RPW + lane;
   if (p >= nrows) return;
   const A *part = static_cast<const A *>(partial) + d.poff + lane;
-  // sixteen loads in flight, added in order; the last round reads +0 past
-  // the last segment (adding +0 leaves every sum but -0 unchanged, and -0
-  // only turns into +0), so that it too is one round trip
+  // sixteen loads in flight; the last round reads +0 past the last segment
+  // (adding +0 leaves every sum but -0 unchanged, and -0 only turns into +0), so
+  // that it too is one round trip
   A sum = 0;
   for (int q = 0; q < d.nseg; q += 16) {
     A t[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) t[e] = q + e < d.nseg ? part[(int64_t)(q + e) * RPW] : (A)0;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) sum += t[e];
+    sum += sum16(t);
   }
   const int64_t row = perm ? (int64_t)perm[p] : p;
   static_cast<A *>(yv)[row] = sum;
@@ -602,7 +616,7 @@ __device__ __forceinline__ void combine_split(const SplitDesc d, const int32_t *
 
 // The single-vector product's combine: one workgroup per split slice, its
 // G = 512 / rpw groups of threads each adding a run of consecutive segments
-// (sixteen loads in flight), then the G sums added in order. With one wave per
+// (sixteen loads in flight), then the groups' sums in pairs. With one wave per
 // slice the longest slice's segments are one chain of round trips: on 4,284
 // rows of 2,633 entries on average, cut every 64 columns, 37 us.
 constexpr int kCombineBlock = 512;
@@ -624,16 +638,18 @@ __global__ void __launch_bounds__(kCombineBlock) k_combine(SpmvArgs a) {
     A t[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) t[e] = q + e < q1 ? part[(int64_t)(q + e) * RPW] : (A)0;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) sum += t[e];
+    sum += sum16(t);
   }
+  const int ng = (d.nseg + per - 1) / per;  // groups that hold a segment
   part_sum[threadIdx.x] = sum;
-  __syncthreads();
+  for (int half = G / 2; half >= 1; half >>= 1) {
+    if (half >= ng) continue;  // uniform over the block
+    __syncthreads();
+    if (g < half && g + half < ng) part_sum[threadIdx.x] = sum += part_sum[threadIdx.x + half * RPW];
+  }
   const int64_t chunk = d.item / WPC;
   const int64_t p = chunk * C + (d.item - chunk * WPC) * RPW + r;
   if (g != 0 || p >= a.nrows) return;
-  const int ng = (d.nseg + per - 1) / per;  // groups that hold a segment
-  for (int q = 1; q < ng; ++q) sum += part_sum[q * RPW + r];
   static_cast<A *>(a.y)[a.perm ? (int64_t)a.perm[p] : p] = sum;
 }
 
