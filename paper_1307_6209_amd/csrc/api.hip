@@ -244,6 +244,10 @@ int default_vec(int C, sell_dtype v, int64_t nnz, int64_t nrows) {
   return V;
 }
 
+bool keeps_y(const sell_matrix *h) {
+  return sell::keeps_y(h->nrows, dtype_size(h->adt), h->padded, dtype_size(h->vdt), h->beta);
+}
+
 // What a batch plans with, on the host: of each handle its chunk widths and, where
 // it has thin segments of automatic widths, its segments. Gathered on the device,
 // so that the host waits for one copy (64 matrices, sell_batch_create: two copies
@@ -718,6 +722,7 @@ sell_status spmv_run(sell_handle h, const void *x, void *y, void *stream, void *
   sell::SpmvArgs a = args_of(h, x, y);
   if (partial) a.partial = partial;
   a.rl = h->rl;  // row_lengths: each row's lanes stop at its end
+  a.keep_y = keeps_y(h);
   if (h->units1) {
     a.units1 = h->units1;
     a.tcol = h->tcol;
@@ -1237,6 +1242,7 @@ sell_status batch_create_impl(const sell_handle *hs, int32_t count, bool persist
     m.tcol = hs[b]->tcol;
     m.tval = hs[b]->tval;
     m.tslots = hs[b]->tslots;
+    m.keep_y = keeps_y(hs[b]);
   }
 
   // capture the batched launch once

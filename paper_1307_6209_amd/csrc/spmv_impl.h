@@ -142,15 +142,17 @@ __device__ __forceinline__ void opaque(T &v) {
   asm volatile("" : "+v"(v));
 }
 
-// y of the row at sorted position p. Permuted rows are stored one by one, several
-// to a line: the L2 gathers a line's rows (64 power-law matrices, sigma = n,
-// C = 32, before thin segments: 111 us with streaming stores, which leave half of
-// the writes to memory partial, 107 so; 200k, sigma = n 13.1 / 12.0; 50k, sigma = 1024 10.8 / 10.1). Not
-// where y alone would fill the L2s and turn x out: 2M, sigma = 2^14 119 / 121.
+// y of the row at sorted position p; keep: through the L2 (keeps_y), else streamed
+// past it. The empty asm keeps the compiler from joining the two stores into one,
+// which is then a plain one for both.
 template <typename A>
-__device__ __forceinline__ void put_row(A *y, const int32_t *__restrict__ perm, int64_t p, int64_t nrows, A v) {
-  if (perm && nrows <= (int64_t)((8 << 20) / sizeof(A))) y[perm[p]] = v;
-  else __builtin_nontemporal_store(v, y + (perm ? (int64_t)perm[p] : p));
+__device__ __forceinline__ void put_row(A *y, const int32_t *__restrict__ perm, int64_t p, bool keep, A v) {
+  if (perm && keep) {
+    y[perm[p]] = v;
+    asm volatile("");
+  } else {
+    __builtin_nontemporal_store(v, y + (perm ? (int64_t)perm[p] : p));
+  }
 }
 
 // One work unit: columns [jb, je) of the rows [h*rpw, (h+1)*rpw) of a chunk
@@ -173,7 +175,7 @@ __device__ __forceinline__ void spmv_unit(const void *__restrict__ valv, const i
                                           int64_t base, const int32_t *__restrict__ perm,
                                           const void *__restrict__ xv, void *__restrict__ yv, int64_t nrows,
                                           int32_t item, int32_t jb, int32_t je, int64_t part,
-                                          void *__restrict__ partial, int lane,
+                                          void *__restrict__ partial, int lane, bool keep,
                                           const int32_t *__restrict__ rlp = nullptr) {
   constexpr bool RL = ZS == 2;
   using V = typename Types<COMBO>::V;
@@ -306,7 +308,7 @@ __device__ __forceinline__ void spmv_unit(const void *__restrict__ valv, const i
 #pragma unroll
     for (int v = 0; v < VV; ++v) {
       const int64_t p = p0 + v;
-      if (p < nrows) put_row(y, perm, p, nrows, acc[v]);
+      if (p < nrows) put_row(y, perm, p, keep, acc[v]);
     }
     return;
   }
@@ -666,7 +668,7 @@ template <int COMBO, int C>
 __device__ __forceinline__ void spmv_group(const void *__restrict__ valv, const int32_t *__restrict__ col,
                                            int64_t base, int w, const int32_t *__restrict__ perm,
                                            const void *__restrict__ xv, void *__restrict__ yv, int64_t nrows,
-                                           int64_t p) {
+                                           int64_t p, bool keep) {
   using V = typename Types<COMBO>::V;
   using X = typename Types<COMBO>::X;
   using A = typename Types<COMBO>::A;
@@ -690,7 +692,7 @@ __device__ __forceinline__ void spmv_group(const void *__restrict__ valv, const 
   for (int d = T / 2; d >= 1; d >>= 1)
 #pragma unroll
     for (int t = 0; t < d; ++t) s[t] = s[t] + s[t + d];
-  if (p < nrows) put_row(static_cast<A *>(yv), perm, p, nrows, s[0]);
+  if (p < nrows) put_row(static_cast<A *>(yv), perm, p, keep, s[0]);
 }
 
 template <int COMBO, int C, int U, int VV, int ZS>
@@ -707,7 +709,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) k_spmv(SpmvArgs a) {
         const int32_t c = u.item + lane / C;
         const int64_t p = (int64_t)c * C + lane % C;
         spmv_group<COMBO, C>(a.val, a.col, a.cs[c] + lane % C, ZS == 2 ? a.rl[p] : a.cl[c], a.perm, a.x, a.y, a.nrows,
-                             p);
+                             p, a.keep_y);
         return;
       }
     }
@@ -721,7 +723,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) k_spmv(SpmvArgs a) {
     u.je = a.cl[C > 64 ? w / (C / 64) : w];
   }
   spmv_unit<COMBO, C, U, VV, ZS>(a.val, a.col, a.cs[C > 64 ? u.item / (C / 64) : u.item], a.perm, a.x, a.y, a.nrows,
-                                 u.item, u.jb, u.je, u.part, a.partial, lane, a.rl);
+                                 u.item, u.jb, u.je, u.part, a.partial, lane, a.keep_y, a.rl);
 }
 
 // Batched form: one launch over the concatenated work units of all
@@ -756,7 +758,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) k_batch(BatchArgs a) {
         for (int q = 0; q < 64 / C - 1; ++q)
           if (q < g) base += ((uint32_t)u.je >> 4 * q & 15u) * C;
         spmv_group<COMBO, C>(m.val, m.col, base, (int)((uint32_t)u.je >> 4 * g & 15u), m.perm, m.x, m.y, m.nrows,
-                             (int64_t)u.item * C + lane);
+                             (int64_t)u.item * C + lane, m.keep_y);
         continue;
       }
     }
@@ -773,7 +775,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) k_batch(BatchArgs a) {
       }
     }
     spmv_unit<COMBO, C, U, 1, true>(m.val, m.col, u.off, m.perm, m.x, m.y, m.nrows, u.item, u.jb, u.je, u.part,
-                                    a.partial, lane);
+                                    a.partial, lane, m.keep_y);
   }
 }
 
@@ -1223,8 +1225,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) k_spmmv_any(SpmvArgs a, i
       PairA8 o;
       o[0] = acc[p][0];
       o[1] = acc[p][1];
-      if (nseg == 1) __builtin_nontemporal_store(o, reinterpret_cast<PairA8 *>(out + vq[p]));
-      else *reinterpret_cast<PairA8 *>(out + vq[p]) = o;
+      *reinterpret_cast<PairA8 *>(out + vq[p]) = o;  // y and segment sums alike through the L2
     } else if (vq[p] < k) {  // the last of an odd k: the pair started at k - 2
       out[vq[p]] = acc[p][1];
     }
