@@ -96,11 +96,12 @@ inline BlockTurns block_turns(const BlockWindows &b, int k) {
   if (k <= 4) return {4, 1};
   if (k <= 12) {
     // Two turns and four. Past kBlockRegCols columns the others are read again in each,
-    // from 20 waves on a CU on: 125-point 60^3 (w 120, r 5, 12 waves), k = 8, 12:
-    // 157, 228 / 238, 357, 40^3 (16 waves) 52, 94 / 55, 82; three unknowns a node
+    // from 20 waves on a CU on, 24 at C = 16: 125-point 60^3 (w 120, r 5, 12 waves),
+    // k = 8, 12: 157, 228 / 238, 357, 40^3 (16 waves) 52, 94 / 55, 82; 300,000 rows of
+    // up to 90 of 1,000 columns (20 waves) 150, 218 / 190, 278; three unknowns a node
     // of 44^3 (w 79, r 7.8, 28 waves) 122, 178 / 111, 170; 49-point 400^2 at C = 32
     // (w 49, 20 waves) 47, 71 / 35, 53; band of 128 84, 125 / 62, 89.
-    if (b.width > kBlockRegCols && block_waves(b, 4) < 20) return other;
+    if (b.width > kBlockRegCols && block_waves(b, 4) < (b.C == 16 ? 24 : 20)) return other;
     // Small groups need three workgroups a CU: stencil, C = 16, k = 8, 12: 34^3 (615
     // groups) 11, 14 / 12, 15; 38^3 (858) 15, 23 / 13, 16.
     if (b.C == 16 && b.groups < 3 * (int64_t)b.cus) return other;

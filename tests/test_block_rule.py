@@ -23,6 +23,7 @@ MEASURED = {
     "125-point 60^3, C 16": (layout(60**3, 16, 4, 120.3, 1541, 30), [2, 3, 4], [5, 6, 7, 8, 9, 12, 16, 32]),
     "125-point 40^3, C 16": (layout(40**3, 16, 4, 117.9, 1141, 30), [2, 4], [5, 8, 12, 16, 32]),
     "3 unknowns, 44^3, C 16": (layout(3 * 44**3, 16, 4, 78.6, 649, 9), [2, 4, 5, 8, 12], [13, 16, 31, 32]),
+    "300,000 x 1,000, up to 90, C 16": (layout(300_000, 16, 4, 47.0, 1000, 1), [2, 3, 4], [5, 8, 12, 13, 16, 32]),
     "band of 128, C 16": (layout(100_000, 16, 4, 128, 191, 1), [2, 4, 5, 8, 12, 13, 16, 31, 32], [1, 33]),
     "band of 16, C 16": (layout(500_000, 16, 4, 16.0, 79, 1), [2, 8, 12, 13, 20, 28, 31], []),
     "band of 12, C 16": (layout(600_000, 16, 4, 12.0, 75, 1), [2, 8, 12, 16, 24, 32], [13, 20, 28, 31]),
