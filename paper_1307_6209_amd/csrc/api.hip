@@ -756,23 +756,6 @@ extern "C" sell_status sell_spmv(sell_handle h, const void *x, void *y, void *st
 
 namespace {
 
-// Right-hand sides per lane (KV) for the block kernel: a power of two <= 8
-// that divides k (aligned vector gathers), with the pass width G*KV not
-// above the next power of two of k.
-int choose_kv(const sell_matrix *h, int k, int ktile) {
-  const int G = 64 / h->g.rpw;
-  int want;
-  if (ktile > 0) want = std::max(1, ktile / G);
-  else want = (int)std::max<int64_t>(1, std::min<int64_t>(next_pow2(k), 16) / G);
-  int kv = 1;
-  while (kv * 2 <= want && kv * 2 <= 8 && k % (kv * 2) == 0) kv *= 2;
-  return kv;
-}
-
-}  // namespace
-
-namespace {
-
 // Doubles of partial sums a block product of width k needs on handle h with
 // passes of width kt (the one-pass row kernels: kt = k).
 int64_t partial_doubles(const sell_matrix *h, int64_t k, int64_t kt) {
@@ -849,10 +832,10 @@ sell_status spmmv_run(sell_handle h, const void *X, void *Y, int32_t k, void *st
       return SELL_OK;
     }
   }
-  int kv = choose_kv(h, k, h->ktile);
+  int kv = sell::pass_width(h->g.rpw, k, h->ktile);
   // the gathers of KV contiguous right-hand sides and the stores of a lane's
   // KV results are vector accesses: keep them aligned (rows of X and Y are k
-  // doubles apart, k % kv == 0 by choose_kv)
+  // doubles apart, k % kv == 0 by pass_width)
   while (kv > 1 && ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y)) % (sizeof(double) * kv)) != 0)
     kv >>= 1;
   const int KT = (64 / h->g.rpw) * kv;
@@ -866,19 +849,18 @@ sell_status spmmv_run(sell_handle h, const void *X, void *Y, int32_t k, void *st
   a.k = k;
   a.kt = KT;
   hipError_t e;
-  // Automatic width, and the pass kernel would need several passes: one pass
-  // of any width instead. us, pass kernel / one pass, at C = 16, 32, 64:
-  // 200,003 rows of random length up to 48, sigma = 1024: k = 5 156, 152, 259 /
-  // 105, 106, 106; k = 7 168, 236, 399 / 117; k = 12 138 (one pass), 171, 222 /
-  // 148, 147; k = 24 224, 227, 263 / 192. 27-point stencil 96^3: k = 5 280,
-  // 249, 383 / 146, 107, 107; k = 24 473, 576, 733 / 369. Power-law 1M,
-  // sigma = n: k = 5 204, 273, 429 / 115, 118, 124; k = 24 265, 297, 356 / 224,
-  // 239, 246. Whole passes of 16 stay (k = 48 at C = 16 and 32): 255, 240 / 271
-  // on the random rows, whose X then fits the L2s better (383, 422 / 331, 355
-  // on the power-law ones).
-  if (h->ktile == 0 && ntiles > 1 && k <= 64 && !(KT == 16 && k % 16 == 0)) {
+  // Automatic width, and the pass kernel would need several passes: one pass of any
+  // width where that wins. Whole passes of 16 stay as they are (k = 48 at C = 16 and
+  // 32, three passes / one: 200,003 rows of up to 48, whose X then fits the L2s better,
+  // 255, 240 / 271; power-law 1M 383, 422 / 331, 355; no line by the size of X has
+  // been measured).
+  const bool local = h->lcol != nullptr;
+  const int lpr = sell::spmmv_any_lanes(h->C, k, local), np = (k + 2 * lpr - 1) / (2 * lpr);
+  const int64_t longest = h->units ? std::min<int64_t>(h->max_len, h->seg_cols) : h->max_len;
+  if (h->ktile == 0 && ntiles > 1 && k <= 64 && !(KT == 16 && k % 16 == 0) &&
+      sell::one_pass_wins(h->padded, longest, h->g.rpw, lpr, np, kv, (int)ntiles)) {
     a.kt = k;
-    e = sell::launch_spmmv_any(h->C, h->lcol != nullptr, a, static_cast<hipStream_t>(stream));
+    e = sell::launch_spmmv_any(h->C, local, a, static_cast<hipStream_t>(stream));
   } else {
     e = sell::launch_spmmv(h->C, kv, a, static_cast<hipStream_t>(stream));
   }

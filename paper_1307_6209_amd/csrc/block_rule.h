@@ -1,13 +1,12 @@
-// Which layouts and widths of the block product run with the x windows in LDS
-// (k_spmmv_xw). Host code only (no HIP), so that it can be checked on its own.
+// Which kernel a block product runs. No HIP, so that it can be checked on its own.
 //
-// The kernel stages kb right-hand sides of a group's window at a time, `turns`
-// times for one launch column. It wins where a staged element serves many slots
-// and the matrix passes by once; it loses to the kernels that read X through L1
-// and L2 where rows are so short that staging is most of the work, where the
-// columns past kBlockRegCols, read again in each turn, and a large window meet, or
-// where few workgroups run. All figures: us, other kernels / this one, FP64; w: mean
-// chunk width, r: slots per window element.
+// The x windows in LDS (k_spmmv_xw): the kernel stages kb right-hand sides of a group's
+// window at a time, `turns` times for one launch column. It wins where a staged element
+// serves many slots and the matrix passes by once; it loses to the kernels that read X
+// through L1 and L2 where rows are so short that staging is most of the work, where the
+// columns past kBlockRegCols, read again in each turn, and a large window meet, or where
+// few workgroups run. All figures: us, other kernels / this one, FP64; w: mean chunk
+// width, r: slots per window element.
 #pragma once
 
 #include <cstddef>
@@ -108,9 +107,9 @@ inline BlockTurns block_turns(const BlockWindows &b, int k) {
     return {4, k <= 8 ? 2 : 4};
   }
   // Two turns of eight, whole ones (rows of Y end inside a line otherwise, written
-  // by halves): stencil 80^3, C = 32, k = 16, 20, 24, 28, 31, 32: 143, 206, 210, 218, 233, 257 /
-  // 104, 207, 162, 258, 320, 203; or where the window is little more than the group's
-  // rows: band of 40 (r 31) 117, 180, 181, 183, 188, 216 / 58, 114, 91, 139, 172, 114;
+  // by halves): stencil 80^3, C = 32, k = 16, 20, 24, 28, 31, 32: 143, 206, 210, 218,
+  // 233, 257 / 104, 207, 162, 258, 320, 203; or where the window is little more than
+  // the group's rows: band of 40 (r 31) 117, 180, 181, 183, 188, 216 / 58, 114, 91, 139, 172, 114;
   // of 28 (r 25) k = 28, 31: 173, 177 / 172, 215. C = 16, k = 20, 28, 31: band of 16
   // (r 13) 126, 132, 140 / 85, 99, 128; of 12 (r 10) 118, 125, 146 / 96, 114, 150.
   if (k % 8 != 0 && b.reuse < (b.C == 16 ? 12.5 : 30)) return other;
@@ -118,8 +117,59 @@ inline BlockTurns block_turns(const BlockWindows &b, int k) {
   // 125-point 40^3 (8 waves) 79, 138 / 104, 203; stencil 44^3, C = 32 (w 26, 12 waves)
   // 32, 62 / 22, 42; 60^3 (16 waves) 64, 120 / 49, 92.
   const int waves = block_waves(b, 8);
-  if (2 * block_window_lds(8, b.maxwin, b.maxseg) > b.lds || waves < (b.width > kBlockRegCols ? 16 : 12)) return other;
+  if (2 * block_window_lds(8, b.maxwin, b.maxseg) > b.lds) return other;
+  if (waves < (b.width > kBlockRegCols ? 16 : 12)) return other;
   return {8, 2};
+}
+
+// Right-hand sides per lane of the pass kernel: a power of two <= 8 that divides k
+// (aligned vector gathers), with the pass width, 64 / rpw times as many, not above
+// ktile or (0) the next power of two of k, 16 at most.
+inline int pass_width(int rpw, int k, int ktile) {
+  int next = 1;
+  while (next < k && next < 16) next <<= 1;
+  const int most = (ktile > 0 ? ktile : next) / (64 / rpw), want = most > 1 ? most : 1;
+  int kv = 1;
+  while (kv * 2 <= want && kv * 2 <= 8 && k % (kv * 2) == 0) kv *= 2;
+  return kv;
+}
+
+// Lanes per row of the one-pass kernel of any width (k_spmmv_any): no fewer than
+// spread a chunk over a wave. local: neighbouring rows share their columns (the layout
+// has x windows), the X rows come from L1 and L2 and the fewest accesses of a wave per
+// nonzero win (7-point stencil 96^3, k = 5, C = 32: 2 lanes 40 us, 4 lanes 55); else
+// each access of a row is a request of its own beyond L1 and one access per row wins
+// (random rows, k = 5: 2 lanes 123 us, 4 lanes 106), up to k = 16, where 4 lanes with
+// two accesses and 8 with one are even (k = 9: random 148 / 143, power-law 144 / 169).
+inline int spmmv_any_lanes(int C, int k, bool local) {
+  const int least = C < 64 ? 64 / C : 2;
+  const int want = local ? (k <= 8 ? 2 : k <= 16 ? 4 : 8) : (k <= 4 ? 2 : k <= 16 ? 4 : 8);
+  return want > least ? want : least;
+}
+
+// Chunk columns in flight of k_spmmv_any (np pairs of right-hand sides a lane) and of
+// the pass kernel (kv right-hand sides a lane).
+constexpr int any_columns(int lpr, int np) { return np >= 3 ? 3 : np == 2 ? (lpr == 2 ? 8 : 4) : 8; }
+constexpr int pass_columns(int kv) { return kv >= 8 ? 4 : kv >= 4 ? 8 : 12; }
+
+// Whether one pass of any width beats the `passes` (two or more) of the pass kernel,
+// kv right-hand sides a lane. It reads the matrix and the lines of X once, but walks
+// a unit's columns in shorter rounds, while the passes walk them side by side: where
+// the product lasts as long as its longest units, of `longest` columns, it loses.
+// `full` counts how many such units the slots would fill; the shorter its rounds and
+// the fewer the passes, the more of them it takes. us, passes / one pass:
+//   power-law 1M, sigma n, C = 16, 32, 64, k = 5        204, 273, 429 / 115, 118, 124
+//   200,003 rows of up to 48, sigma 1024, k = 5, 24     156, 152, 259 / 106; 224, 227, 263 / 192
+//   27-point stencil 96^3, k = 5, 24 (no windows)       280, 249, 383 / 146, 107, 107; 473, 576, 733 / 369
+//   power-law 50,000, sigma n, C = 8, k = 20 (full 50)  94 / 163
+//   150,000, C = 16, k = 10 (full 170)                  69 / 92
+//   500,000, C = 8, k = 20 (full 520)                   192 / 196
+//   300 x 50,000, 300 per row, C = 16, k = 10 (19)      77 / 146
+inline bool one_pass_wins(int64_t padded, int64_t longest, int rpw, int lpr, int np, int kv, int passes) {
+  const double full = (double)padded / ((double)(longest > 1 ? longest : 1) * rpw);
+  const double ratio = (double)pass_columns(kv) / any_columns(lpr, np), need = (ratio - 1) / (passes - 1);
+  if (need >= 0.55) return full >= 450 * need;
+  return ratio < 2.5 || full >= 32;
 }
 
 }  // namespace sell

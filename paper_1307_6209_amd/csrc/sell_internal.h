@@ -347,19 +347,8 @@ hipError_t launch_spmmv(int C, int KV, const SpmvArgs &a, hipStream_t s);
 // Block form with LPR lanes per row (LPR 4: k = 16; LPR 8: k = 32 or 64;
 // C >= 16): one pass, a.kt == a.k.
 hipError_t launch_spmmv_rows(int C, int LPR, const SpmvArgs &a, hipStream_t s);
-// Block form of any 2 <= k <= 64 in one pass (C in 8..128), a.kt == a.k. Lanes
-// per row, no fewer than spread a chunk over a wave. local: neighbouring rows
-// share their columns (the layout has x windows), the X rows come from L1 and
-// L2 and the fewest accesses of a wave per nonzero win (stencil 96^3, k = 5 at
-// C = 32: 2 lanes 107 us, 4 lanes 145); else each access of a row is a request
-// of its own beyond L1 and one access per row wins (random rows, k = 5: 2 lanes
-// 123, 4 lanes 106), up to k = 16, where 4 lanes with two accesses and 8 with
-// one are even (k = 9: random 148 / 143, power-law 144 / 169).
-inline int spmmv_any_lanes(int C, int k, bool local) {
-  const int least = C < 64 ? 64 / C : 2;
-  const int want = local ? (k <= 8 ? 2 : k <= 16 ? 4 : 8) : (k <= 4 ? 2 : k <= 16 ? 4 : 8);
-  return want > least ? want : least;
-}
+// Block form of any 2 <= k <= 64 in one pass (C in 8..128), a.kt == a.k. local: see
+// spmmv_any_lanes.
 hipError_t launch_spmmv_any(int C, bool local, const SpmvArgs &a, hipStream_t s);
 // Block form with the x windows in LDS (C 16, 32 or 64, any k; no split chunks):
 // kb right-hand sides at a time, `turns` times in a launch column, as block_turns

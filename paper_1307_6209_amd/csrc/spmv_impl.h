@@ -830,7 +830,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) k_spmmv(SpmvArgs a) {
   // twelve against eight for KV <= 2: k = 2 213 -> 225, k = 4 391 -> 409
   // (210 -> 214); sixteen 234 / 112 and 401 / 207; for KV = 4 (k = 8) four
   // 579, six 639, eight 680.
-  constexpr int U = KV >= 8 ? 4 : KV >= 4 ? 8 : 12;
+  constexpr int U = pass_columns(KV);
   using VecT = typename DVec<KV>::type;
 
   const int lane = threadIdx.x & 63;
@@ -1143,7 +1143,7 @@ typedef double PairA8 __attribute__((ext_vector_type(2), aligned(8)));
 template <int LPR, int NP>
 __global__ void __launch_bounds__(64 * kWavesPerBlock) k_spmmv_any(SpmvArgs a, int C, int rpw, int sub) {
   constexpr int RPA = 64 / LPR;                    // rows per wave
-  constexpr int U = NP >= 3 ? 3 : NP == 2 ? (LPR == 2 ? 8 : 4) : 8;
+  constexpr int U = any_columns(LPR, NP);
   const int lane = threadIdx.x & 63;
   const int64_t wv = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   const int64_t w = wv / sub;
