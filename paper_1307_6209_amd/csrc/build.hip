@@ -596,7 +596,8 @@ __global__ void __launch_bounds__(kBlock) k_fill(const int64_t *__restrict__ rpt
   // a tile is read 1 << lr rows at a time, 64 >> lr entries of each, 1 << lj
   // times over; column j of it lies rotated by j << lr rows in LDS, so that
   // the lanes of such a read fall on all banks
-  const int lr = lc < 3 ? lc : 3, lj = 4 + lr - lc > 0 ? 4 + lr - lc : 0;
+  constexpr int lr = 3;
+  const int lj = 7 - lc > 0 ? 7 - lc : 0;
   const int64_t w = (int64_t)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t s0 = w << (rc + lc), range = (int64_t)1 << (rc + lc);
   if (s0 >= padded) return;  // uniform over the wave; no barrier below
@@ -916,9 +917,12 @@ hipError_t build_fill(const int64_t *rpt, const int32_t *col, const double *val,
   const int lc = __builtin_ctz((unsigned)C);
   // small matrices: fewer columns a wave, slots on their own (50,000 rows of up
   // to 20 entries: 32 us with 64 columns in tiles, 21 with the tiles unused but
-  // their LDS taken, 11 so)
+  // their LDS taken, 11 so). C < 8: a wave's columns are fewer slots than a tile
+  // holds, and its chunks, one after another, leave most of the reads' lanes idle
+  // (build of the 27-point stencil 100^3, C = 1, 2, 4: 2,610, 1,398, 817 us with
+  // tiles, 606, 400, 298 without)
   int rc = 6;
-  const bool tiles = padded >> (rc + lc) >= 2048;
+  const bool tiles = lc >= 3 && padded >> (rc + lc) >= 2048;
   while (!tiles && rc > 1 && padded >> (rc + lc) < 8192) --rc;
   const int64_t waves = (padded + ((int64_t)1 << (rc + lc)) - 1) >> (rc + lc);
   const dim3 nb(blocks_for(waves, kBlock / 64));
