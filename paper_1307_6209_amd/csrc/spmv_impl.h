@@ -697,14 +697,18 @@ __device__ __forceinline__ void spmv_group(const void *__restrict__ valv, const 
 
 // UN: the waves take the units of a layout with split chunks; else one item each, in
 // a kernel without the paths of groups and thin segments (with them, unused, 200,003
-// rows of up to 48 columns of 20,000, BF16, C = 32: 37.2 us, without 35.1).
+// rows of up to 48 columns of 20,000, BF16, C = 32: 37.2 us, without 35.1). With UN
+// units1 is never null; the test of it is what keeps the instance at 70 to 76 VGPRs,
+// six waves a SIMD: at 63, eight waves, more units' columns of x are in flight than
+// the L2 holds (power-law 500k, sigma 1024, FP64, C = 64, 128: 33.3, 94.2 us; with
+// it 31.4, 84.5).
 template <int COMBO, int C, int U, int VV, int ZS, bool UN>
 __global__ void __launch_bounds__(64 * kWavesPerBlock) k_spmv(SpmvArgs a) {
   const int lane = threadIdx.x & 63;
   const int64_t w = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   if (w >= a.nwork) return;
   Unit1 u{(int32_t)w, 1, 0, 0, -1, 0, 0};
-  if constexpr (UN) {
+  if (UN && a.units1) {
     u = a.units1[w];
     if constexpr (C >= 8 && C <= 32) {
       if (u.nseg == 0) {  // a group of short chunks
