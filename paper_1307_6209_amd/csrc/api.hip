@@ -245,7 +245,8 @@ int default_vec(int C, sell_dtype v, int64_t nnz, int64_t nrows) {
 }
 
 bool keeps_y(const sell_matrix *h) {
-  return sell::keeps_y(h->nrows, dtype_size(h->adt), h->padded, dtype_size(h->vdt), h->beta);
+  return sell::keeps_y(h->nrows, dtype_size(h->adt), h->ncols, dtype_size(h->xdt), h->padded, dtype_size(h->vdt),
+                       h->beta);
 }
 
 // What a batch plans with, on the host: of each handle its chunk widths and, where

@@ -11,6 +11,7 @@
 
 #include "block_rule.h"
 #include "sellcs.h"
+#include "store_rule.h"
 
 namespace sell {
 
@@ -157,25 +158,6 @@ __host__ __device__ inline int32_t single_seg_cols(int64_t total_steps, int T, i
   const int64_t a = T > 16 ? T : 16;
   cols = (cols + a - 1) / a * a;
   return cols < S ? (int32_t)cols : S;
-}
-
-// Permuted rows of y are stored one by one, several to a line. Through the L2, which
-// gathers a line's rows: where the product is a short one, whose end waits for
-// streaming stores, and on padding-heavy layouts, whose gathers leave room in the L2.
-// Else they turn x out of it and are streamed past it. us, streamed / through the L2:
-//   50,000 rows of up to 48, sigma 1024, C = 16, FP64, FP32     14.9 / 13.7, 13.2 / 11.6
-//   100,000 of up to 24, sigma n, C = 32                        9.6 / 7.8, 8.8 / 7.3
-//   200,003 of up to 12, sigma n, C = 32 (14 MB)                10.5 / 9.0, 9.0 / 7.3
-//   200,003 of up to 48, sigma 1024, C = 16 (46, 31 MB)         49.9 / 50.7, 45.9 / 47.9
-//   the same in BF16 / FP64 (23 MB)                             45.9 / 48.7
-//   power-law 500k, sigma n, C = 16, BF16 / FP64 (13 MB)        18.3 / 19.6
-//   power-law 500k, sigma 1024 (beta 0.14), C = 32              28.4 / 27.6, 22.1 / 21.5
-//   power-law 1M, sigma 1024, C = 32, FP32 (y of 4 MB)          42.9 / 41.8
-//   64 power-law matrices of up to 200,000 rows, sigma n        111 / 106
-//   power-law 2M, sigma 2^14 (y of 16 MB)                       119 / 121
-inline bool keeps_y(int64_t nrows, size_t ysize, int64_t padded, size_t vsize, double beta) {
-  const size_t y = (size_t)nrows * ysize, matrix = (size_t)padded * (vsize + 4);
-  return (y <= (2 << 20) && matrix <= (16 << 20)) || (y <= (8 << 20) && beta < 0.5);
 }
 
 // Thin segments: where at most thin_rows rows of a slice still hold entries the
